@@ -137,11 +137,12 @@ constexpr int kMlpWeights = kMlpHidden * kMlpIn + kMlpHidden + kMlpHidden * kMlp
 void fill_f64(double* p, size_t n, double v, hipStream_t s);
 void fill_f32(float* p, size_t n, float v, hipStream_t s);
 void fill_i32(int* p, size_t n, int v, hipStream_t s);
+void fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s);
 // exclusive scan of n ints; the total goes to *total (device)
 void scan_excl_i32(const int* in, int* out, int64_t n, int* total, hipStream_t s);
-// three scans of n ints in one set of launches; total[0..2] their totals
-void scan3_excl_i32(const int* in0, const int* in1, const int* in2, int* out0, int* out1, int* out2, int64_t n,
-                    int* total, hipStream_t s);
+// na scans of n ints in one set of launches: array j at in + j n, its scan at
+// out + j n, its sum in total[j]
+void scan_excl_i32_n(const int* in, int* out, int na, int64_t n, int* total, hipStream_t s);
 // stable LSD radix sort of (key, value) pairs on key bits [begin_bit, bits)
 void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bits, hipStream_t s, int begin_bit = 0);
 // The same sort, ping-ponging between the caller's buffers (kalt / valt hold
@@ -172,8 +173,6 @@ void tree_split_flags(int b0, int nb, const int* level, const int* count, int m,
 void tree_make_children(int b0, int nb, int child_base, const int* flag, const int* off, const uint64_t* keys,
                         int* level, uint64_t* pixel, int* first, int* count, int* parent, int* child0,
                         int wave_level, hipStream_t s);
-void box_geometry(int nb, const int* level, const uint64_t* pixel, double* cen /*[nb][4]: x,y,z,rho*/,
-                  double* rad, double* gdd /*[nb][8]*/, hipStream_t s);
 void locate_targets(const uint64_t* keys, int64_t m, const int* child0, const int* level, uint64_t* leaf,
                     hipStream_t s);
 // Queued tree levels (device-resident level bounds ls, chunk counts ccnt of
@@ -188,9 +187,11 @@ void tree_init_queued(int* ls, int nls, int* ctl, hipStream_t s);
 void tree_level_queued(int* ls, int L, int* ccnt, int* wpre, int grid, int cgrid, int cap, int* ctl, int m,
                        int split_ok, const uint64_t* keys, int* level, uint64_t* pixel, int* first, int* count,
                        int* parent, int* child0, int wave_level, hipStream_t s);
-void target_ranges(const int* leaf, int64_t m, int nbox, int* tfirst, int* tcount, hipStream_t s);
-void flag_nonzero(const int* count, int n, int* flag, hipStream_t s);
-void compact_index(const int* flag, const int* off, int n, int* out, hipStream_t s);
+// (tcount: the end of each leaf's run until mark_needed makes it a count)
+void target_ranges(const int* leaf, int64_t m, int* tfirst, int* tcount, hipStream_t s);
+// run ends to counts, and need[b] = 1 for every box with a target below it
+// (need starts at 0)
+void mark_needed(const int* tfirst, int nbox, int* tcount, const int* parent, uint8_t* need, hipStream_t s);
 
 // walk
 struct WalkCtx {
@@ -218,9 +219,6 @@ void walk_boxes(int nb, const double* cen, const double* rad, const double* gdd,
 constexpr int64_t kM2LTeam2MinBoxes = 65536;
 inline int m2l_team_width(int64_t n) { return n >= kM2LTeam2MinBoxes ? 2 : 4; }
 constexpr int kM2LTeamF32 = 4;
-// M2L order: boxes of levels <= lc first, then the others; most team rounds
-// first within each part, a round being tw_coarse pairs for the first part
-// and tw_fine for the second (16-bit keys, ties in table order)
 // One walk round in three launches (classify + per-chunk scans, scan of the
 // chunk totals into tot[3]: children pairs, M2L pairs, P2P pairs; emit),
 // sized on the device: st = {frontier size, M2L base, P2P base} of this
@@ -237,8 +235,6 @@ void walk_round_scan(const int2* F, const int* st, const WalkCtx& w, uint8_t* ac
 void walk_round_emit(const int2* F, const int* st, const WalkCtx& w, const uint8_t* action, const int* coff,
                      int cstride, const int* tot, const WalkCaps& cap, int2* Fnext, uint64_t* m2l, uint64_t* p2p,
                      int* st_next, int* overflow, int grid, hipStream_t s);
-void m2l_order_keys(const int* off, const int* level, int lc, int tw_coarse, int tw_fine, int nbox, uint64_t* keys,
-                    uint32_t* vals, hipStream_t s);
 // precision tier: M2L into boxes of levels <= kFp32CoarseLevel stays FP64
 // (the large contributions of coarse boxes nearly cancel on smooth skies,
 // which FP32 rounding would show)
@@ -248,9 +244,77 @@ constexpr int kFp32CoarseLevel = 6;
 // keys, and CSR offsets from the sorted targets
 void pair_split(const uint64_t* sorted, int np, int* src, int* tgt, hipStream_t s);
 void csr_offsets(const int* tgt, int np, int nbox, int* off, hipStream_t s);
-// sort keys (8 bits) putting the boxes with the most work first, in
-// power-of-two buckets; flag the boxes that have any
-void work_order_keys(const long long* work, int n, uint64_t* keys, uint32_t* vals, int* flag, hipStream_t s);
+
+// ---------------------------------------------------------------- plan lists
+// What the list walk reads of a source box.
+struct alignas(64) WalkRec {
+    double x, y, z, r;  // centre, radius
+    double rlo;         // low part of the double-double radius
+    double cp, sp;      // cos, sin of the protected radius
+    int child0, count;
+};
+static_assert(sizeof(WalkRec) == 64, "one aligned segment");
+// centre and scale [nb][4] (x, y, z, rho), radius, double-double forms
+// gdd [nb][8], the walk's records of every box, and hfar: the chord beyond
+// ratio R from the centre (boxes of fewer than min_count particles: 4)
+void box_records(int nb, const int* level, const uint64_t* pixel, const int* child0, const int* count, double c_s,
+                 double c_t, double sigma, double ratio, int min_count, double* cen, double* rad, double* gdd,
+                 WalkRec* rec, double4* ttrig, double* dtrig, double* hfar, hipStream_t s);
+struct GroupCtx {
+    const WalkRec* rec;
+    const double4* ttrig;  // [nb] cos, sin of R and of R / c_t
+    const double* gdd;     // [nb][8]
+    const double* dtrig;   // [nb][kWalkDtrig]
+    const uint8_t* need;   // [nb] boxes with targets below
+    // hand-down list of split box s (children 12 + 4s ..): dcnt[s] entries at
+    // s cd, or at doff[s] (not null: lists of exact size)
+    const int *dlist, *dcnt;
+    const int64_t* doff;
+    int cd;                // room per list without doff
+    double c_s, c_t, sigma;
+};
+struct GroupOut {
+    int *mcnt, *pcnt, *tflag, *nflag;  // [nb] FMM acts, direct acts, leaf with targets, box with targets
+    const int *moff, *poff;            // their CSR offsets (fill)
+    int *msrc, *psrc, *ment;           // sources; ment (may be null): target box of every FMM act
+    int *dlist, *dcnt, *dmax;          // hand-down lists; *dmax: the longest one that did not fit (starts at 0)
+    int dcap;                          // entries of a list that are written
+    int* big;                          // [1 + nb / 4] groups of many pairs: their number, then the groups
+    uint8_t* bigflag;                  // [nb / 4]
+};
+// split boxes of one level (boxes box0 .. box1 - 1): hand-down lists and FMM act counts
+void group_walk_level(const GroupCtx& w, const GroupOut& o, int box0, int box1, hipStream_t s);
+// leaves with targets: act counts (and the counts and flags of all other boxes)
+void group_walk_count(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t s);
+void group_walk_fill(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t s);
+// the leaves with targets as a list tl, the CSR ends moff[nbox] and
+// poff[nbox], and out[0..5] (host memory): the totals of the four counts,
+// *dmax, and the boxes with targets before box lc1
+void target_leaves(const int* tflag, const int* toff, const int* noff, int nbox, int lc1, const int* tot,
+                   const int* dmax, int* tl, int* moff, int* poff, int* out, hipStream_t s);
+// 8-bit sort keys of the boxes with targets: levels <= lc first, then the
+// others; most team rounds first within each part (tw_coarse or tw_fine pairs
+// a round), so the teams of a wave run the same number of rounds.  The sort is
+// stable: boxes of one round count keep their index order, which is level by
+// level in key order, so the teams of a workgroup are mostly neighbours
+// sharing sources in the cache (3 % less M2L time than ordering by exact
+// list length).
+void m2l_keys(const int* moff, const int* nflag, const int* noff, const int* level, int lc, int tw_coarse,
+              int tw_fine, int nbox, uint64_t* keys, uint32_t* vals, hipStream_t s);
+struct NearCtx {
+    const WalkRec* rec;
+    const uint64_t* pixel;
+    const int *level, *first;
+    const int *tfirst, *tcount;
+    const double *tx, *ty, *tz;
+    const double* hfar;  // [nb] a close leaf farther than this from every target goes through its expansion
+};
+// Direct-act lists praw (CSR poff) of the ntl leaves tl to psrc: entries summed
+// particle by particle first (nn[T] of them), then those taken through their
+// expansion; ordered: both in the order in which Algorithm 1's frontier walk
+// emits them (the second part backwards)
+void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, const int* poff, const int* praw, int* psrc, int* nn,
+                hipStream_t s);
 // ---------------------------------------------------------------- fmm
 struct FmmCtx {
     int p;
@@ -266,6 +330,7 @@ struct FmmCtx {
     double* local;       // [nb][2p+2]
     const double* zrec;  // [2p+2] zeros
     double npm_sigma;    // near-particle model radius (0: point masses)
+    const uint8_t* need; // [nb] boxes whose local expansion is used (null: all)
 };
 // Near-particle model (Epanechnikov profile of radius sigma): with u =
 // |d|^2/4 and t = sin^2(sigma/2), the interior potential is (q/4pi)(log t -
@@ -310,35 +375,36 @@ void lensing_from_hessian(const double* hess, int64_t m, double* out, hipStream_
 void fmm_l2p(const FmmCtx& c, const double* tx, const double* ty, const double* tz, const int* tleaf,
              const uint32_t* tperm, int64_t m, double psi_shift, double* psi, double* defl, int64_t m_out,
              hipStream_t s, double* hess = nullptr);
-// Direct-act lists split into the leaves summed particle by particle (near)
-// and those taken through their multipole expansion (far), both in CSR form
-// by target box, with the work each box gives the two kernels.
-struct NearLists {
-    DVec<int> near_off, near_src, far_off, far_src;  // the src arrays hold np entries' room
-};
-void near_split(const FmmCtx& c, const int* off, const int* src, const int* ent_t, int nbox, int np,
-                const int* tfirst, const int* tcount, const double* tx, const double* ty, const double* tz,
-                NearLists& out, hipStream_t s);
+// the ratio and particle count from which a close leaf is taken through its
+// expansion at order p (kM2PMinOrder up)
+constexpr int kM2PMinOrder = 12;
+double m2p_ratio(int p);
+int m2p_min_count(int p);
 // Near-field work items: segment [y, z) of box x's list, results to the
 // outputs (w < 0) or to partial slots w .. w + tcount[x] - 1; reduce records
 // (box, segments, first slot) for the boxes cut into several segments.
 struct WorkItems {
-    DVec<int4> items, red;
-    DVec<double> part;  // [nslot][4]
+    const int4 *items = nullptr, *red = nullptr;
+    double* part = nullptr;  // [nslot][4]
     int n = 0, nred = 0, nslot = 0;
+};
+// The items of both kinds (direct sums, expansions) in shared buffers
+struct NearWork {
+    DVec<int4> items, red;
+    DVec<double> part;
+    WorkItems near, far;
 };
 constexpr int kSegNear = 128;  // close leaves per direct-sum item
 constexpr int kSegFar = 128;   // close leaves per expansion item
-// Work items of two lists of the same boxes (a and b; seg close leaves per
-// item), with one read-back of the totals; count == nullptr: work counted
-// per entry instead of per particle
-void build_items2(const int* off_a, const int* src_a, const int* count_a, int seg_a, WorkItems& out_a,
-                  const int* off_b, const int* src_b, const int* count_b, int seg_b, WorkItems& out_b,
-                  const int* tcount, int nbox, hipStream_t s);
+// Work items of the ntl leaves tl: the first nn[T] entries of each list (CSR
+// off) in segments of seg_near, the others in segments of seg_far; pin: host
+// memory for 6 totals (one read-back)
+void build_items(const int* tl, int ntl, const int* off, const int* nn, const int* src, const int* count,
+                 const int* tcount, int seg_near, int seg_far, NearWork& out, int* pin, hipStream_t s);
 // per box: pairs[b] = targets x particles of the near leaves, evals[b] =
 // targets x far leaves
-void near_work(const int* count, const NearLists& nl, const int* tcount, int nbox, long long* pairs,
-               long long* evals, hipStream_t s);
+void near_work(const int* count, const int* off, const int* nn, const int* src, const int* tcount, int nbox,
+               long long* pairs, long long* evals, hipStream_t s);
 // fp32: the precision tier's pair arithmetic (two-float coordinates, FP32
 // log / reciprocal, FP64 sums per tile)
 // part: the partial slots of the split boxes ([w.nslot][4] doubles), or

@@ -246,6 +246,14 @@ SFMM_HD BoxGeomDD box_geometry(int level, uint64_t pix) {
     return g;
 }
 
+// Protected radius of a source box (Sec. 3.5): c_s R, widened to R + sigma
+// under the near-particle model so that a particle's whole profile lies
+// inside it.
+SFMM_HD double protected_radius(double r, double c_s, double sigma) {
+    const double p = c_s * r;
+    return (sigma > 0.0 && r + sigma > p) ? r + sigma : p;
+}
+
 // "B_T is far from B_S" (Sec. 3.5): d - R_T - c_s R_S > 0 and R_T < c_t d,
 // each by more than the relative tie guard.  FP64 first; double-double when
 // either margin is within kMacFilter of zero.

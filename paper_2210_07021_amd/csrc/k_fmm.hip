@@ -406,6 +406,7 @@ __global__ void __launch_bounds__(128) k_l2l(FmmCtx c, int b0, int nb) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nb) return;
     const int b = b0 + i;
+    if (c.need && !c.need[b]) return;  // no target below: nothing reads this record
     const int par = c.parent[b];
     double rho_t, rho_s;
     const Frame ft = box_frame(c.cen, b, &rho_t);

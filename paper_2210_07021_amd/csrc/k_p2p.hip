@@ -59,7 +59,6 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-constexpr int kM2PMinOrder = 12;
 // A close leaf S is evaluated through its Lemma 1 expansion at the targets
 // of T when every target is beyond ratio R_S from its centre, ratio = 1 / x
 // with the truncation term x^(p+1) at most 1e-4 tau_p (tau_p: the tolerance
@@ -89,138 +88,22 @@ __global__ void k_entry_box(const int* __restrict__ off, int nbox, int np, int* 
     ent_t[k] = lo;
 }
 
-// flag[k] = 1 when entry k goes to the direct sum, 2 when it goes to the
-// multipole evaluation, 0 when its target box holds no target; bnear / bfar
-// count each block's entries of the two kinds.
-constexpr int kNearBlk = 256;
-__global__ void __launch_bounds__(kNearBlk) k_near_flags(FmmCtx c, const int* __restrict__ ent_t,
-                                                         const int* __restrict__ src, int np,
-                                                         const int* __restrict__ tfirst,
-                                                         const int* __restrict__ tcount,
-                                                         const double* __restrict__ tx,
-                                                         const double* __restrict__ ty,
-                                                         const double* __restrict__ tz, double ratio, int min_count,
-                                                         uint8_t* __restrict__ flag, int* __restrict__ bnear,
-                                                         int* __restrict__ bfar) {
-    __shared__ int wn[kNearBlk / 64], wf[kNearBlk / 64];
-    const int k = blockIdx.x * kNearBlk + threadIdx.x;
-    bool is_near = false, is_far = false;
-    if (k < np) {
-        const int T = ent_t[k], S = src[k];
-        const int nt = tcount[T];
-        if (nt > 0 && c.p >= kM2PMinOrder && c.count[S] >= min_count) {
-            // beyond every particle's profile too (near-particle model)
-            const double a = fmax(ratio * c.rad[S], c.rad[S] + c.npm_sigma);
-            if (a < 3.0) {
-                const double* cs = c.cen + 4 * (size_t)S;
-                const double* ct = c.cen + 4 * (size_t)T;
-                // whole box T beyond a + R_T (every point of a box lies within R of its centre)
-                const double b = a + c.rad[T];
-                const double ex = cs[0] - ct[0], ey = cs[1] - ct[1], ez = cs[2] - ct[2];
-                const double d2 = ex * ex + ey * ey + ez * ez;
-                const double hb = 2.0 * sin(0.5 * b);
-                if (b < 3.0 && d2 > hb * hb * (1.0 + 1e-12)) {
-                    is_far = true;
-                } else {
-                    const double h = 2.0 * sin(0.5 * a);
-                    const double thr = h * h;
-                    is_far = true;
-                    const int t0 = tfirst[T];
-                    for (int i = t0; i < t0 + nt; ++i) {
-                        const double dx = tx[i] - cs[0], dy = ty[i] - cs[1], dz = tz[i] - cs[2];
-                        if (!(dx * dx + dy * dy + dz * dz > thr)) {
-                            is_far = false;
-                            break;
-                        }
-                    }
-                }
-            }
-        }
-        is_near = nt > 0 && !is_far;
-        flag[k] = (uint8_t)((is_near ? 1 : 0) | (is_far ? 2 : 0));
-    }
-    const uint64_t mn = __ballot(is_near), mf = __ballot(is_far);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        wn[wave] = __popcll(mn);
-        wf[wave] = __popcll(mf);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int sn = 0, sf = 0;
-        for (int w = 0; w < kNearBlk / 64; ++w) {
-            sn += wn[w];
-            sf += wf[w];
-        }
-        bnear[blockIdx.x] = sn;
-        bfar[blockIdx.x] = sf;
-    }
-}
-
-// Entry k's place in the near and far lists: its block's base (scan of the
-// block counts) plus the entries of its kind before it in the block.  The
-// first entry of each target box also records the two places, which become
-// the box's CSR offsets.
-__global__ void __launch_bounds__(kNearBlk) k_near_scatter(const int* __restrict__ src,
-                                                           const int* __restrict__ ent_t, int np,
-                                                           const uint8_t* __restrict__ flag,
-                                                           const int* __restrict__ bnoff,
-                                                           const int* __restrict__ bfoff, int* __restrict__ near_src,
-                                                           int* __restrict__ far_src, int* __restrict__ first_near,
-                                                           int* __restrict__ first_far) {
-    __shared__ int wn[kNearBlk / 64], wf[kNearBlk / 64];
-    const int k = blockIdx.x * kNearBlk + threadIdx.x;
-    const int f = k < np ? flag[k] : 0;
-    const uint64_t mn = __ballot(f & 1), mf = __ballot(f & 2);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) {
-        wn[wave] = __popcll(mn);
-        wf[wave] = __popcll(mf);
-    }
-    __syncthreads();
-    if (k >= np) return;
-    int pn = bnoff[blockIdx.x], pf = bfoff[blockIdx.x];
-    for (int w = 0; w < wave; ++w) {
-        pn += wn[w];
-        pf += wf[w];
-    }
-    const uint64_t lt = (lane == 0) ? 0ULL : (~0ULL >> (64 - lane));
-    pn += __popcll(mn & lt);
-    pf += __popcll(mf & lt);
-    if (f & 1) near_src[pn] = src[k];
-    if (f & 2) far_src[pf] = src[k];
-    const int T = ent_t[k];
-    if (k == 0 || ent_t[k - 1] != T) {
-        first_near[T] = pn;
-        first_far[T] = pf;
-    }
-}
-
-// CSR offsets of the two lists: box b starts where the entry off[b] of the
-// full list (the first entry of the first non-empty box >= b) would land.
-__global__ void k_near_offsets(const int* __restrict__ off, const int* __restrict__ ent_t, int nbox, int np,
-                               const int* __restrict__ first_near, const int* __restrict__ ntot,
-                               const int* __restrict__ first_far, const int* __restrict__ ftot,
-                               int* __restrict__ near_off, int* __restrict__ far_off) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b > nbox) return;
-    const int k = off[b];
-    near_off[b] = k < np ? first_near[ent_t[k]] : *ntot;
-    far_off[b] = k < np ? first_far[ent_t[k]] : *ftot;
-}
-
 // Work of each box: pairs[T] = tcount[T] * (particles of the near leaves),
 // evals[T] = tcount[T] * (far leaves)
-__global__ void k_near_work(const int* __restrict__ count, const int* __restrict__ near_off,
-                            const int* __restrict__ near_src, const int* __restrict__ far_off,
+__global__ void k_near_work(const int* __restrict__ count, const int* __restrict__ off,
+                            const int* __restrict__ nn, const int* __restrict__ src,
                             const int* __restrict__ tcount, int nbox, long long* __restrict__ pairs,
                             long long* __restrict__ evals) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nbox) return;
     long long ns = 0;
-    for (int k = near_off[b]; k < near_off[b + 1]; ++k) ns += count[near_src[k]];
+    int nf = 0;
+    if (tcount[b] > 0 && off[b + 1] > off[b]) {  // nn is set for these
+        for (int k = off[b]; k < off[b] + nn[b]; ++k) ns += count[src[k]];
+        nf = off[b + 1] - off[b] - nn[b];
+    }
     pairs[b] = ns * (long long)tcount[b];
-    evals[b] = (long long)(far_off[b + 1] - far_off[b]) * (long long)tcount[b];
+    evals[b] = (long long)nf * (long long)tcount[b];
 }
 
 void entry_box(const int* off, int nbox, int np, int* ent_t, hipStream_t s) {
@@ -229,110 +112,79 @@ void entry_box(const int* off, int nbox, int np, int* ent_t, hipStream_t s) {
     SFMM_LAUNCH_CHECK();
 }
 
-void near_split(const FmmCtx& c, const int* off, const int* src, const int* ent_t, int nbox, int np,
-                const int* tfirst, const int* tcount, const double* tx, const double* ty, const double* tz,
-                NearLists& out, hipStream_t s) {
-    out.near_off.resize(nbox + 1);
-    out.far_off.resize(nbox + 1);
-    // every entry goes to at most one of the two lists, so np bounds both:
-    // no read-back of the totals (which stay on the device for the offsets)
-    out.near_src.resize(std::max(np, 1));
-    out.far_src.resize(std::max(np, 1));
+void near_work(const int* count, const int* off, const int* nn, const int* src, const int* tcount, int nbox,
+               long long* pairs, long long* evals, hipStream_t s) {
     if (nbox <= 0) return;
-    const int nb = std::max((np + kNearBlk - 1) / kNearBlk, 1);
-    DVec<uint8_t> flag;
-    DVec<int> bnear, bfar, bnoff, bfoff, first_near, first_far, tot;
-    flag.resize(std::max(np, 1));
-    bnear.resize(nb);
-    bfar.resize(nb);
-    bnoff.resize(nb);
-    bfoff.resize(nb);
-    first_near.resize(nbox);
-    first_far.resize(nbox);
-    tot.resize(2);
-    fill_i32(tot.data(), 2, 0, s);
-    if (np > 0) {
-        k_near_flags<<<nb, kNearBlk, 0, s>>>(c, ent_t, src, np, tfirst, tcount, tx, ty, tz, m2p_ratio(c.p),
-                                             m2p_min_count(c.p), flag.data(), bnear.data(), bfar.data());
-        SFMM_LAUNCH_CHECK();
-        scan_excl_i32(bnear.data(), bnoff.data(), nb, tot.data(), s);
-        scan_excl_i32(bfar.data(), bfoff.data(), nb, tot.data() + 1, s);
-    }
-    if (np > 0) {
-        k_near_scatter<<<nb, kNearBlk, 0, s>>>(src, ent_t, np, flag.data(), bnoff.data(), bfoff.data(),
-                                               out.near_src.data(), out.far_src.data(), first_near.data(),
-                                               first_far.data());
-        SFMM_LAUNCH_CHECK();
-    }
-    k_near_offsets<<<nblk(nbox + 1, 256), 256, 0, s>>>(off, ent_t, nbox, np, first_near.data(), tot.data(),
-                                                       first_far.data(), tot.data() + 1, out.near_off.data(),
-                                                       out.far_off.data());
-    SFMM_LAUNCH_CHECK();
-}
-
-void near_work(const int* count, const NearLists& nl, const int* tcount, int nbox, long long* pairs,
-               long long* evals, hipStream_t s) {
-    if (nbox <= 0) return;
-    k_near_work<<<nblk(nbox, 256), 256, 0, s>>>(count, nl.near_off.data(), nl.near_src.data(), nl.far_off.data(),
-                                                tcount, nbox, pairs, evals);
+    k_near_work<<<nblk(nbox, 256), 256, 0, s>>>(count, off, nn, src, tcount, nbox, pairs, evals);
     SFMM_LAUNCH_CHECK();
 }
 
 // ------------------------------------------------------------ work items
-// Per box b with targets and a non-empty list: nseg = ceil(K / seg) items;
-// boxes cut into several items get nseg * tcount partial slots.
-__global__ void k_seg_count(const int* __restrict__ off, const int* __restrict__ tcount, int nbox, int seg,
-                            int* __restrict__ nseg, int* __restrict__ nslot, int* __restrict__ multi) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbox) return;
-    const int K = off[b + 1] - off[b];
-    const int ns = (tcount[b] > 0 && K > 0) ? (K + seg - 1) / seg : 0;
-    nseg[b] = ns;
-    nslot[b] = ns > 1 ? ns * tcount[b] : 0;
-    multi[b] = ns > 1 ? 1 : 0;
-}
-
-// Items (box, first entry, end entry, partial slot base or -1) and the
-// reduce records (box, nseg, base) of the boxes cut into several segments
-__global__ void k_seg_emit(const int* __restrict__ off, const int* __restrict__ tcount, int nbox, int seg,
-                           const int* __restrict__ nseg, const int* __restrict__ item_off,
-                           const int* __restrict__ slot_off, const int* __restrict__ red_off,
-                           int4* __restrict__ items, int4* __restrict__ red) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbox) return;
-    const int ns = nseg[b];
-    if (ns == 0) return;
-    const int nt = tcount[b];
-    for (int sg = 0; sg < ns; ++sg) {
-        const int kb = off[b] + sg * seg, ke = min(kb + seg, off[b + 1]);
-        items[item_off[b] + sg] = make_int4(b, kb, ke, ns > 1 ? slot_off[b] + sg * nt : -1);
+// Leaf i of the list tl has two lists in one CSR run: nn[T] entries for the
+// direct sum, then the entries for the expansions.  Per kind: ceil(K / seg)
+// items, and for a leaf cut into several of them as many times tcount partial
+// slots and one reduce record.  cnt [6][ntl]: items, slots, reduce records of
+// the first kind, then of the second.
+__global__ void k_item_count(const int* __restrict__ tl, int ntl, const int* __restrict__ off,
+                             const int* __restrict__ nn, const int* __restrict__ tcount, int seg_near, int seg_far,
+                             int* __restrict__ cnt) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ntl) return;
+    const int T = tl[i], n = off[T + 1] - off[T], nt = tcount[T];
+    const int k[2] = {n > 0 ? nn[T] : 0, n > 0 ? n - nn[T] : 0}, seg[2] = {seg_near, seg_far};
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int ns = (k[q] + seg[q] - 1) / seg[q];
+        cnt[(size_t)(3 * q + 0) * ntl + i] = ns;
+        cnt[(size_t)(3 * q + 1) * ntl + i] = ns > 1 ? ns * nt : 0;
+        cnt[(size_t)(3 * q + 2) * ntl + i] = ns > 1 ? 1 : 0;
     }
-    if (ns > 1) red[red_off[b]] = make_int4(b, ns, slot_off[b], 0);
 }
 
-// Sort key of each item: leading zeros of its work, targets x particles (or
-// targets x entries when count is null); heaviest power-of-two bucket first
-// (one wave per item: its lanes sum the particle counts of the segment)
-__global__ void k_item_keys(const int4* __restrict__ items, int n, const int* __restrict__ src,
+// Items (box, first entry, end entry, partial slot base or -1), the direct
+// sums' first, and the reduce records (box, segments, base)
+__global__ void k_item_emit(const int* __restrict__ tl, int ntl, const int* __restrict__ off,
+                            const int* __restrict__ nn, const int* __restrict__ tcount, int seg_near, int seg_far,
+                            const int* __restrict__ pos, int n_near, int red_near, int4* __restrict__ items,
+                            int4* __restrict__ red) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ntl) return;
+    const int T = tl[i], nt = tcount[T], k0 = off[T], k2 = off[T + 1];
+    if (k2 == k0) return;
+    const int k1 = k0 + nn[T];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int ka = q ? k1 : k0, kb = q ? k2 : k1, seg = q ? seg_far : seg_near;
+        const int ns = (kb - ka + seg - 1) / seg;
+        const int at = pos[(size_t)(3 * q) * ntl + i] + (q ? n_near : 0), slot = pos[(size_t)(3 * q + 1) * ntl + i];
+        for (int sg = 0; sg < ns; ++sg)
+            items[at + sg] = make_int4(T, ka + sg * seg, min(ka + (sg + 1) * seg, kb), ns > 1 ? slot + sg * nt : -1);
+        if (ns > 1) red[pos[(size_t)(3 * q + 2) * ntl + i] + (q ? red_near : 0)] = make_int4(T, ns, slot, 0);
+    }
+}
+
+// Sort key of each item: direct sums (the first n_near) before expansions,
+// then by the leading zeros of the work, targets x particles (targets x
+// entries for expansions), heaviest power-of-two bucket first (a wave per
+// item: its lanes sum the particle counts of the segment)
+__global__ void k_item_keys(const int4* __restrict__ items, int n, int n_near, const int* __restrict__ src,
                             const int* __restrict__ count, const int* __restrict__ tcount,
                             uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
     const int i = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (i >= n) return;  // uniform across the wave
     const int4 it = items[i];
-    long long w = 0;
-    if (count) {
+    long long w = it.z - it.y;
+    if (i < n_near) {
         long long part = 0;
         for (int k = it.y + lane; k < it.z; k += 64) part += count[src[k]];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
         w = part;
-    } else {
-        w = it.z - it.y;
     }
     if (lane != 0) return;
     w *= tcount[it.x];
-    keys[i] = (w > 0) ? (uint64_t)__clzll((unsigned long long)w) : 255ULL;
+    keys[i] = (i < n_near ? 0u : 128u) | (w > 0 ? (unsigned)__clzll(w) : 127u);
     vals[i] = (uint32_t)i;
 }
 
@@ -342,71 +194,50 @@ __global__ void k_gather_items(const int4* __restrict__ in, const uint32_t* __re
     if (i < n) out[i] = in[idx[i]];
 }
 
-namespace {
-// The two halves of building one list's work items around the read-back of
-// its three totals (items, partial slots, reduce records), so that two lists
-// can share one read-back.
-struct ItemCounts {
-    DVec<int> nseg, nslot, multi, item_off, slot_off, red_off;
-};
-
-void items_count(const int* off, const int* tcount, int nbox, int seg, ItemCounts& t, int* tot, hipStream_t s) {
-    t.nseg.resize(nbox);
-    t.nslot.resize(nbox);
-    t.multi.resize(nbox);
-    t.item_off.resize(nbox);
-    t.slot_off.resize(nbox);
-    t.red_off.resize(nbox);
-    k_seg_count<<<nblk(nbox, 256), 256, 0, s>>>(off, tcount, nbox, seg, t.nseg.data(), t.nslot.data(),
-                                                t.multi.data());
+void build_items(const int* tl, int ntl, const int* off, const int* nn, const int* src, const int* count,
+                 const int* tcount, int seg_near, int seg_far, NearWork& out, int* pin, hipStream_t s) {
+    out.near = WorkItems();
+    out.far = WorkItems();
+    if (ntl <= 0) return;
+    DVec<int> cnt, pos;
+    cnt.resize(6 * (size_t)ntl);
+    pos.resize(6 * (size_t)ntl);
+    k_item_count<<<nblk(ntl, 256), 256, 0, s>>>(tl, ntl, off, nn, tcount, seg_near, seg_far, cnt.data());
     SFMM_LAUNCH_CHECK();
-    scan3_excl_i32(t.nseg.data(), t.nslot.data(), t.multi.data(), t.item_off.data(), t.slot_off.data(),
-                   t.red_off.data(), nbox, tot, s);
-}
-
-void items_emit(const int* off, const int* src, const int* count, const int* tcount, int nbox, int seg,
-                const ItemCounts& t, const int* h, WorkItems& out, hipStream_t s) {
-    out.n = h[0];
-    out.nslot = h[1];
-    out.nred = h[2];
-    out.items.resize(std::max(out.n, 1));
-    out.red.resize(std::max(out.nred, 1));
-    out.part.resize(4 * (size_t)std::max(out.nslot, 1));
-    if (out.n == 0) return;
+    scan_excl_i32_n(cnt.data(), pos.data(), 6, ntl, pin, s);
+    SFMM_HIP(hipStreamSynchronize(s));
+    const int n_near = pin[0], n = pin[0] + pin[3], red_near = pin[2];
+    out.items.resize(std::max(n, 1));
+    out.red.resize(std::max(pin[2] + pin[5], 1));
+    out.part.resize(4 * (size_t)std::max(pin[1] + pin[4], 1));
+    out.near.items = out.items.data();
+    out.near.red = out.red.data();
+    out.near.part = out.part.data();
+    out.near.n = pin[0];
+    out.near.nslot = pin[1];
+    out.near.nred = pin[2];
+    out.far.items = out.items.data() + n_near;
+    out.far.red = out.red.data() + red_near;
+    out.far.part = out.part.data() + 4 * (size_t)pin[1];
+    out.far.n = pin[3];
+    out.far.nslot = pin[4];
+    out.far.nred = pin[5];
+    if (n == 0) return;
     DVec<int4> raw;
     DVec<uint64_t> keys;
     DVec<uint32_t> vals;
-    raw.resize(out.n);
-    keys.resize(out.n);
-    vals.resize(out.n);
-    k_seg_emit<<<nblk(nbox, 256), 256, 0, s>>>(off, tcount, nbox, seg, t.nseg.data(), t.item_off.data(),
-                                               t.slot_off.data(), t.red_off.data(), raw.data(), out.red.data());
+    raw.resize(n);
+    keys.resize(n);
+    vals.resize(n);
+    k_item_emit<<<nblk(ntl, 256), 256, 0, s>>>(tl, ntl, off, nn, tcount, seg_near, seg_far, pos.data(), n_near,
+                                               red_near, raw.data(), out.red.data());
     SFMM_LAUNCH_CHECK();
-    k_item_keys<<<nblk(64 * (int64_t)out.n, 256), 256, 0, s>>>(raw.data(), out.n, src, count, tcount, keys.data(),
-                                                             vals.data());
+    k_item_keys<<<nblk(64 * (int64_t)n, 256), 256, 0, s>>>(raw.data(), n, n_near, src, count, tcount, keys.data(),
+                                                           vals.data());
     SFMM_LAUNCH_CHECK();
-    radix_sort_u64(keys.data(), vals.data(), out.n, 8, s);
-    k_gather_items<<<nblk(out.n, 256), 256, 0, s>>>(raw.data(), vals.data(), out.n, out.items.data());
+    radix_sort_u64(keys.data(), vals.data(), n, 8, s);
+    k_gather_items<<<nblk(n, 256), 256, 0, s>>>(raw.data(), vals.data(), n, out.items.data());
     SFMM_LAUNCH_CHECK();
-}
-}  // namespace
-
-void build_items2(const int* off_a, const int* src_a, const int* count_a, int seg_a, WorkItems& out_a,
-                  const int* off_b, const int* src_b, const int* count_b, int seg_b, WorkItems& out_b,
-                  const int* tcount, int nbox, hipStream_t s) {
-    out_a.n = out_a.nred = out_a.nslot = 0;
-    out_b.n = out_b.nred = out_b.nslot = 0;
-    if (nbox <= 0) return;
-    ItemCounts ta, tb;
-    DVec<int> tot;
-    tot.resize(6);
-    items_count(off_a, tcount, nbox, seg_a, ta, tot.data(), s);
-    items_count(off_b, tcount, nbox, seg_b, tb, tot.data() + 3, s);
-    int h[6];
-    SFMM_HIP(hipMemcpyAsync(h, tot.data(), sizeof(h), hipMemcpyDeviceToHost, s));
-    SFMM_HIP(hipStreamSynchronize(s));
-    items_emit(off_a, src_a, count_a, tcount, nbox, seg_a, ta, h, out_a, s);
-    items_emit(off_b, src_b, count_b, tcount, nbox, seg_b, tb, h + 3, out_b, s);
 }
 
 // Adds the per-segment results of every box cut into several items, in
@@ -960,10 +791,10 @@ void reduce_items(const WorkItems& w, const int* tfirst, const int* tcount, cons
                   double* defl, int64_t m_out, double* part, hipStream_t s, double* hess) {
     if (w.nred <= 0) return;
     if (hess)
-        k_near_reduce<true><<<(unsigned)w.nred, 64, 0, s>>>(w.red.data(), tfirst, tcount, tperm, part, psi, defl,
+        k_near_reduce<true><<<(unsigned)w.nred, 64, 0, s>>>(w.red, tfirst, tcount, tperm, part, psi, defl,
                                                             hess, m_out);
     else
-        k_near_reduce<false><<<(unsigned)w.nred, 64, 0, s>>>(w.red.data(), tfirst, tcount, tperm, part, psi, defl,
+        k_near_reduce<false><<<(unsigned)w.nred, 64, 0, s>>>(w.red, tfirst, tcount, tperm, part, psi, defl,
                                                              nullptr, m_out);
     SFMM_LAUNCH_CHECK();
 }
@@ -973,11 +804,11 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
              double* psi, double* defl, int64_t m_out, hipStream_t s, double* part, double* hess) {
     if (w.n <= 0) return;
     if (hess && !part && w.nred > 0) throw Error(ST_INTERNAL, "the Hessian needs partial slots of 8 doubles");
-    if (!part) part = w.part.data();
+    if (!part) part = w.part;
     const NpmK nk = npm_params(c.npm_sigma);
     const bool npm = c.npm_sigma > 0.0;
 #define P2P_(T, H, N)                                                                                          \
-    k_p2p<T, H, N><<<(unsigned)w.n, 64, 0, s>>>(c, w.items.data(), src, tfirst, tcount, tx, ty, tz, tperm, psi, \
+    k_p2p<T, H, N><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
                                                 defl, m_out, part, kLogPoly, hess, nk)
 #define P2P_N(T, H)              \
     if (npm) P2P_(T, H, true);   \
@@ -1000,14 +831,14 @@ void fmm_m2p(const FmmCtx& c, const WorkItems& w, const int* src, const int* tfi
              double* defl, int64_t m_out, hipStream_t s, double* part, double* hess) {
     if (w.n <= 0 || c.p < kM2PMinOrder) return;
     if (hess && !part && w.nred > 0) throw Error(ST_INTERNAL, "the Hessian needs partial slots of 8 doubles");
-    if (!part) part = w.part.data();
+    if (!part) part = w.part;
 #define L_(P)                                                                                                 \
     case P:                                                                                                   \
         if (hess)                                                                                             \
-            k_m2p<P, true><<<(unsigned)w.n, 64, 0, s>>>(c, w.items.data(), src, tfirst, tcount, tx, ty, tz,  \
+            k_m2p<P, true><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz,  \
                                                         tperm, psi, defl, m_out, part, hess);                 \
         else                                                                                                  \
-            k_m2p<P, false><<<(unsigned)w.n, 64, 0, s>>>(c, w.items.data(), src, tfirst, tcount, tx, ty, tz, \
+            k_m2p<P, false><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, \
                                                          tperm, psi, defl, m_out, part, nullptr);             \
         break;
     SFMM_DISPATCH(c.p, L_)

@@ -386,39 +386,7 @@ void tree_level_queued(int* ls, int L, int* ccnt, int* wpre, int grid, int cgrid
     SFMM_LAUNCH_CHECK();
 }
 
-// ------------------------------------------------------------------ geometry
-__global__ void k_box_geometry(int nb, const int* level, const uint64_t* pixel, double* cen, double* rad,
-                               double* gdd) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    const BoxGeomDD g = box_geometry(level[b], pixel[b]);
-    cen[4 * b + 0] = g.c[0].hi;
-    cen[4 * b + 1] = g.c[1].hi;
-    cen[4 * b + 2] = g.c[2].hi;
-    cen[4 * b + 3] = tan(0.5 * g.r.hi);  // coefficient scale rho
-    rad[b] = g.r.hi;
-    double* o = gdd + 8 * b;
-    o[0] = g.c[0].hi; o[1] = g.c[0].lo;
-    o[2] = g.c[1].hi; o[3] = g.c[1].lo;
-    o[4] = g.c[2].hi; o[5] = g.c[2].lo;
-    o[6] = g.r.hi;    o[7] = g.r.lo;
-}
-
-void box_geometry(int nb, const int* level, const uint64_t* pixel, double* cen, double* rad, double* gdd,
-                  hipStream_t s) {
-    if (nb <= 0) return;
-    k_box_geometry<<<nblocks(nb, 128), 128, 0, s>>>(nb, level, pixel, cen, rad, gdd);
-    SFMM_LAUNCH_CHECK();
-}
-
-// Protected radius of a source box (Sec. 3.5): c_s R, widened to R + sigma
-// under the near-particle model so that a particle's whole profile lies
-// inside it.  FP64 and double-double forms.
-__device__ __forceinline__ double protected_radius(double r, double c_s, double sigma) {
-    const double p = c_s * r;
-    return (sigma > 0.0 && r + sigma > p) ? r + sigma : p;
-}
-
+// ------------------------------------------------------------------ walk records
 __global__ void k_walk_boxes(int nb, const double* cen, const double* rad, const double* gdd, const int* child0,
                              const int* count, double c_s, double c_t, double sigma, double4* geo, double2* strig,
                              double4* ttrig, int2* cc, double* dtrig) {
@@ -482,9 +450,9 @@ void locate_targets(const uint64_t* keys, int64_t m, const int* child0, const in
     SFMM_LAUNCH_CHECK();
 }
 
-// Targets in plan order: each leaf's targets form one run.  The run's first target
-// writes tfirst, its last one the end index into tcount; k_range_counts turns
-// the end into a count (tcount starts at 0, so empty leaves stay 0).
+// Targets in plan order: each leaf's targets form one run.  The run's first
+// target writes tfirst, its last one the end index into tcount (mark_needed
+// turns the end into a count; tcount starts at 0, so empty leaves stay 0).
 __global__ void k_target_ranges(const int* leaf, int64_t m, int* tfirst, int* tcount) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= m) return;
@@ -493,38 +461,9 @@ __global__ void k_target_ranges(const int* leaf, int64_t m, int* tfirst, int* tc
     if (i == m - 1 || leaf[i + 1] != b) tcount[b] = (int)(i + 1);
 }
 
-__global__ void k_range_counts(const int* tfirst, int nbox, int* tcount) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nbox && tcount[b] > 0) tcount[b] -= tfirst[b];
-}
-
-void target_ranges(const int* leaf, int64_t m, int nbox, int* tfirst, int* tcount, hipStream_t s) {
+void target_ranges(const int* leaf, int64_t m, int* tfirst, int* tcount, hipStream_t s) {
     if (m <= 0) return;
     k_target_ranges<<<nblocks(m, 256), 256, 0, s>>>(leaf, m, tfirst, tcount);
-    SFMM_LAUNCH_CHECK();
-    k_range_counts<<<nblocks(nbox, 256), 256, 0, s>>>(tfirst, nbox, tcount);
-    SFMM_LAUNCH_CHECK();
-}
-
-__global__ void k_flag_nonzero(const int* count, int n, int* flag) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) flag[i] = count[i] > 0 ? 1 : 0;
-}
-
-void flag_nonzero(const int* count, int n, int* flag, hipStream_t s) {
-    if (n <= 0) return;
-    k_flag_nonzero<<<nblocks(n, 256), 256, 0, s>>>(count, n, flag);
-    SFMM_LAUNCH_CHECK();
-}
-
-__global__ void k_compact_index(const int* flag, const int* off, int n, int* out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && flag[i]) out[off[i]] = i;
-}
-
-void compact_index(const int* flag, const int* off, int n, int* out, hipStream_t s) {
-    if (n <= 0) return;
-    k_compact_index<<<nblocks(n, 256), 256, 0, s>>>(flag, off, n, out);
     SFMM_LAUNCH_CHECK();
 }
 
@@ -850,46 +789,6 @@ void pair_split(const uint64_t* sorted, int np, int* src, int* tgt, hipStream_t 
 
 void csr_offsets(const int* tgt, int np, int nbox, int* off, hipStream_t s) {
     k_csr_offsets<<<nblocks(nbox + 1, 256), 256, 0, s>>>(tgt, np, nbox, off);
-    SFMM_LAUNCH_CHECK();
-}
-
-// M2L order keys: boxes of levels <= lc first (bit 15 clear), then the rest;
-// most team rounds (tw_coarse or tw_fine pairs a round) first within each
-// part, so the teams of a wave run the same number of rounds.  The sort is
-// stable: boxes of one round count keep their index order, which is level by
-// level in key order, so the teams of a workgroup are mostly neighbours
-// sharing sources in the cache (3 % less M2L time than ordering by exact
-// list length).
-__global__ void k_m2l_order_keys(const int* off, const int* level, int lc, int tw_coarse, int tw_fine, int nbox,
-                                 uint64_t* keys, uint32_t* vals) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nbox) return;
-    const bool fine = level[b] > lc;
-    const int tw = fine ? tw_fine : tw_coarse;
-    const uint32_t rounds = (uint32_t)(off[b + 1] - off[b] + tw - 1) / (uint32_t)tw;
-    keys[b] = ((uint64_t)fine << 15) | (uint64_t)(0x7fffu - (rounds < 0x7fffu ? rounds : 0x7fffu));
-    vals[b] = (uint32_t)b;
-}
-
-void m2l_order_keys(const int* off, const int* level, int lc, int tw_coarse, int tw_fine, int nbox, uint64_t* keys,
-                    uint32_t* vals, hipStream_t s) {
-    if (nbox <= 0) return;
-    k_m2l_order_keys<<<nblocks(nbox, 256), 256, 0, s>>>(off, level, lc, tw_coarse, tw_fine, nbox, keys, vals);
-    SFMM_LAUNCH_CHECK();
-}
-
-__global__ void k_work_order_keys(const long long* work, int n, uint64_t* keys, uint32_t* vals, int* flag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
-    const unsigned long long v = (unsigned long long)work[b];
-    keys[b] = (v == 0) ? 255ULL : (uint64_t)__clzll(v);
-    vals[b] = (uint32_t)b;
-    flag[b] = v > 0 ? 1 : 0;
-}
-
-void work_order_keys(const long long* work, int n, uint64_t* keys, uint32_t* vals, int* flag, hipStream_t s) {
-    if (n <= 0) return;
-    k_work_order_keys<<<nblocks(n, 256), 256, 0, s>>>(work, n, keys, vals, flag);
     SFMM_LAUNCH_CHECK();
 }
 

@@ -186,6 +186,12 @@ void fill_i32(int* p, size_t n, int v, hipStream_t s) {
     SFMM_LAUNCH_CHECK();
 }
 
+void fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s) {
+    if (!n) return;
+    k_fill<uint8_t><<<grid_for(n, 256), 256, 0, s>>>(p, n, v);
+    SFMM_LAUNCH_CHECK();
+}
+
 // ------------------------------------------------------------------ scan
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
@@ -242,19 +248,15 @@ __global__ void k_scan_add(int* out, int64_t n, const int* boff) {
         if (base + k < n) out[base + k] += add;
 }
 
-// Three scans of n ints at once (blockIdx.y picks the array): the same tile
-// scan / block-sum scan / add-back as scan_excl_i32, a third of the launches.
-struct Scan3 {
-    const int* in[3];
-    int* out[3];
-    int* aux[3];  // tile sums (or the totals, with a single tile)
-};
-
-__global__ void k_scan_tiles3(Scan3 a, int64_t n) {
+// na scans of n ints at once (blockIdx.y picks the array): the same tile scan
+// / block-sum scan / add-back as scan_excl_i32 in one set of launches.  Array j
+// lies at in + j n and its scan at out + j n; total[j] is its sum.  aux holds
+// the tile sums (or the totals, with a single tile), au apart.
+__global__ void k_scan_tiles_n(const int* __restrict__ in, int* __restrict__ out, int64_t n, int* aux, int64_t au) {
     __shared__ int sh[kScanThreads / 64];
     const int j = blockIdx.y;
-    const int* in = a.in[j];
-    int* out = a.out[j];
+    in += j * n;
+    out += j * n;
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int v[kScanItems];
     int s = 0;
@@ -270,39 +272,35 @@ __global__ void k_scan_tiles3(Scan3 a, int64_t n) {
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
-    if (threadIdx.x == 0) a.aux[j][blockIdx.x] = tot;
+    if (threadIdx.x == 0) aux[j * au + blockIdx.x] = tot;
 }
 
-__global__ void k_scan_add3(Scan3 a, int64_t n) {
+__global__ void k_scan_add_n(int* out, int64_t n, const int* boff, int64_t nb) {
     const int j = blockIdx.y;
-    int* out = a.out[j];
+    out += j * n;
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    const int add = a.aux[j][blockIdx.x];
+    const int add = boff[j * nb + blockIdx.x];
     for (int k = threadIdx.x; k < kScanTile; k += kScanThreads)
         if (base + k < n) out[base + k] += add;
 }
 
-void scan3_excl_i32(const int* in0, const int* in1, const int* in2, int* out0, int* out1, int* out2, int64_t n,
-                    int* total, hipStream_t s) {
+void scan_excl_i32_n(const int* in, int* out, int na, int64_t n, int* total, hipStream_t s) {
     if (n <= 0) {
-        fill_i32(total, 3, 0, s);
+        fill_i32(total, na, 0, s);
         return;
     }
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    Scan3 a{{in0, in1, in2}, {out0, out1, out2}, {total, total + 1, total + 2}};
     if (nb == 1) {
-        k_scan_tiles3<<<dim3(1, 3), kScanThreads, 0, s>>>(a, n);
+        k_scan_tiles_n<<<dim3(1, na), kScanThreads, 0, s>>>(in, out, n, total, 1);
         SFMM_LAUNCH_CHECK();
         return;
     }
-    int* bsum = (int*)pool_alloc(sizeof(int) * 3 * nb);
-    int* boff = (int*)pool_alloc(sizeof(int) * 3 * nb);
-    for (int j = 0; j < 3; ++j) a.aux[j] = bsum + j * nb;
-    k_scan_tiles3<<<dim3((unsigned)nb, 3), kScanThreads, 0, s>>>(a, n);
+    int* bsum = (int*)pool_alloc(sizeof(int) * na * nb);
+    int* boff = (int*)pool_alloc(sizeof(int) * na * nb);
+    k_scan_tiles_n<<<dim3((unsigned)nb, na), kScanThreads, 0, s>>>(in, out, n, bsum, nb);
     SFMM_LAUNCH_CHECK();
-    scan3_excl_i32(bsum, bsum + nb, bsum + 2 * nb, boff, boff + nb, boff + 2 * nb, nb, total, s);
-    for (int j = 0; j < 3; ++j) a.aux[j] = boff + j * nb;
-    k_scan_add3<<<dim3((unsigned)nb, 3), kScanThreads, 0, s>>>(a, n);
+    scan_excl_i32_n(bsum, boff, na, nb, total, s);
+    k_scan_add_n<<<dim3((unsigned)nb, na), kScanThreads, 0, s>>>(out, n, boff, nb);
     SFMM_LAUNCH_CHECK();
     // freed blocks are only reused by later stream-ordered work on this stream
     pool_free(bsum);

@@ -116,19 +116,32 @@ struct sfmm_plan_impl {
     DVec<int> level, first, count, parent, child0;
     DVec<uint64_t> pixel;
     DVec<double> cen, rad, gdd;
-    // interaction lists in CSR form by target box
-    int n_m2l = 0, n_p2p = 0;
-    DVec<int> m2l_off, m2l_src, p2p_off, p2p_src, m2l_order;
+    // interaction lists in CSR form by target box: the boxes with targets
+    // below them (need) only
+    DVec<uint8_t> need;
+    int n_m2l = 0;
+    DVec<int> m2l_off, m2l_src, m2l_order;
+    int n_order = 0;     // boxes in m2l_order (those with targets)
     int n_m2l_fp64 = 0;  // the first n_m2l_fp64 boxes of m2l_order take the FP64 M2L
+    int lc = 29;         // last FP64 level (the precision tier's; 29: every box)
+    // Algorithm 1's lists of every box, made when the exports or the
+    // statistics ask
+    struct FullLists {
+        bool ready = false;
+        int n_m2l = 0, n_p2p = 0;
+        DVec<int> m2l_off, m2l_src, m2l_ent, p2p_off, p2p_src;
+    } full;
     // targets, sorted by key
     DVec<double> tx, ty, tz;
     DVec<uint32_t> tperm;
     DVec<uint64_t> tkeys;
     DVec<int> tleaf, tfirst, tcount;
     mutable int ntl = -1;  // leaves with targets and direct-sum work (counted when the statistics ask)
-    // direct-act lists split into direct sums and multipole evaluations
-    NearLists nl;
-    WorkItems near_items, far_items;
+    // direct-act lists of the leaves with targets (tl), in one CSR: nn[T]
+    // entries summed directly, then those taken through their expansions
+    int ntl_all = 0;
+    DVec<int> tl, p2p_off, p2p_src, nn;
+    NearWork work;
     mutable long long n_p2p_pairs = -1, n_m2p_evals = -1;  // summed on the first stats request
     // expansions
     DVec<double> mult, local;
@@ -137,14 +150,14 @@ struct sfmm_plan_impl {
     DVec<double> hess_part;  // partial slots of 8 doubles (sfmm_execute_hessian)
     // per-pair order policies
     DVec<int> m2l_ent;        // target box of every FMM-act entry (per-pair order policies)
-    DVec<int> p2p_ent;        // target box of every direct-act entry (until the near-field split)
     DVec<float> mlp_w;        // order network (learned policy)
     DVec<float4> decay;       // per-box multipole decay features
     DVec<uint8_t> m2l_ord;    // order of every FMM act (last execute)
     DVec<int> ord_off, ord_src;  // FMM acts split by order
-    // sum of p'^2 over the FMM acts of the last execute; -1: still in osq_dev
-    mutable long long m2l_order_sq = 0;
-    DVec<long long> osq_dev;
+    // sum of p'^2 over Algorithm 1's FMM acts at the last execute's orders; -1:
+    // not summed yet (done when the statistics ask)
+    long long m2l_order_sq = -1;
+    bool ran_policy = false;  // the last execute used the per-pair orders
     bool executed = false;
     // judge of the per-pair order policies (first execute of the plan)
     bool judged = false, judge_failed = false;
@@ -186,8 +199,10 @@ struct sfmm_plan_impl {
         c.local = local.data();
         c.zrec = zrec.data();
         c.npm_sigma = opt.npm_sigma;
+        c.need = need.data();
         return c;
     }
+    bool tier() const { return n_m2l_fp64 < n_order; }  // some boxes take the FP32 M2L
 };
 
 namespace {
@@ -338,11 +353,6 @@ void build_tree(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     if (!build_levels_queued(P, m, (int)cap, s)) build_levels_exact(P, m, s);
     prof.end(stage_tree);
     P.nbox = P.lvl_start.back();
-    P.cen.resize(4 * (size_t)P.nbox);
-    P.rad.resize(P.nbox);
-    P.gdd.resize(8 * (size_t)P.nbox);
-    StageScope st(prof, S_GEOM);
-    box_geometry(P.nbox, P.level.data(), P.pixel.data(), P.cen.data(), P.rad.data(), P.gdd.data(), s);
 }
 
 // Stable sort on the target field only: within one target the pairs keep the
@@ -479,8 +489,11 @@ bool walk(sfmm_plan_impl& P, const WalkCtx& w, bool exact, DVec<uint64_t>& m2l, 
     return true;
 }
 
-void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
-    const int stage_walk = prof.begin(S_WALK);
+// Algorithm 1's lists of every box (exports, statistics): the frontier walk
+// and a stable sort of its pairs by target.
+void ensure_full(sfmm_plan_impl& P, hipStream_t s) {
+    auto& F = P.full;
+    if (F.ready) return;
     DVec<double4> geo, ttrig;
     DVec<double2> strig;
     DVec<int2> cc;
@@ -505,49 +518,181 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     w.c_t = P.opt.c_t;
     w.sigma = P.opt.npm_sigma;
     DVec<uint64_t> m2l, p2p;
-    int n_m2l = 0, n_p2p = 0;
-    if (!walk(P, w, false, m2l, p2p, &n_m2l, &n_p2p, s) && !walk(P, w, true, m2l, p2p, &n_m2l, &n_p2p, s))
+    if (!walk(P, w, false, m2l, p2p, &F.n_m2l, &F.n_p2p, s) && !walk(P, w, true, m2l, p2p, &F.n_m2l, &F.n_p2p, s))
         throw Error(ST_INTERNAL, "the interaction walk overflowed its exactly sized buffers");
+    m2l.grow(std::max(F.n_m2l, 1), s);
+    p2p.grow(std::max(F.n_p2p, 1), s);
+    sort_pairs_to_csr(m2l, F.n_m2l, P.nbox, F.m2l_off, F.m2l_src, &F.m2l_ent, s);
+    sort_pairs_to_csr(p2p, F.n_p2p, P.nbox, F.p2p_off, F.p2p_src, nullptr, s);
+    F.ready = true;
+}
+
+// The last FP64 level of the precision tier (29: every box)
+int fp64_level(const sfmm_plan_impl& P) {
+    if (P.opt.precision != SFMM_FP32_MIXED) return 29;
+    // SFMM_FP32_COARSE_LEVEL overrides the last FP64 level (-1: none), for
+    // tuning it and for tests
+    const char* v = std::getenv("SFMM_FP32_COARSE_LEVEL");
+    return v ? (int)std::max(-1L, std::min(29L, std::strtol(v, nullptr, 10))) : kFp32CoarseLevel;
+}
+
+// Room of a hand-down list.  The lists of clustered-1e7 hold at most ~100
+// sources at the default MACs; a plan with a longer one (looser MACs) makes
+// them once more with exact sizes.
+constexpr int kHandDown = 256;
+
+// Box records and the lists of the boxes with targets.
+void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
+    const int nb = P.nbox;
+    DVec<WalkRec> rec;
+    DVec<double4> ttrig;
+    DVec<double> dtrig, hfar;
+    {
+        StageScope st(prof, S_GEOM);
+        P.cen.resize(4 * (size_t)nb);
+        P.rad.resize(nb);
+        P.gdd.resize(8 * (size_t)nb);
+        rec.resize(nb);
+        ttrig.resize(nb);
+        dtrig.resize(kWalkDtrig * (size_t)nb);
+        hfar.resize(nb);
+        // expansions in the near field from order kM2PMinOrder up
+        const int min_count = P.p >= kM2PMinOrder ? m2p_min_count(P.p) : 0x7fffffff;
+        box_records(nb, P.level.data(), P.pixel.data(), P.child0.data(), P.count.data(), P.opt.c_s, P.opt.c_t,
+                    P.opt.npm_sigma, m2p_ratio(P.p), min_count, P.cen.data(), P.rad.data(), P.gdd.data(), rec.data(),
+                    ttrig.data(), dtrig.data(), hfar.data(), s);
+    }
+    const int stage_walk = prof.begin(S_WALK);
+    const int nlev = (int)P.lvl_start.size() - 1, nsplit = (nb - 12) / 4;
+    // SFMM_WALK_RATIO also shrinks the hand-down lists: tests use it to drive
+    // the fallback
+    const char* forced = std::getenv("SFMM_WALK_RATIO");
+    const int cd = forced ? std::max(1, (int)std::atof(forced)) : kHandDown;
+    DVec<int> dlist, dcnt, cnt, off, tot;
+    DVec<int64_t> doff;
+    DVec<int> big;
+    DVec<uint8_t> bigflag;
+    big.resize((size_t)nb / 4 + 1);
+    bigflag.resize(nb / 4);
+    dlist.resize((size_t)std::max(nsplit, 1) * cd);
+    dcnt.resize(std::max(nsplit, 1));
+    cnt.resize(4 * (size_t)nb);
+    off.resize(4 * (size_t)nb);
+    tot.resize(5);
+    P.m2l_off.resize((size_t)nb + 1);
+    P.p2p_off.resize((size_t)nb + 1);
+    P.tl.resize(nb);
+    GroupCtx w{rec.data(),  ttrig.data(), P.gdd.data(), dtrig.data(), P.need.data(), dlist.data(),
+               dcnt.data(), nullptr,      cd,           P.opt.c_s,    P.opt.c_t,     P.opt.npm_sigma};
+    GroupOut o{};
+    o.mcnt = cnt.data();
+    o.pcnt = o.mcnt + nb;
+    o.tflag = o.mcnt + 2 * (size_t)nb;
+    o.nflag = o.mcnt + 3 * (size_t)nb;
+    o.dlist = dlist.data();
+    o.dcnt = dcnt.data();
+    o.dmax = tot.data() + 4;
+    o.dcap = cd;
+    o.big = big.data();
+    o.bigflag = bigflag.data();
+    const int* toff = off.data() + 2 * (size_t)nb;
+    const int* noff = off.data() + 3 * (size_t)nb;
+    const int lc = P.lc = fp64_level(P);
+    int* h = P.pin->p;
+    // the totals of the lists, once every hand-down list is made
+    auto count = [&]() {
+        fill_i32(big.data(), 1, 0, s);
+        group_walk_count(w, o, nb, s);
+        scan_excl_i32_n(cnt.data(), off.data(), 4, nb, tot.data(), s);
+        SFMM_HIP(hipMemcpyAsync(P.m2l_off.data(), off.data(), sizeof(int) * nb, hipMemcpyDeviceToDevice, s));
+        SFMM_HIP(hipMemcpyAsync(P.p2p_off.data(), off.data() + nb, sizeof(int) * nb, hipMemcpyDeviceToDevice, s));
+        target_leaves(o.tflag, toff, noff, nb, P.lvl_start[std::min(lc + 1, nlev)], tot.data(), o.dmax, P.tl.data(),
+                      P.m2l_off.data(), P.p2p_off.data(), h, s);
+        SFMM_HIP(hipStreamSynchronize(s));
+    };
+    fill_i32(tot.data(), 5, 0, s);
+    for (int L = 0; L + 1 < nlev; ++L) group_walk_level(w, o, P.lvl_start[L], P.lvl_start[L + 1], s);
+    count();
+    if (h[4] > 0) {
+        // a hand-down list did not fit: once more with lists of exact size,
+        // every level counted before it is written
+        doff.resize(std::max(nsplit, 1));
+        w.doff = doff.data();
+        std::vector<int> hc;
+        std::vector<int64_t> ho;
+        int64_t used = 0;
+        for (int L = 0; L + 1 < nlev; ++L) {
+            const int s0 = (P.lvl_start[L + 1] - 12) / 4, s1 = L + 2 <= nlev ? (P.lvl_start[L + 2] - 12) / 4 : s0;
+            fill_i32(dcnt.data() + s0, s1 - s0, 0, s);
+            o.dcap = 0;
+            group_walk_level(w, o, P.lvl_start[L], P.lvl_start[L + 1], s);
+            hc.resize(s1 - s0);
+            ho.resize(s1 - s0);
+            SFMM_HIP(hipMemcpyAsync(hc.data(), dcnt.data() + s0, sizeof(int) * (s1 - s0), hipMemcpyDeviceToHost, s));
+            SFMM_HIP(hipStreamSynchronize(s));
+            for (int k = 0; k < s1 - s0; ++k) {
+                ho[k] = used;
+                used += hc[k];
+            }
+            SFMM_HIP(hipMemcpyAsync(doff.data() + s0, ho.data(), sizeof(int64_t) * (s1 - s0), hipMemcpyHostToDevice, s));
+            dlist.grow((size_t)used, s);
+            SFMM_HIP(hipStreamSynchronize(s));
+            w.dlist = o.dlist = dlist.data();
+            o.dcap = 0x7fffffff;
+            group_walk_level(w, o, P.lvl_start[L], P.lvl_start[L + 1], s);
+        }
+        fill_i32(tot.data(), 5, 0, s);
+        count();
+    }
+    P.n_m2l = h[0];
+    const int n_p2p = h[1];
+    P.ntl_all = h[2];
+    P.n_order = h[3];
+    P.n_m2l_fp64 = h[5];
+    // target box of every entry: the per-pair order policies need it
+    const bool ent = P.opt.order_policy != SFMM_ORDER_FIXED;
+    DVec<int> praw;
+    P.m2l_src.resize(std::max(P.n_m2l, 1));
+    praw.resize(std::max(n_p2p, 1));
+    if (ent) P.m2l_ent.resize(std::max(P.n_m2l, 1));
+    o.moff = P.m2l_off.data();
+    o.poff = P.p2p_off.data();
+    o.msrc = P.m2l_src.data();
+    o.psrc = praw.data();
+    o.ment = ent ? P.m2l_ent.data() : nullptr;
+    group_walk_fill(w, o, nb, s);
     prof.end(stage_walk);
     StageScope st(prof, S_LISTS);
-    P.n_m2l = n_m2l;
-    P.n_p2p = n_p2p;
-    m2l.grow(std::max(n_m2l, 1), s);
-    p2p.grow(std::max(n_p2p, 1), s);
-    // target box of every entry: the per-pair order policies need it for the
-    // FMM acts, the near-field split for the direct acts
-    const bool ent = P.opt.order_policy != SFMM_ORDER_FIXED;
-    sort_pairs_to_csr(m2l, n_m2l, P.nbox, P.m2l_off, P.m2l_src, ent ? &P.m2l_ent : nullptr, s);
-    sort_pairs_to_csr(p2p, n_p2p, P.nbox, P.p2p_off, P.p2p_src, &P.p2p_ent, s);
-    // M2L work order: target boxes with the most team rounds first, so the
-    // lanes of a wave carry the same work
+    P.p2p_src.resize(std::max(n_p2p, 1));
+    P.nn.resize(nb);
+    const NearCtx nc{rec.data(),      P.pixel.data(), P.level.data(), P.first.data(), P.tfirst.data(),
+                     P.tcount.data(), P.tx.data(),    P.ty.data(),    P.tz.data(),    hfar.data()};
+    near_lists(nc, P.opt.precision == SFMM_FP32_MIXED, P.tl.data(), P.ntl_all, n_p2p, P.p2p_off.data(), praw.data(), P.p2p_src.data(), P.nn.data(), s);
+    const int segn = P.opt.near_segment > 0 ? P.opt.near_segment : kSegNear;
+    const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : kSegFar;
+    build_items(P.tl.data(), P.ntl_all, P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.count.data(),
+                P.tcount.data(), segn, segf, P.work, h, s);
+    P.ntl = -1;  // counted by the statistics: a read-back the plan itself does not need
+    // M2L work order: boxes with the most team rounds first, so that the
+    // lanes of a wave carry the same work (the precision tier's FP64 levels
+    // before the others)
     DVec<uint64_t> k;
     DVec<uint32_t> v;
-    k.resize(P.nbox);
-    v.resize(P.nbox);
-    // precision tier: boxes of the coarse levels first (they stay FP64)
-    const bool tier = P.opt.precision == SFMM_FP32_MIXED;
-    int lc = 29;
-    if (tier) {
-        // SFMM_FP32_COARSE_LEVEL overrides the last FP64 level (-1: none), for
-        // tuning it and for tests
-        const char* v = std::getenv("SFMM_FP32_COARSE_LEVEL");
-        lc = v ? (int)std::max(-1L, std::min(29L, std::strtol(v, nullptr, 10))) : kFp32CoarseLevel;
-    }
-    const int nlev = (int)P.lvl_start.size() - 1;
-    P.n_m2l_fp64 = tier ? P.lvl_start[std::min(lc + 1, nlev)] : P.nbox;
-    m2l_order_keys(P.m2l_off.data(), P.level.data(), lc, m2l_team_width(P.n_m2l_fp64), kM2LTeamF32, P.nbox, k.data(),
-                   v.data(), s);
-    radix_sort_u64(k.data(), v.data(), P.nbox, 16, s);
-    P.m2l_order.resize(P.nbox);
-    SFMM_HIP(hipMemcpyAsync(P.m2l_order.data(), v.data(), sizeof(int) * P.nbox, hipMemcpyDeviceToDevice, s));
+    k.resize(std::max(P.n_order, 1));
+    v.resize(std::max(P.n_order, 1));
+    m2l_keys(P.m2l_off.data(), o.nflag, noff, P.level.data(), lc, m2l_team_width(P.n_m2l_fp64), kM2LTeamF32, nb,
+             k.data(), v.data(), s);
+    radix_sort_u64(k.data(), v.data(), P.n_order, 8, s);
+    P.m2l_order.resize(std::max(P.n_order, 1));
+    if (P.n_order)
+        SFMM_HIP(hipMemcpyAsync(P.m2l_order.data(), v.data(), sizeof(int) * P.n_order, hipMemcpyDeviceToDevice, s));
 }
 
 // Boxes that have items: the items minus the extra segments of split boxes
 int count_boxes(const WorkItems& w, hipStream_t s) {
     if (w.nred == 0) return w.n;
     std::vector<int4> r(w.nred);
-    SFMM_HIP(hipMemcpyAsync(r.data(), w.red.data(), sizeof(int4) * w.nred, hipMemcpyDeviceToHost, s));
+    SFMM_HIP(hipMemcpyAsync(r.data(), w.red, sizeof(int4) * w.nred, hipMemcpyDeviceToHost, s));
     SFMM_HIP(hipStreamSynchronize(s));
     int extra = 0;
     for (const int4& x : r) extra += x.y - 1;
@@ -589,15 +734,10 @@ void build_targets(sfmm_plan_impl& P, const double* tgt, hipStream_t s) {
         }
         gather_targets(P.tperm.data(), ls, M, u.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), s);
     }
-    target_ranges(P.tleaf.data(), M, P.nbox, P.tfirst.data(), P.tcount.data(), s);
-    near_split(P.ctx(), P.p2p_off.data(), P.p2p_src.data(), P.p2p_ent.data(), P.nbox, P.n_p2p, P.tfirst.data(),
-               P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.nl, s);
-    P.p2p_ent.reset();  // stream-ordered pool: later work on this stream may reuse it
-    const int segn = P.opt.near_segment > 0 ? P.opt.near_segment : kSegNear;
-    const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : kSegFar;
-    build_items2(P.nl.near_off.data(), P.nl.near_src.data(), P.count.data(), segn, P.near_items,
-                 P.nl.far_off.data(), P.nl.far_src.data(), nullptr, segf, P.far_items, P.tcount.data(), P.nbox, s);
-    P.ntl = -1;  // counted by the statistics: a read-back the plan itself does not need
+    target_ranges(P.tleaf.data(), M, P.tfirst.data(), P.tcount.data(), s);
+    P.need.resize(P.nbox);
+    fill_u8(P.need.data(), P.nbox, 0, s);
+    mark_needed(P.tfirst.data(), P.nbox, P.tcount.data(), P.parent.data(), P.need.data(), s);
 }
 
 // Order from a tolerance, by a measured calibration at the default MACs
@@ -724,13 +864,79 @@ struct ExecScratch {
 // Bytes of ExecScratch a plan needs (each part 256-byte aligned).
 size_t exec_scratch_bytes(const sfmm_plan_impl& P, size_t* off_far = nullptr, size_t* off_multf = nullptr) {
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t near = al(sizeof(double) * 4 * (size_t)std::max(P.near_items.nslot, 1));
-    const size_t far = al(sizeof(double) * 4 * (size_t)std::max(P.far_items.nslot, 1));
-    const bool tier = P.n_m2l_fp64 < P.nbox;
-    const size_t mf = tier ? al(sizeof(float) * 2 * (size_t)P.p * (size_t)P.nbox) : 0;
+    const size_t near = al(sizeof(double) * 4 * (size_t)std::max(P.work.near.nslot, 1));
+    const size_t far = al(sizeof(double) * 4 * (size_t)std::max(P.work.far.nslot, 1));
+    const size_t mf = P.tier() ? al(sizeof(float) * 2 * (size_t)P.p * (size_t)P.nbox) : 0;
     if (off_far) *off_far = near;
     if (off_multf) *off_multf = near + far;
     return near + far + mf;
+}
+
+// The boxes and FMM-act lists of one Lemma 3 pass: the plan's own (boxes with
+// targets), or every box with Algorithm 1's full lists (exports).
+struct FarView {
+    const int *off, *src, *ent;
+    const int* order;  // boxes, the first n_fp64 of them taking the FP64 M2L
+    int n, n_fp64, n_pairs;
+};
+
+// The order of every FMM act of a view under the plan's order policy
+void pair_orders(sfmm_plan_impl& P, const FmmCtx& c, const FarView& v, hipStream_t s) {
+    const double kt = SFMM_ORDER_KAPPA * P.opt.tolerance;
+    P.m2l_ord.resize(v.n_pairs);
+    if (P.opt.order_policy == SFMM_ORDER_BOUND) {
+        order_bound(c, v.ent, v.src, v.n_pairs, kt, P.m2l_ord.data(), s);
+    } else {
+        P.decay.resize(P.nbox);
+        order_box_decay(c, P.nbox, P.decay.data(), s);
+        order_mlp(c, v.ent, v.src, P.decay.data(), kt, nullptr, v.n_pairs, P.mlp_w.data(), P.p, kOrderMargin,
+                  P.m2l_ord.data(), nullptr, s);
+    }
+}
+
+// Lemma 3 over a view's lists: the orders of the plan's policy, or (fixed)
+// the plan order for every FMM act.
+void m2l_stage(sfmm_plan_impl& P, const FmmCtx& c, const FarView& v, float* multf, bool fixed, hipStream_t s) {
+    const bool tier = v.n_fp64 < v.n;
+    if (tier) {
+        if (!multf) {
+            P.multf.resize((size_t)P.nbox * 2 * P.p);
+            multf = P.multf.data();
+        }
+        mult_to_f32(c, P.nbox, multf, s);
+    }
+    // one pass per order: (order, CSR offsets, sources); the first pass
+    // writes the local records, later ones add to them
+    auto m2l_pass = [&](int p, bool acc, const int* off, const int* src) {
+        fmm_m2l(c, p, acc, v.order, v.n_fp64, off, src, s);
+        if (tier) fmm_m2l_f32(c, p, acc, multf, v.order + v.n_fp64, v.n - v.n_fp64, off, src, s);
+    };
+    if (fixed || P.opt.order_policy == SFMM_ORDER_FIXED || v.n_pairs == 0) {
+        m2l_pass(P.p, false, v.off, v.src);
+        return;
+    }
+    pair_orders(P, c, v, s);
+    DVec<long long> osq;
+    osq.resize(1);
+    order_split(v.off, v.src, P.m2l_ord.data(), P.nbox, v.n_pairs, P.p, P.ord_off, P.ord_src, osq.data(), s);
+    // class q holds the orders in (4q, 4q + 4]; the top class the plan
+    // order.  In the precision tier every box runs all its classes in
+    // one launch, each pair's monopole part completed inside its
+    // class; the FP64 path takes one pass per class and the monopole
+    // parts from one pass afterwards
+    if (tier && m2l_f32_tail_supported(P.p)) {
+        // the precision tier: its FP64 and its FP32 boxes each take
+        // every class in one launch, monopole parts included
+        fmm_m2l_f64_classes(c, v.order, v.n_fp64, P.ord_off.data(), P.ord_src.data(), P.nbox, s);
+        fmm_m2l_f32_classes(c, multf, v.order + v.n_fp64, v.n - v.n_fp64, P.ord_off.data(), P.ord_src.data(), P.nbox,
+                            s);
+    } else {
+        for (int q = 0; q < (P.p + kOrderStep - 1) / kOrderStep; ++q) {
+            const int pq = std::min((q + 1) * kOrderStep, P.p);
+            m2l_pass(pq, q > 0, P.ord_off.data() + (size_t)q * P.nbox, P.ord_src.data());
+        }
+        m2l_qtail(c, v.off, v.src, P.m2l_ord.data(), P.nbox, s);
+    }
 }
 
 // The five stages of Sec. 3.7 on a plan; xs = null: the plan's own buffers.
@@ -766,62 +972,11 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     // FMM acts: Lemma 3
     {
         StageScope st(prof, S_M2L);
-        const bool tier = P.n_m2l_fp64 < P.nbox;
-        float* multf = xs ? xs->multf : nullptr;
-        if (tier) {
-            if (!xs) {
-                P.multf.resize((size_t)P.nbox * 2 * P.p);
-                multf = P.multf.data();
-            }
-            mult_to_f32(c, P.nbox, multf, s);
-        }
-        // one pass per order: (order, CSR offsets, sources); the first pass
-        // writes the local records, later ones add to them
-        auto m2l_pass = [&](int p, bool acc, const int* off, const int* src) {
-            fmm_m2l(c, p, acc, P.m2l_order.data(), P.n_m2l_fp64, off, src, s);
-            if (tier)
-                fmm_m2l_f32(c, p, acc, multf, P.m2l_order.data() + P.n_m2l_fp64,
-                            P.nbox - P.n_m2l_fp64, off, src, s);
-        };
-        if (fixed || P.opt.order_policy == SFMM_ORDER_FIXED || P.n_m2l == 0) {
-            m2l_pass(P.p, false, P.m2l_off.data(), P.m2l_src.data());
-            P.m2l_order_sq = (long long)P.n_m2l * P.p * P.p;
-        } else {
-            const double kt = SFMM_ORDER_KAPPA * P.opt.tolerance;
-            P.m2l_ord.resize(P.n_m2l);
-            if (P.opt.order_policy == SFMM_ORDER_BOUND) {
-                order_bound(c, P.m2l_ent.data(), P.m2l_src.data(), P.n_m2l, kt, P.m2l_ord.data(), s);
-            } else {
-                P.decay.resize(P.nbox);
-                order_box_decay(c, P.nbox, P.decay.data(), s);
-                order_mlp(c, P.m2l_ent.data(), P.m2l_src.data(), P.decay.data(), kt, nullptr, P.n_m2l,
-                          P.mlp_w.data(), P.p, kOrderMargin, P.m2l_ord.data(), nullptr, s);
-            }
-            P.osq_dev.resize(1);
-            order_split(P.m2l_off.data(), P.m2l_src.data(), P.m2l_ord.data(), P.nbox, P.n_m2l, P.p, P.ord_off,
-                        P.ord_src, P.osq_dev.data(), s);
-            P.m2l_order_sq = -1;
-            // class q holds the orders in (4q, 4q + 4]; the top class the plan
-            // order.  In the precision tier every box runs all its classes in
-            // one launch, each pair's monopole part completed inside its
-            // class; the FP64 path takes one pass per class and the monopole
-            // parts from one pass afterwards
-            const bool tail_in_pass = tier && m2l_f32_tail_supported(P.p);
-            if (tail_in_pass) {
-                // the precision tier: its FP64 and its FP32 boxes each take
-                // every class in one launch, monopole parts included
-                fmm_m2l_f64_classes(c, P.m2l_order.data(), P.n_m2l_fp64, P.ord_off.data(), P.ord_src.data(),
-                                    P.nbox, s);
-                fmm_m2l_f32_classes(c, multf, P.m2l_order.data() + P.n_m2l_fp64, P.nbox - P.n_m2l_fp64,
-                                    P.ord_off.data(), P.ord_src.data(), P.nbox, s);
-            } else {
-                for (int q = 0; q < (P.p + kOrderStep - 1) / kOrderStep; ++q) {
-                    const int pq = std::min((q + 1) * kOrderStep, P.p);
-                    m2l_pass(pq, q > 0, P.ord_off.data() + (size_t)q * P.nbox, P.ord_src.data());
-                }
-                m2l_qtail(c, P.m2l_off.data(), P.m2l_src.data(), P.m2l_ord.data(), P.nbox, s);
-            }
-        }
+        const FarView v{P.m2l_off.data(), P.m2l_src.data(), P.m2l_ent.data(), P.m2l_order.data(),
+                        P.n_order,        P.n_m2l_fp64,     P.n_m2l};
+        m2l_stage(P, c, v, xs ? xs->multf : nullptr, fixed, s);
+        P.ran_policy = !fixed && P.opt.order_policy != SFMM_ORDER_FIXED;
+        P.m2l_order_sq = -1;
     }
     // down-pass: Lemma 4 from level 1 down
     {
@@ -838,22 +993,37 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     double* far_part = xs ? xs->far_part : nullptr;
     double* near_part = xs ? xs->near_part : nullptr;
     if (hess) {
-        P.hess_part.resize(8 * ((size_t)std::max(P.far_items.nslot, 1) + (size_t)std::max(P.near_items.nslot, 1)));
+        P.hess_part.resize(8 * ((size_t)std::max(P.work.far.nslot, 1) + (size_t)std::max(P.work.near.nslot, 1)));
         far_part = P.hess_part.data();
-        near_part = P.hess_part.data() + 8 * (size_t)std::max(P.far_items.nslot, 1);
+        near_part = P.hess_part.data() + 8 * (size_t)std::max(P.work.far.nslot, 1);
     }
     {
         StageScope st(prof, S_M2P);
-        fmm_m2p(c, P.far_items, P.nl.far_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(),
+        fmm_m2p(c, P.work.far, P.p2p_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(),
                 P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, s, far_part, hess);
     }
     {
         StageScope st(prof, S_P2P);
-        fmm_p2p(c, P.opt.precision == SFMM_FP32_MIXED, P.near_items, P.nl.near_src.data(), P.tfirst.data(),
+        fmm_p2p(c, P.opt.precision == SFMM_FP32_MIXED, P.work.near, P.p2p_src.data(), P.tfirst.data(),
                 P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, s,
                 near_part, hess);
     }
     prof.flush();
+}
+
+// Every box (levels in order, so the FP64 levels come first) with its full
+// lists; order (may be null) is filled with the box indices.
+FarView full_view(sfmm_plan_impl& P, DVec<int>* order) {
+    if (order) {
+        std::vector<int> id(P.nbox);
+        for (int b = 0; b < P.nbox; ++b) id[b] = b;
+        order->resize(P.nbox);
+        SFMM_HIP(hipMemcpy(order->data(), id.data(), sizeof(int) * P.nbox, hipMemcpyHostToDevice));
+    }
+    const auto& F = P.full;
+    const int nlev = (int)P.lvl_start.size() - 1;
+    return FarView{F.m2l_off.data(), F.m2l_src.data(), F.m2l_ent.data(), order ? order->data() : nullptr, P.nbox,
+                   P.lvl_start[std::min(P.lc + 1, nlev)], F.n_m2l};
 }
 
 constexpr int kJudgeDefault = 32;
@@ -1061,11 +1231,11 @@ sfmm_status sfmm_plan(const double* src, const double* q, int64_t N, const doubl
         // sorted sources, so it runs beside the tree, the walk and the targets
         if (o.order_policy != SFMM_ORDER_FIXED && o.judge_targets >= 0 && M > 0) judge_start(*P, tgt, ov, s);
         build_tree(*P, s, prof);
-        build_lists(*P, s, prof);
         {
             StageScope st(prof, S_TGT);
             build_targets(*P, tgt, s);
         }
+        build_lists(*P, s, prof);
         if (o.order_policy == SFMM_ORDER_LEARNED) {
             P->mlp_w.resize(kMlpWeights);
             SFMM_HIP(hipMemcpyAsync(P->mlp_w.data(), o.mlp_weights, sizeof(float) * kMlpWeights,
@@ -1249,8 +1419,9 @@ sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
     }
     try {
         PoolStream ps(nullptr);
-        const sfmm_plan_impl& P = *plan;
+        sfmm_plan_impl& P = *plan;
         P.wait();
+        ensure_full(P, nullptr);
         std::memset(out, 0, sizeof(*out));
         out->n_sources = P.N;
         out->n_targets = P.M;
@@ -1259,15 +1430,16 @@ sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
         std::vector<int> c0(P.nbox);
         if (P.nbox) SFMM_HIP(hipMemcpy(c0.data(), P.child0.data(), sizeof(int) * P.nbox, hipMemcpyDeviceToHost));
         out->n_leaves = std::count_if(c0.begin(), c0.end(), [](int v) { return v < 0; });
-        out->n_m2l = P.n_m2l;
-        out->n_p2p = P.n_p2p;
-        if (P.ntl < 0) P.ntl = count_boxes(P.near_items, nullptr);
+        out->n_m2l = P.full.n_m2l;
+        out->n_p2p = P.full.n_p2p;
+        if (P.ntl < 0) P.ntl = count_boxes(P.work.near, nullptr);
         out->n_target_leaves = P.ntl;
         if (P.n_p2p_pairs < 0 && P.nbox > 0) {
             DVec<long long> w, tot;
             w.resize(2 * (size_t)P.nbox);
             tot.resize(2);
-            near_work(P.count.data(), P.nl, P.tcount.data(), P.nbox, w.data(), w.data() + P.nbox, nullptr);
+            near_work(P.count.data(), P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.tcount.data(), P.nbox,
+                      w.data(), w.data() + P.nbox, nullptr);
             sum_i64(w.data(), P.nbox, tot.data(), nullptr);
             sum_i64(w.data() + P.nbox, P.nbox, tot.data() + 1, nullptr);
             long long h[2];
@@ -1277,8 +1449,19 @@ sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
         }
         out->n_p2p_pairs = P.n_p2p_pairs < 0 ? 0 : P.n_p2p_pairs;
         out->n_m2p_evals = P.n_m2p_evals < 0 ? 0 : P.n_m2p_evals;
-        if (P.executed && P.m2l_order_sq < 0)
-            SFMM_HIP(hipMemcpy(&P.m2l_order_sq, P.osq_dev.data(), sizeof(long long), hipMemcpyDeviceToHost));
+        if (P.executed && P.m2l_order_sq < 0) {
+            if (P.ran_policy && P.full.n_m2l > 0) {
+                const FarView v = full_view(P, nullptr);
+                DVec<int> bo, bs;
+                DVec<long long> osq;
+                osq.resize(1);
+                pair_orders(P, P.ctx(), v, nullptr);
+                order_split(v.off, v.src, P.m2l_ord.data(), P.nbox, v.n_pairs, P.p, bo, bs, osq.data(), nullptr);
+                SFMM_HIP(hipMemcpy(&P.m2l_order_sq, osq.data(), sizeof(long long), hipMemcpyDeviceToHost));
+            } else {
+                P.m2l_order_sq = (long long)P.full.n_m2l * P.p * P.p;
+            }
+        }
         out->m2l_order_sq = P.executed ? P.m2l_order_sq : 0;
         out->order = P.p;
         out->leaf_size = P.opt.leaf_size;
@@ -1324,10 +1507,13 @@ sfmm_status sfmm_export_lists(sfmm_plan_t plan, int64_t* m2l_src, int64_t* m2l_t
                               int64_t* p2p_tgt) {
     try {
         if (!plan) throw Error(ST_INVALID_ARG, "plan is NULL");
-        const sfmm_plan_impl& P = *plan;
+        PoolStream ps(nullptr);
+        sfmm_plan_impl& P = *plan;
         P.wait();
-        export_csr(P.m2l_off, P.m2l_src, P.nbox, P.n_m2l, m2l_src, m2l_tgt);
-        export_csr(P.p2p_off, P.p2p_src, P.nbox, P.n_p2p, p2p_src, p2p_tgt);
+        ensure_full(P, nullptr);
+        SFMM_HIP(hipStreamSynchronize(nullptr));
+        export_csr(P.full.m2l_off, P.full.m2l_src, P.nbox, P.full.n_m2l, m2l_src, m2l_tgt);
+        export_csr(P.full.p2p_off, P.full.p2p_src, P.nbox, P.full.n_p2p, p2p_src, p2p_tgt);
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
@@ -1367,7 +1553,8 @@ sfmm_status sfmm_export_work(sfmm_plan_t plan, int64_t* tgt_count, int64_t* pair
         copy_widen(tgt_count, P.tcount.data(), P.nbox);
         DVec<long long> w;
         w.resize(2 * (size_t)P.nbox);
-        near_work(P.count.data(), P.nl, P.tcount.data(), P.nbox, w.data(), w.data() + P.nbox, nullptr);
+        near_work(P.count.data(), P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.tcount.data(), P.nbox, w.data(),
+                  w.data() + P.nbox, nullptr);
         copy_widen(pairs, w.data(), P.nbox);
         copy_widen(evals, w.data() + P.nbox, P.nbox);
         return SFMM_OK;
@@ -1380,9 +1567,22 @@ sfmm_status sfmm_export_expansions(sfmm_plan_t plan, double* multipole, double* 
     try {
         PoolStream ps(nullptr);
         if (!plan) throw Error(ST_INVALID_ARG, "plan is NULL");
-        const sfmm_plan_impl& P = *plan;
+        sfmm_plan_impl& P = *plan;
         P.wait();
         if (!P.executed) throw Error(ST_INVALID_ARG, "plan has not been executed");
+        if (local && P.N > 0 && P.n_order < P.nbox) {
+            // the execute made the local expansions of the boxes with targets
+            // only: here those of every box, at the same orders
+            ensure_full(P, nullptr);
+            DVec<int> order;
+            const FarView v = full_view(P, &order);
+            FmmCtx c = P.ctx();
+            c.need = nullptr;
+            m2l_stage(P, c, v, nullptr, !P.ran_policy, nullptr);
+            for (int L = 1; L + 1 < (int)P.lvl_start.size(); ++L)
+                fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1] - P.lvl_start[L], nullptr);
+            SFMM_HIP(hipStreamSynchronize(nullptr));
+        }
         const int p = P.p, w = 2 * p + 2;
         const size_t nb = P.nbox;
         std::vector<double> cen(4 * nb);
@@ -1422,12 +1622,10 @@ sfmm_status sfmm_order_samples(sfmm_plan_t plan, int64_t n, uint64_t seed, float
         P.wait();
         if (!P.executed) throw Error(ST_INVALID_ARG, "plan has not been executed");
         if (n == 0) return SFMM_OK;
-        if (P.n_m2l == 0) throw Error(ST_INVALID_ARG, "plan has no FMM acts");
         hipStream_t s = nullptr;
-        if (P.m2l_ent.n < (size_t)P.n_m2l) {
-            P.m2l_ent.resize(P.n_m2l);
-            entry_box(P.m2l_off.data(), P.nbox, P.n_m2l, P.m2l_ent.data(), s);
-        }
+        ensure_full(P, s);
+        const auto& F = P.full;
+        if (F.n_m2l == 0) throw Error(ST_INVALID_ARG, "plan has no FMM acts");
         // pairs drawn with a counter-based generator (splitmix64)
         std::vector<int> idx(n);
         for (int64_t i = 0; i < n; ++i) {
@@ -1435,7 +1633,7 @@ sfmm_status sfmm_order_samples(sfmm_plan_t plan, int64_t n, uint64_t seed, float
             z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ULL;
             z = (z ^ (z >> 27)) * 0x94d049bb133111ebULL;
             z ^= z >> 31;
-            idx[i] = (int)(z % (uint64_t)P.n_m2l);
+            idx[i] = (int)(z % (uint64_t)F.n_m2l);
         }
         DVec<int> didx;
         DVec<float> feat, lab;
@@ -1447,14 +1645,14 @@ sfmm_status sfmm_order_samples(sfmm_plan_t plan, int64_t n, uint64_t seed, float
         const double kt = SFMM_ORDER_KAPPA * P.opt.tolerance;
         P.decay.resize(P.nbox);
         order_box_decay(c, P.nbox, P.decay.data(), s);
-        order_features(c, P.m2l_ent.data(), P.m2l_src.data(), didx.data(), n, P.decay.data(), kt, feat.data(), s);
-        order_labels(c, P.m2l_ent.data(), P.m2l_src.data(), didx.data(), (int)n, kt, lab.data(), s);
+        order_features(c, F.m2l_ent.data(), F.m2l_src.data(), didx.data(), n, P.decay.data(), kt, feat.data(), s);
+        order_labels(c, F.m2l_ent.data(), F.m2l_src.data(), didx.data(), (int)n, kt, lab.data(), s);
         SFMM_HIP(hipMemcpy(features, feat.data(), sizeof(float) * n * kMlpIn, hipMemcpyDeviceToHost));
         SFMM_HIP(hipMemcpy(labels, lab.data(), sizeof(float) * n, hipMemcpyDeviceToHost));
         if (pairs) {
-            std::vector<int> ent(P.n_m2l), src(P.n_m2l);
-            SFMM_HIP(hipMemcpy(ent.data(), P.m2l_ent.data(), sizeof(int) * P.n_m2l, hipMemcpyDeviceToHost));
-            SFMM_HIP(hipMemcpy(src.data(), P.m2l_src.data(), sizeof(int) * P.n_m2l, hipMemcpyDeviceToHost));
+            std::vector<int> ent(F.n_m2l), src(F.n_m2l);
+            SFMM_HIP(hipMemcpy(ent.data(), F.m2l_ent.data(), sizeof(int) * F.n_m2l, hipMemcpyDeviceToHost));
+            SFMM_HIP(hipMemcpy(src.data(), F.m2l_src.data(), sizeof(int) * F.n_m2l, hipMemcpyDeviceToHost));
             for (int64_t i = 0; i < n; ++i) {
                 pairs[2 * i] = ent[idx[i]];
                 pairs[2 * i + 1] = src[idx[i]];
