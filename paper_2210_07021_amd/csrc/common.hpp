@@ -346,7 +346,8 @@ struct NpmK {
 };
 NpmK npm_params(double sigma);
 void fmm_p2m(const FmmCtx& c, int nb, hipStream_t s);
-void fmm_m2m(const FmmCtx& c, int b0, int nb, hipStream_t s);
+// Lemma 2 into the parents of boxes c0 .. c1 - 1 (one level)
+void fmm_m2m(const FmmCtx& c, int c0, int c1, hipStream_t s);
 // M2L at order p <= c.p over the boxes order[0..n) (order may be null: box
 // i); acc_in adds to the local records instead of overwriting them
 void fmm_m2l(const FmmCtx& c, int p, bool acc_in, const int* order, int n, const int* off, const int* src,
@@ -367,7 +368,8 @@ void fmm_m2l_f32_classes(const FmmCtx& c, const float* multf, const int* order, 
 // and its FP64 boxes (the coarse levels), likewise in one launch
 void fmm_m2l_f64_classes(const FmmCtx& c, const int* order, int n, const int* boff, const int* bsrc, int nbox,
                          hipStream_t s);
-void fmm_l2l(const FmmCtx& c, int b0, int nb, hipStream_t s);
+// Lemma 4 into boxes c0 .. c1 - 1 (one level) from their parents
+void fmm_l2l(const FmmCtx& c, int c0, int c1, hipStream_t s);
 // (kappa - kappa_bar, gamma_1, gamma_2, mu) [4][m] from the Hessian [3][m]
 void lensing_from_hessian(const double* hess, int64_t m, double* out, hipStream_t s);
 // hess [3][m_out] (may be null): also the Hessian of Sec. 2.2 in the

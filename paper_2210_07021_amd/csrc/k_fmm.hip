@@ -1,6 +1,6 @@
 // The numeric passes of the sFMM (Sec. 3.2-3.3, 3.6): Lemma 1 on leaves,
-// Lemma 2 up the tree, Lemma 3 over the FMM-act lists, Lemma 4 down the
-// tree, and the local expansion at each target.  One lane owns one box (or
+// Lemma 3 over the FMM-act lists, and the local expansion at each target
+// (Lemmas 2 and 4, up and down the tree: k_shift.hip).  One lane owns one box (or
 // one target) and holds its order-P coefficients in registers; P is a
 // template parameter so every loop over l unrolls.
 #include "common.hpp"
@@ -60,32 +60,6 @@ __global__ void __launch_bounds__(128) k_p2m(FmmCtx c, int nb) {
         p2m_add<P>(a, f, inv_rho, v.x, v.y, v.z, v.w);
     }
     p2m_finish<P>(a, c.mult + (size_t)b * (2 * P + 2));
-}
-
-// Lemma 2: every split box of one level gathers its 4 children.  Four
-// consecutive lanes per box, lane 4i + k translating child k (an empty child
-// has a zero record); each output entry is summed over the four lanes by two
-// lane exchanges, (c0 + c1) + (c2 + c3), as it is formed, and lane 4i writes
-// it.
-template <int P>
-__global__ void __launch_bounds__(128) k_m2m(FmmCtx c, int b0, int nb) {
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = gid >> 2, kc = gid & 3;
-    if (i >= nb) return;  // the four lanes of a box leave together
-    const int b = b0 + i;
-    const int ch0 = c.child0[b];
-    if (ch0 < 0) return;
-    const int ch = ch0 + kc;
-    double rho_t, rho_s;
-    const Frame ft = box_frame(c.cen, b, &rho_t);
-    const Frame fs = box_frame(c.cen, ch, &rho_s);
-    const TransGeom G = trans_geom<kM2M>(fs, rho_s, ft, rho_t);
-    const double* in = c.mult + (size_t)ch * (2 * P + 2);
-    double* out = c.mult + (size_t)b * (2 * P + 2);
-    translate_emit<P>([&](int k) { return in[k]; }, G, [&](int k, double v) {
-        const double s = quad_sum(v);
-        if (kc == 0) out[k] = s;
-    });
 }
 
 // Lemma 3 with four lanes per target box (a team): in each round lane r of
@@ -400,27 +374,6 @@ void fmm_m2l_f64_classes(const FmmCtx& c, const int* order, int n, const int* bo
     SFMM_LAUNCH_CHECK();
 }
 
-// Lemma 4: every box of one level takes its parent's local expansion
-template <int P>
-__global__ void __launch_bounds__(128) k_l2l(FmmCtx c, int b0, int nb) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nb) return;
-    const int b = b0 + i;
-    if (c.need && !c.need[b]) return;  // no target below: nothing reads this record
-    const int par = c.parent[b];
-    double rho_t, rho_s;
-    const Frame ft = box_frame(c.cen, b, &rho_t);
-    const Frame fs = box_frame(c.cen, par, &rho_s);
-    double* loc = c.local + (size_t)b * (2 * P + 2);
-    double acc[2 * P + 2];
-#pragma unroll
-    for (int k = 0; k < 2 * P + 2; ++k) acc[k] = loc[k];
-    const TransGeom G = trans_geom<kL2L>(fs, rho_s, ft, rho_t);
-    translate_add<P>(c.local + (size_t)par * (2 * P + 2), G, acc);
-#pragma unroll
-    for (int k = 0; k < 2 * P + 2; ++k) loc[k] = acc[k];
-}
-
 // Local expansion at each target (sorted by leaf); writes psi and alpha in
 // the caller's target order
 template <int P>
@@ -476,14 +429,6 @@ void fmm_p2m(const FmmCtx& c, int nb, hipStream_t s) {
     SFMM_LAUNCH_CHECK();
 }
 
-void fmm_m2m(const FmmCtx& c, int b0, int nb, hipStream_t s) {
-    if (nb <= 0) return;
-#define L_(P) case P: k_m2m<P><<<nblk(4 * (int64_t)nb, 128), 128, 0, s>>>(c, b0, nb); break;
-    SFMM_DISPATCH(c.p, L_)
-#undef L_
-    SFMM_LAUNCH_CHECK();
-}
-
 void fmm_m2l(const FmmCtx& c, int p, bool acc_in, const int* order, int n, const int* off, const int* src,
              hipStream_t s) {
     if (n <= 0) return;
@@ -521,14 +466,6 @@ void fmm_m2l_f32(const FmmCtx& c, int p, bool acc_in, const float* multf, const 
 
 bool m2l_f32_tail_supported(int p) { return p >= 5 && p <= 24; }
 
-
-void fmm_l2l(const FmmCtx& c, int b0, int nb, hipStream_t s) {
-    if (nb <= 0) return;
-#define L_(P) case P: k_l2l<P><<<nblk(nb, 128), 128, 0, s>>>(c, b0, nb); break;
-    SFMM_DISPATCH(c.p, L_)
-#undef L_
-    SFMM_LAUNCH_CHECK();
-}
 
 void fmm_l2p(const FmmCtx& c, const double* tx, const double* ty, const double* tz, const int* tleaf,
              const uint32_t* tperm, int64_t m, double psi_shift, double* psi, double* defl, int64_t m_out,

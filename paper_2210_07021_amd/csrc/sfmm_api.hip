@@ -967,7 +967,7 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     {
         StageScope st(prof, S_M2M);
         for (int L = nlev - 2; L >= 0; --L)
-            fmm_m2m(c, P.lvl_start[L], P.lvl_start[L + 1] - P.lvl_start[L], s);
+            fmm_m2m(c, P.lvl_start[L + 1], P.lvl_start[L + 2], s);
     }
     // FMM acts: Lemma 3
     {
@@ -981,7 +981,7 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     // down-pass: Lemma 4 from level 1 down
     {
         StageScope st(prof, S_L2L);
-        for (int L = 1; L < nlev; ++L) fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1] - P.lvl_start[L], s);
+        for (int L = 1; L < nlev; ++L) fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1], s);
     }
     // far field at the targets, then the direct acts
     {
@@ -1580,7 +1580,7 @@ sfmm_status sfmm_export_expansions(sfmm_plan_t plan, double* multipole, double* 
             c.need = nullptr;
             m2l_stage(P, c, v, nullptr, !P.ran_policy, nullptr);
             for (int L = 1; L + 1 < (int)P.lvl_start.size(); ++L)
-                fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1] - P.lvl_start[L], nullptr);
+                fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1], nullptr);
             SFMM_HIP(hipStreamSynchronize(nullptr));
         }
         const int p = P.p, w = 2 * p + 2;
