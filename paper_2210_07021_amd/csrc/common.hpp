@@ -158,35 +158,32 @@ void sum_f64(const double* x, int64_t n, double* out, hipStream_t s, int stride 
 void sum_i64(const long long* x, int64_t n, long long* out, hipStream_t s);
 
 // ---------------------------------------------------------------- tree
-// Copy [3][n] planes, check they are unit vectors (err bit 1: non-finite,
-// bit 2: off the sphere by more than 1e-6), renormalise ones off by more
-// than 1e-14, and compute their order-29 keys.
+// Copy [3][n] planes, check they are unit vectors (err[0] = 1: non-finite,
+// err[1] = 1: off the sphere by more than 1e-6; host memory, zero before),
+// renormalise ones off by more than 1e-14, and compute their order-29 keys.
 void prepare_points(const double* in, const double* q /*nullable*/, int64_t n, double4* u /*[n] x,y,z,q*/,
                     uint64_t* keys, uint32_t* idx, int* err, hipStream_t s);
 void gather_targets(const uint32_t* idx, const uint64_t* leaf_sorted, int64_t n, const double4* u, double* ox,
                     double* oy, double* oz, int* leaf, hipStream_t s);
 void gather_records(const uint32_t* idx, int64_t n, const double4* u, double4* out, hipStream_t s);
-void tree_base_level(const uint64_t* keys, int64_t n, int* level, uint64_t* pixel, int* first, int* count,
-                     int* parent, int* child0, hipStream_t s);
-void tree_split_flags(int b0, int nb, const int* level, const int* count, int m, int max_level, int* flag,
-                      hipStream_t s);
-void tree_make_children(int b0, int nb, int child_base, const int* flag, const int* off, const uint64_t* keys,
-                        int* level, uint64_t* pixel, int* first, int* count, int* parent, int* child0,
-                        int wave_level, hipStream_t s);
+// The tree from the sorted keys (two reads of them): split boxes per level and
+// tile of points (cnt [kTreeLevels][tree_tiles(n)], scanned by the caller),
+// the first point of every split box in level order (lv.soff[L] = splits above
+// level L), and the box table: the 12 base pixels, then four children per
+// split box.
+constexpr int kTreeLevels = 30;  // levels 0 .. 28 can split; the last one stays empty
+struct TreeLevels {
+    int soff[kTreeLevels + 2];
+};
+int tree_tiles(int64_t n);
+void tree_count(const uint64_t* keys, int64_t n, int m, int max_level, int* cnt, hipStream_t s);
+void tree_emit(const uint64_t* keys, int64_t n, int m, int max_level, int* cnt, const TreeLevels& lv, int* sfirst,
+               hipStream_t s);
+void tree_boxes(const uint64_t* keys, int64_t n, int m, int max_level, const TreeLevels& lv, const int* sfirst,
+                int nsplit, int* level, uint64_t* pixel, int* first, int* count, int* parent, int* child0,
+                hipStream_t s);
 void locate_targets(const uint64_t* keys, int64_t m, const int* child0, const int* level, uint64_t* leaf,
                     hipStream_t s);
-// Queued tree levels (device-resident level bounds ls, chunk counts ccnt of
-// at least ceil(cap / kTreeChunk) entries, per-box ranks wpre of cap
-// entries, overflow flag ctl[0]).
-constexpr int kTreeChunk = 1024;
-// levels below wave_level boxes take a wave per box, larger ones a lane per
-// box; kWaveLevel is the default (SFMM_WAVE_LEVEL overrides it, for tests)
-constexpr int kWaveLevel = 65536;
-int tree_wave_level();
-void tree_init_queued(int* ls, int nls, int* ctl, hipStream_t s);
-void tree_level_queued(int* ls, int L, int* ccnt, int* wpre, int grid, int cgrid, int cap, int* ctl, int m,
-                       int split_ok, const uint64_t* keys, int* level, uint64_t* pixel, int* first, int* count,
-                       int* parent, int* child0, int wave_level, hipStream_t s);
 // (tcount: the end of each leaf's run until mark_needed makes it a count)
 void target_ranges(const int* leaf, int64_t m, int* tfirst, int* tcount, hipStream_t s);
 // run ends to counts, and need[b] = 1 for every box with a target below it

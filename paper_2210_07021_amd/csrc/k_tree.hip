@@ -5,7 +5,6 @@
 #include "geom.hpp"
 
 #include <algorithm>
-#include <cstdlib>
 
 namespace sfmm {
 
@@ -17,7 +16,7 @@ static unsigned nblocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b > 
 // gather after the key sort moves one aligned record per point (q = 0 when
 // the points carry no charge).
 __global__ void k_prepare_points(const double* in, const double* q, int64_t n, double4* u, uint64_t* keys,
-                                 uint32_t* idx, int* err) {
+                                 uint32_t* idx, volatile int* err) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     double a = in[i], b = in[n + i], c = in[2 * n + i];
@@ -26,7 +25,7 @@ __global__ void k_prepare_points(const double* in, const double* q, int64_t n, d
     if (!(isfinite(a) && isfinite(b) && isfinite(c))) e |= 1;
     else if (!(fabs(r2 - 1.0) <= 2e-6)) e |= 2;
     if (e) {
-        atomicOr(err, e);
+        err[e - 1] = 1;  // host memory, one int per kind
         a = 0.0; b = 0.0; c = 1.0;
     } else if (fabs(r2 - 1.0) > 1e-14) {
         const double inv = 1.0 / sqrt(r2);
@@ -75,7 +74,20 @@ void gather_records(const uint32_t* idx, int64_t n, const double4* u, double4* o
     SFMM_LAUNCH_CHECK();
 }
 
-// ------------------------------------------------------------------ levels
+// ------------------------------------------------------------------ tree
+// The whole tree at once from the sorted keys.  A box of level L holds more
+// than m points exactly when its first point i and point i + m share its
+// pixel, and i is the first point of its level-L pixel exactly when point i -
+// 1 does not share it.  So with common(i, j) the deepest level at which keys i
+// and j share a pixel, the split boxes that start at point i are those of the
+// levels common(i - 1, i) < L <= min(common(i, i + m), max_level - 1).  One
+// pass counts them per level, a scan gives every split box its place in its
+// level's list (ordered by first point), one pass writes their first points,
+// and a last one cuts every split box's points into its four children: split
+// s has the children 12 + 4s .. 12 + 4s + 3.  Against two launches a level and
+// a read-back every eight levels (24 levels: 0.40 ms of kernels on
+// clustered-1e7, and most of a small plan's tree time is launches) the passes
+// read the keys twice.
 __device__ int lower_bound_u64(const uint64_t* a, int lo, int hi, uint64_t v) {
     while (lo < hi) {
         const int mid = lo + ((hi - lo) >> 1);
@@ -85,304 +97,144 @@ __device__ int lower_bound_u64(const uint64_t* a, int lo, int hi, uint64_t v) {
     return lo;
 }
 
-__global__ void k_base_level(const uint64_t* keys, int n, int* level, uint64_t* pixel, int* first, int* count,
-                             int* parent, int* child0) {
-    const int f = threadIdx.x;
-    if (f >= 12) return;
-    const int a = lower_bound_u64(keys, 0, n, (uint64_t)f << (2 * kOrder));
-    const int b = lower_bound_u64(keys, 0, n, (uint64_t)(f + 1) << (2 * kOrder));
-    level[f] = 0;
-    pixel[f] = (uint64_t)f;
-    first[f] = a;
-    count[f] = b - a;
-    parent[f] = -1;
-    child0[f] = -1;
-}
-
-void tree_base_level(const uint64_t* keys, int64_t n, int* level, uint64_t* pixel, int* first, int* count,
-                     int* parent, int* child0, hipStream_t s) {
-    k_base_level<<<1, 64, 0, s>>>(keys, (int)n, level, pixel, first, count, parent, child0);
-    SFMM_LAUNCH_CHECK();
-}
-
-__global__ void k_split_flags(int b0, int nb, const int* level, const int* count, int m, int max_level, int* flag) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nb) return;
-    const int b = b0 + i;
-    flag[i] = (count[b] > m && level[b] < max_level) ? 1 : 0;
-}
-
-void tree_split_flags(int b0, int nb, const int* level, const int* count, int m, int max_level, int* flag,
-                      hipStream_t s) {
-    k_split_flags<<<nblocks(nb, 256), 256, 0, s>>>(b0, nb, level, count, m, max_level, flag);
-    SFMM_LAUNCH_CHECK();
-}
-
-// The four children of box b (pixel p at level L) when it splits (slot >= 0:
-// the split box's index among its level's split boxes, children at
-// child_base + 4 slot): each child's point range is cut from the parent's
-// sorted keys; child0[b] = -1 when it does not split.
-__device__ void children_thread(int b, int slot, int child_base, const uint64_t* __restrict__ keys, int* level,
-                                uint64_t* pixel, int* first, int* count, int* parent, int* child0) {
-    if (slot < 0) {
-        child0[b] = -1;
-        return;
-    }
-    const int c0 = child_base + 4 * slot;
-    child0[b] = c0;
-    const int L = level[b] + 1;
-    const int shift = 2 * (kOrder - L);
-    const int end = first[b] + count[b];
-    int lo = first[b];
-    for (int c = 0; c < 4; ++c) {
-        const uint64_t pix = pixel[b] * 4 + (uint64_t)c;
-        const int e = (c == 3) ? end : lower_bound_u64(keys, lo, end, (pix + 1) << shift);
-        level[c0 + c] = L;
-        pixel[c0 + c] = pix;
-        first[c0 + c] = lo;
-        count[c0 + c] = e - lo;
-        parent[c0 + c] = b;
-        child0[c0 + c] = -1;
-        lo = e;
-    }
-}
-
-__global__ void k_make_children(int b0, int nb, int child_base, const int* flag, const int* off,
-                                const uint64_t* keys, int* level, uint64_t* pixel, int* first, int* count,
-                                int* parent, int* child0) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nb) return;
-    children_thread(b0 + i, flag[i] ? off[i] : -1, child_base, keys, level, pixel, first, count, parent, child0);
-}
-
-// First index in [lo, hi) whose key is >= v (hi when none), found by the 64
-// lanes of a wave together: each step tests 64 evenly spaced keys of the
-// range and keeps the gap where the predicate turns true, so a range of n
-// keys takes about log(n) / log(65) dependent loads.  Every lane returns the
-// same index (the loop is uniform across the wave).
-__device__ int wave_lower_bound_u64(const uint64_t* __restrict__ a, int lo, int hi, uint64_t v) {
-    const int lane = threadIdx.x & 63;
-    while (hi > lo) {
-        const int n = hi - lo;
-        if (n <= 64) {
-            const bool p = lane < n && a[lo + lane] >= v;
-            const uint64_t m = __ballot(p);
-            return m ? lo + (int)__ffsll((unsigned long long)m) - 1 : hi;
-        }
-        const int q = lo + (int)(((int64_t)(lane + 1) * n) / 65);  // in [lo, hi)
-        const uint64_t m = __ballot(a[q] >= v);
-        const int j = m ? (int)__ffsll((unsigned long long)m) - 1 : 64;
-        const int qprev = j > 0 ? __shfl(q, j - 1, 64) : lo - 1;
-        const int qj = j < 64 ? __shfl(q, j, 64) : hi;
-        lo = qprev + 1;
-        hi = qj;
+// first index in [lo, hi) of a sorted int list with a[] >= v
+__device__ __forceinline__ int lower_bound_i32(const int* a, int lo, int hi, int v) {
+    while (lo < hi) {
+        const int mid = lo + ((hi - lo) >> 1);
+        if (a[mid] < v) lo = mid + 1;
+        else hi = mid;
     }
     return lo;
 }
 
-// children_thread with the whole wave on one box (levels of few, large
-// boxes); b and slot are uniform across the wave.
-__device__ void children_wave(int b, int slot, int child_base, const uint64_t* __restrict__ keys, int* level,
-                              uint64_t* pixel, int* first, int* count, int* parent, int* child0) {
-    const int lane = threadIdx.x & 63;
-    if (slot < 0) {
-        if (lane == 0) child0[b] = -1;
-        return;
-    }
-    const int c0 = child_base + 4 * slot;
-    const int L = level[b] + 1;
-    const int shift = 2 * (kOrder - L);
-    const int end = first[b] + count[b];
-    const int f0 = first[b];
-    const uint64_t pb = pixel[b] * 4;
-    const int e0 = wave_lower_bound_u64(keys, f0, end, (pb + 1) << shift);
-    const int e1 = wave_lower_bound_u64(keys, e0, end, (pb + 2) << shift);
-    const int e2 = wave_lower_bound_u64(keys, e1, end, (pb + 3) << shift);
-    if (lane < 4) {
-        const int c = lane;
-        const int st = c == 0 ? f0 : c == 1 ? e0 : c == 2 ? e1 : e2;
-        const int en = c == 0 ? e0 : c == 1 ? e1 : c == 2 ? e2 : end;
-        level[c0 + c] = L;
-        pixel[c0 + c] = pb + (uint64_t)c;
-        first[c0 + c] = st;
-        count[c0 + c] = en - st;
-        parent[c0 + c] = b;
-        child0[c0 + c] = -1;
-    }
-    if (lane == 0) child0[b] = c0;
+// deepest level at which two order-29 keys share a pixel (-1: none)
+__device__ __forceinline__ int common_level(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    return x == 0 ? kOrder : max(-1, kOrder - 1 - (63 - (int)__clzll((long long)x)) / 2);
 }
 
-// k_make_children with one wave per box
-__global__ void k_make_children_wave(int b0, int nb, int child_base, const int* flag, const int* off,
-                                     const uint64_t* keys, int* level, uint64_t* pixel, int* first, int* count,
-                                     int* parent, int* child0) {
-    const int i = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
-    if (i >= nb) return;  // uniform across the wave
-    children_wave(b0 + i, flag[i] ? off[i] : -1, child_base, keys, level, pixel, first, count, parent, child0);
+// Bits of the levels of the split boxes that start at point i.
+__device__ __forceinline__ uint32_t split_levels(const uint64_t* __restrict__ keys, int64_t n, int64_t i, int64_t m,
+                                                 int max_level) {
+    if (i + m >= n) return 0;
+    const uint64_t k = keys[i];
+    const int c = min(common_level(k, keys[i + m]), max_level - 1);
+    const int d = i == 0 ? -1 : common_level(keys[i - 1], k);
+    return c > d ? (uint32_t)((2ull << c) - (1ull << (d + 1))) : 0u;
 }
 
-void tree_make_children(int b0, int nb, int child_base, const int* flag, const int* off, const uint64_t* keys,
-                        int* level, uint64_t* pixel, int* first, int* count, int* parent, int* child0,
-                        int wave_level, hipStream_t s) {
-    if (nb <= 0) return;
-    if (nb < wave_level) {
-        k_make_children_wave<<<nblocks((int64_t)nb * 64, 256), 256, 0, s>>>(b0, nb, child_base, flag, off, keys,
-                                                                           level, pixel, first, count, parent,
-                                                                           child0);
-    } else {
-        k_make_children<<<nblocks(nb, 256), 256, 0, s>>>(b0, nb, child_base, flag, off, keys, level, pixel, first,
-                                                        count, parent, child0);
-    }
-    SFMM_LAUNCH_CHECK();
-}
-
-// ------------------------------------------------------------------ queued levels
-// The same level loop with the level bounds in device memory (ls[L] ..
-// ls[L+1] - 1 are level L's boxes), so levels run back to back without a
-// read-back each: per level, split counts per chunk of kTreeChunk boxes,
-// then the children (which also set ls[L+2], or the overflow flag ctl[0]
-// when the children would pass the capacity): two launches per level.
-constexpr int kTreeThreads = 256;
-constexpr int kTreePer = kTreeChunk / kTreeThreads;
-
-__device__ int tree_block_excl(int v, int* sh, int* total) {
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    int x = v;
+// A wave takes kMarkPoints consecutive points, 64 at a time; lane L holds the
+// running count of level L.  EMIT: it starts from the scanned counts, and
+// every split box's first point goes to its place.
+constexpr int kMarkPoints = 512;
+template <bool EMIT>
+__global__ void __launch_bounds__(256) k_tree_mark(const uint64_t* __restrict__ keys, int64_t n, int64_t m,
+                                                   int max_level, int nt, int* __restrict__ cnt,
+                                                   TreeLevels lv, int* __restrict__ sfirst) {
+    const int tile = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6), lane = threadIdx.x & 63;
+    if (tile >= nt) return;  // uniform across the wave
+    const uint64_t lt = (1ull << lane) - 1;
+    int run = EMIT && lane < kTreeLevels ? cnt[(size_t)lane * nt + tile] + lv.soff[lane] : 0;
+    for (int k = 0; k < kMarkPoints; k += 64) {
+        const int64_t i = (int64_t)tile * kMarkPoints + k + lane;
+        const uint32_t bits = split_levels(keys, n, i, m, max_level);
+        uint32_t any = bits;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) sh[wv] = x;
-    __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kTreeThreads / 64; ++w) {
-        const int ws = sh[w];
-        before += (w < wv) ? ws : 0;
-        all += ws;
-    }
-    *total = all;
-    __syncthreads();
-    return before + x - v;
-}
-
-__global__ void k_tree_init(int* ls, int nls, int* ctl) {
-    const int t = threadIdx.x;
-    if (t < nls) ls[t] = (t == 0) ? 0 : 12;
-    if (t == 0) ctl[0] = 0;
-}
-
-// Per chunk: the split count, and for each box its rank among the chunk's
-// split boxes (wpre, -1 when it does not split).
-__global__ void __launch_bounds__(kTreeThreads) k_tree_count(const int* ls, int L, const int* count, int m,
-                                                              int split_ok, int* ccnt, int* wpre) {
-    __shared__ int sh[kTreeThreads / 64];
-    const int b0 = ls[L], nb = ls[L + 1] - b0;
-    const int nch = (nb + kTreeChunk - 1) / kTreeChunk;
-    for (int j = blockIdx.x; j < nch; j += gridDim.x) {
-        const int i0 = j * kTreeChunk + threadIdx.x * kTreePer;
-        int f[kTreePer], c = 0;
-#pragma unroll
-        for (int q = 0; q < kTreePer; ++q) {
-            f[q] = (split_ok && i0 + q < nb && count[b0 + i0 + q] > m) ? 1 : 0;
-            c += f[q];
-        }
-        int tot;
-        int e = tree_block_excl(c, sh, &tot);
-#pragma unroll
-        for (int q = 0; q < kTreePer; ++q) {
-            if (i0 + q < nb) wpre[i0 + q] = f[q] ? e : -1;
-            e += f[q];
-        }
-        if (threadIdx.x == 0) ccnt[j] = tot;
-    }
-}
-
-// Sum of ccnt[0 .. n) by the whole wave (every lane returns it).
-__device__ int wave_sum_prefix(const int* ccnt, int n) {
-    const int lane = threadIdx.x & 63;
-    int sum = 0;
-    for (int k = lane; k < n; k += 64) sum += ccnt[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    return sum;
-}
-
-// Children of every box of the level: a wave per box on levels of fewer
-// than wave_level boxes, else a lane per box (grid-stride either way).  A
-// split box's slot is the split count of the chunks before its own (summed
-// here from the per-chunk counts) plus its rank in its chunk.  The first
-// wave of workgroup 0 sums all chunks: the next level's bounds ls[L+2], or
-// the overflow flag when the children would pass cap boxes (boxes whose
-// children would not fit write none; the caller then rebuilds the tree).
-__global__ void __launch_bounds__(kTreeThreads) k_tree_children(int* ls, int L, const int* ccnt, const int* wpre,
-                                                                 int* ctl, int cap, const uint64_t* __restrict__ keys,
-                                                                 int* level, uint64_t* pixel, int* first, int* count,
-                                                                 int* parent, int* child0, int wave_level) {
-    if (ctl[0]) {  // an earlier level overflowed: this one stays empty
-        if (blockIdx.x == 0 && threadIdx.x == 0) ls[L + 2] = ls[L + 1];
-        return;
-    }
-    const int b0 = ls[L], nb = ls[L + 1] - b0, child_base = ls[L + 1];
-    const int nch = (nb + kTreeChunk - 1) / kTreeChunk;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (blockIdx.x == 0 && wave == 0) {
-        const int tot = wave_sum_prefix(ccnt, nch);
-        if (lane == 0) {
-            const int64_t need = (int64_t)child_base + 4 * (int64_t)tot;
-            if (need > cap) {
-                ctl[0] = 1;
-                ls[L + 2] = ls[L + 1];
-            } else {
-                ls[L + 2] = (int)need;
+        for (int o = 32; o > 0; o >>= 1) any |= __shfl_xor(any, o, 64);
+        any = __builtin_amdgcn_readfirstlane(any);
+        while (any) {
+            const int L = __ffs(any) - 1;
+            any &= any - 1;
+            const uint64_t mask = __ballot(bits >> L & 1);
+            if (EMIT) {
+                const int base = __builtin_amdgcn_readlane(run, L);
+                if (bits >> L & 1) sfirst[base + __popcll(mask & lt)] = (int)i;
             }
+            if (lane == L) run += __popcll(mask);
         }
     }
-    const int nw = gridDim.x * (kTreeThreads / 64);
-    if (nb < wave_level) {
-        for (int i = blockIdx.x * (kTreeThreads / 64) + wave; i < nb; i += nw) {
-            const int r = wpre[i];
-            const int pre = wave_sum_prefix(ccnt, i / kTreeChunk);
-            int slot = r >= 0 ? pre + r : -1;
-            if (slot >= 0 && (int64_t)child_base + 4 * (int64_t)slot + 4 > cap) continue;  // overflow
-            children_wave(b0 + i, slot, child_base, keys, level, pixel, first, count, parent, child0);
-        }
-    } else {
-        // a wave takes 64 consecutive boxes, which span at most two chunks
-        for (int base = (blockIdx.x * (kTreeThreads / 64) + wave) * 64; base < nb; base += nw * 64) {
-            const int c0 = base / kTreeChunk;
-            const int pre0 = wave_sum_prefix(ccnt, c0);
-            const int i = base + lane;
-            if (i >= nb) continue;
-            const int pre = (i / kTreeChunk == c0) ? pre0 : pre0 + ccnt[c0];
-            const int r = wpre[i];
-            const int slot = r >= 0 ? pre + r : -1;
-            if (slot >= 0 && (int64_t)child_base + 4 * (int64_t)slot + 4 > cap) continue;  // overflow
-            children_thread(b0 + i, slot, child_base, keys, level, pixel, first, count, parent, child0);
-        }
-    }
+    if (!EMIT && lane < kTreeLevels) cnt[(size_t)lane * nt + tile] = run;
 }
 
-int tree_wave_level() {
-    const char* v = std::getenv("SFMM_WAVE_LEVEL");
-    if (!v) return kWaveLevel;
-    const long w = std::strtol(v, nullptr, 10);
-    return (int)std::max(0L, std::min(w, 0x7fffffffL));
-}
+int tree_tiles(int64_t n) { return (int)std::max<int64_t>(1, (n + kMarkPoints - 1) / kMarkPoints); }
 
-void tree_init_queued(int* ls, int nls, int* ctl, hipStream_t s) {
-    k_tree_init<<<1, 64, 0, s>>>(ls, nls, ctl);
+void tree_count(const uint64_t* keys, int64_t n, int m, int max_level, int* cnt, hipStream_t s) {
+    const int nt = tree_tiles(n);
+    k_tree_mark<false><<<nblocks((int64_t)nt * 64, 256), 256, 0, s>>>(keys, n, m, max_level, nt, cnt, TreeLevels{},
+                                                                      nullptr);
     SFMM_LAUNCH_CHECK();
 }
 
-void tree_level_queued(int* ls, int L, int* ccnt, int* wpre, int grid, int cgrid, int cap, int* ctl, int m,
-                       int split_ok, const uint64_t* keys, int* level, uint64_t* pixel, int* first, int* count,
-                       int* parent, int* child0, int wave_level, hipStream_t s) {
-    k_tree_count<<<grid, kTreeThreads, 0, s>>>(ls, L, count, m, split_ok, ccnt, wpre);
+void tree_emit(const uint64_t* keys, int64_t n, int m, int max_level, int* cnt, const TreeLevels& lv, int* sfirst,
+               hipStream_t s) {
+    const int nt = tree_tiles(n);
+    k_tree_mark<true><<<nblocks((int64_t)nt * 64, 256), 256, 0, s>>>(keys, n, m, max_level, nt, cnt, lv, sfirst);
     SFMM_LAUNCH_CHECK();
-    k_tree_children<<<cgrid, kTreeThreads, 0, s>>>(ls, L, ccnt, wpre, ctl, cap, keys, level, pixel, first, count,
-                                                   parent, child0, wave_level);
+}
+
+// Four lanes per split box: lane q finds where child q ends (from the box's
+// first point in growing steps, then by bisection), writes the child, and
+// looks up the child's own split (child0) and the box's index (the children's
+// parent) in the level lists.  The first workgroup's first 12 threads write
+// the base pixels instead.  Bound by the chain of dependent loads (~40, a few
+// of them past the L2).
+__global__ void __launch_bounds__(256) k_tree_boxes(const uint64_t* __restrict__ keys, int n, int m, int max_level,
+                                                    TreeLevels lv, const int* __restrict__ sfirst, int nsplit,
+                                                    int* __restrict__ level, uint64_t* __restrict__ pixel,
+                                                    int* __restrict__ first, int* __restrict__ count,
+                                                    int* __restrict__ parent, int* __restrict__ child0) {
+    if (blockIdx.x == 0) {
+        const int f = threadIdx.x;
+        if (f >= 12) return;
+        const int a = lower_bound_u64(keys, 0, n, (uint64_t)f << (2 * kOrder));
+        const int b = lower_bound_u64(keys, 0, n, (uint64_t)(f + 1) << (2 * kOrder));
+        level[f] = 0;
+        pixel[f] = (uint64_t)f;
+        first[f] = a;
+        count[f] = b - a;
+        parent[f] = -1;
+        child0[f] = b - a > m && max_level > 0 ? 12 + 4 * lower_bound_i32(sfirst, lv.soff[0], lv.soff[1], a) : -1;
+        return;
+    }
+    const int t = (blockIdx.x - 1) * 256 + threadIdx.x;
+    const int s = t >> 2, q = t & 3;
+    if (s >= nsplit) return;  // the four lanes of a box leave together
+    int L = 0;
+    while (s >= lv.soff[L + 1]) ++L;
+    const int i0 = sfirst[s];
+    const uint64_t pix = keys[i0] >> (2 * (kOrder - L)), cp = 4 * pix + (uint64_t)q;
+    const uint64_t v = (cp + 1) << (2 * (kOrder - L - 1));
+    // the end of child q: keys[lo] < v (or lo = i0), keys[hi] >= v or hi = n
+    int lo = i0, hi = n;
+    for (int64_t step = 64; (int64_t)lo + step < n; step <<= 2) {
+        if (keys[lo + step] < v) {
+            lo += (int)step;
+        } else {
+            hi = lo + (int)step;
+            break;
+        }
+    }
+    const int end = lower_bound_u64(keys, lo, hi, v);
+    const int st = __shfl_up(end, 1, 4);
+    const int beg = q == 0 ? i0 : st;
+    int b = (int)pix;
+    if (L > 0) b = 12 + 4 * (lower_bound_i32(sfirst, lv.soff[L - 1], lv.soff[L], i0 + 1) - 1) + (int)(pix & 3);
+    const int c = 12 + 4 * s + q;
+    level[c] = L + 1;
+    pixel[c] = cp;
+    first[c] = beg;
+    count[c] = end - beg;
+    parent[c] = b;
+    child0[c] = end - beg > m && L + 1 < max_level
+                    ? 12 + 4 * lower_bound_i32(sfirst, lv.soff[L + 1], lv.soff[L + 2], beg)
+                    : -1;
+}
+
+void tree_boxes(const uint64_t* keys, int64_t n, int m, int max_level, const TreeLevels& lv, const int* sfirst,
+                int nsplit, int* level, uint64_t* pixel, int* first, int* count, int* parent, int* child0,
+                hipStream_t s) {
+    k_tree_boxes<<<1 + (nsplit > 0 ? nblocks(4 * (int64_t)nsplit, 256) : 0), 256, 0, s>>>(
+        keys, (int)n, m, max_level, lv, sfirst, nsplit, level, pixel, first, count, parent, child0);
     SFMM_LAUNCH_CHECK();
 }
 

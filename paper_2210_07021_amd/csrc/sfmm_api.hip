@@ -21,9 +21,12 @@ using namespace sfmm;
 namespace {
 thread_local std::string g_last_error;
 
-// pinned host scratch for the counts read back during planning
+// pinned host memory that the plan's kernels write what the host reads back
+// into: counts at p, the two error words of each point set, the total charge
 struct Pinned {
     int* p = nullptr;
+    int* err(int set) const { return p + 48 + 2 * set; }
+    double* q() const { return reinterpret_cast<double*>(p + 56); }
     Pinned() { SFMM_HIP(hipHostMalloc((void**)&p, 64 * sizeof(int), hipHostMallocDefault)); }
     ~Pinned() {
         if (p) (void)hipHostFree(p);
@@ -207,12 +210,6 @@ struct sfmm_plan_impl {
 
 namespace {
 
-int read_int(const int* dev, sfmm_plan_impl& P, hipStream_t s) {
-    SFMM_HIP(hipMemcpyAsync(P.pin->p, dev, sizeof(int), hipMemcpyDeviceToHost, s));
-    SFMM_HIP(hipStreamSynchronize(s));
-    return P.pin->p[0];
-}
-
 void validate(const sfmm_options& o) {
     auto bad = [](const std::string& m) { throw Error(ST_INVALID_ARG, m); };
     if (o.order < 0 || o.order > kMaxOrder) bad("order must be in [0, 64]");
@@ -233,126 +230,63 @@ void validate(const sfmm_options& o) {
     if (!(o.npm_sigma >= 0.0 && o.npm_sigma <= 0.5)) bad("npm_sigma must be in [0, 0.5]");
 }
 
-// Sort points by key and keep the permutation; outputs resized here: the
-// sorted points as (x, y, z, q) records (sources, rec != nullptr) or as three
-// coordinate arrays (targets).
-// Keys, records in caller order and the identity permutation; throws on
-// non-finite points or points off the unit sphere.
-void prepare_checked(const double* in, const double* q_in, int64_t n, DVec<double4>& u, DVec<uint64_t>& keys,
-                     DVec<uint32_t>& perm, sfmm_plan_impl& P, hipStream_t s, const char* what) {
-    DVec<int> err;
-    err.resize(1);
-    fill_i32(err.data(), 1, 0, s);
-    prepare_points(in, q_in, n, u.data(), keys.data(), perm.data(), err.data(), s);
-    const int e = read_int(err.data(), P, s);
-    if (e & 1) throw Error(ST_INVALID_ARG, std::string(what) + ": non-finite coordinates");
-    if (e & 2) throw Error(ST_INVALID_ARG, std::string(what) + ": points off the unit sphere by more than 1e-6");
+// The error words that prepare_points left in host memory (after a wait)
+void check_points(const int* err, const char* what) {
+    if (err[0]) throw Error(ST_INVALID_ARG, std::string(what) + ": non-finite coordinates");
+    if (err[1]) throw Error(ST_INVALID_ARG, std::string(what) + ": points off the unit sphere by more than 1e-6");
 }
 
 // Sources: keys, sort by key, records (x, y, z, q) in key order.
 void sort_points(const double* in, const double* q_in, int64_t n, DVec<double4>& rec, DVec<uint32_t>& perm,
-                 DVec<uint64_t>& keys, sfmm_plan_impl& P, hipStream_t s, const char* what) {
+                 DVec<uint64_t>& keys, int* err, hipStream_t s) {
     rec.resize(n);
     perm.resize(n);
     keys.resize(n);
     if (n == 0) return;
     DVec<double4> u;
     u.resize(n);
-    prepare_checked(in, q_in, n, u, keys, perm, P, s, what);
+    prepare_points(in, q_in, n, u.data(), keys.data(), perm.data(), err, s);
     radix_sort_u64(keys.data(), perm.data(), n, 62, s);
     gather_records(perm.data(), n, u.data(), rec.data(), s);
 }
 
-constexpr int kTreeBatch = 8;  // queued levels between two read-backs
-
-// Levels with a host read of the split count after each: the arrays grow as
-// needed.
-void build_levels_exact(sfmm_plan_impl& P, int m, hipStream_t s) {
-    tree_base_level(P.skeys.data(), P.N, P.level.data(), P.pixel.data(), P.first.data(), P.count.data(),
-                    P.parent.data(), P.child0.data(), s);
-    P.lvl_start.assign({0, 12});
-    DVec<int> flag, off, tot;
-    tot.resize(1);
-    const int wave_level = tree_wave_level();
-    for (int L = 0;; ++L) {
-        const int b0 = P.lvl_start[L], b1 = P.lvl_start[L + 1], nb = b1 - b0;
-        flag.resize(nb);
-        off.resize(nb);
-        tree_split_flags(b0, nb, P.level.data(), P.count.data(), m, P.opt.max_level, flag.data(), s);
-        scan_excl_i32(flag.data(), off.data(), nb, tot.data(), s);
-        const int nsplit = read_int(tot.data(), P, s);
-        if (nsplit == 0) break;
-        const size_t need = (size_t)b1 + 4 * (size_t)nsplit;
-        if (need > 0x7fffffff) throw Error(ST_INVALID_ARG, "tree too large");
-        P.level.grow(need, s);
-        P.pixel.grow(need, s);
-        P.first.grow(need, s);
-        P.count.grow(need, s);
-        P.parent.grow(need, s);
-        P.child0.grow(need, s);
-        tree_make_children(b0, nb, b1, flag.data(), off.data(), P.skeys.data(), P.level.data(), P.pixel.data(),
-                           P.first.data(), P.count.data(), P.parent.data(), P.child0.data(), wave_level, s);
-        P.lvl_start.push_back((int)need);
-    }
-}
-
-// Levels queued kTreeBatch at a time with the level bounds on the device;
-// false when the children of some level would pass cap boxes (nothing of
-// the partial build is kept then).
-bool build_levels_queued(sfmm_plan_impl& P, int m, int cap, hipStream_t s) {
-    constexpr int kLs = 32;  // level bounds ls[0 .. max_level + 2]
-    DVec<int> ls, ctl, ccnt, wpre;
-    ls.resize(kLs);
-    ctl.resize(1);
-    const int nch = (cap + kTreeChunk - 1) / kTreeChunk;
-    ccnt.resize(nch);
-    wpre.resize(cap);
-    const int grid = std::min(nch, 1024);
-    const int cgrid = 2048;  // 8192 waves
-    tree_base_level(P.skeys.data(), P.N, P.level.data(), P.pixel.data(), P.first.data(), P.count.data(),
-                    P.parent.data(), P.child0.data(), s);
-    tree_init_queued(ls.data(), kLs, ctl.data(), s);
-    const int lmax = P.opt.max_level;
-    const int wave_level = tree_wave_level();
+// The tree (k_tree.hip).  The one wait of the plan's first half is here: the
+// splits per level size the box table, and the checks of the points and the
+// total charge are read with them.
+void build_tree(sfmm_plan_impl& P, hipStream_t s) {
+    const int m = P.opt.leaf_size, lmax = P.opt.max_level, nt = tree_tiles(P.N);
+    DVec<int> cnt, off, sfirst;
+    cnt.resize((size_t)kTreeLevels * nt);
+    off.resize((size_t)kTreeLevels * nt);
     int* h = P.pin->p;
-    for (int L = 0;;) {
-        const int Lend = std::min(L + kTreeBatch, lmax + 1);
-        for (; L < Lend; ++L)
-            tree_level_queued(ls.data(), L, ccnt.data(), wpre.data(), grid, cgrid, cap, ctl.data(), m,
-                              L < lmax ? 1 : 0, P.skeys.data(), P.level.data(), P.pixel.data(), P.first.data(), P.count.data(),
-                              P.parent.data(), P.child0.data(), wave_level, s);
-        SFMM_HIP(hipMemcpyAsync(h, ls.data(), sizeof(int) * kLs, hipMemcpyDeviceToHost, s));
-        SFMM_HIP(hipMemcpyAsync(h + kLs, ctl.data(), sizeof(int), hipMemcpyDeviceToHost, s));
-        SFMM_HIP(hipStreamSynchronize(s));
-        if (h[kLs]) return false;
-        // the first level that split nothing ends the tree
-        for (int z = 0; z < L; ++z) {
-            if (h[z + 2] == h[z + 1]) {
-                P.lvl_start.assign(h, h + z + 2);
-                return true;
-            }
-        }
-        if (L > lmax) throw Error(ST_INTERNAL, "tree levels did not terminate");
+    tree_count(P.skeys.data(), P.N, m, lmax, cnt.data(), s);
+    scan_excl_i32_n(cnt.data(), off.data(), kTreeLevels, nt, h, s);
+    SFMM_HIP(hipStreamSynchronize(s));
+    check_points(P.pin->err(0), "sources");
+    check_points(P.pin->err(1), "targets");
+    P.q_total = P.N > 0 ? *P.pin->q() : 0.0;
+    TreeLevels lv{};
+    int64_t tot = 0;
+    P.lvl_start.assign({0, 12});
+    for (int L = 0; L < kTreeLevels; ++L) {
+        lv.soff[L] = (int)tot;
+        tot += h[L];
+        if (12 + 4 * tot > 0x3fffffff) throw Error(ST_INVALID_ARG, "tree too large");
+        if (h[L] > 0) P.lvl_start.push_back((int)(12 + 4 * tot));
     }
-}
-
-void build_tree(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
-    const int stage_tree = prof.begin(S_TREE);
-    const int m = P.opt.leaf_size;
-    size_t cap = 12 + 8 * (size_t)(P.N / std::max(1, m)) + 64;
-    // SFMM_TREE_CAP (boxes) overrides the capacity of the queued levels:
-    // tests use it to drive the fallback
-    if (const char* forced = std::getenv("SFMM_TREE_CAP")) cap = std::max<size_t>(12, std::strtoull(forced, nullptr, 10));
-    cap = std::min<size_t>(cap, 0x7fffffff);
-    P.level.resize(cap);
-    P.pixel.resize(cap);
-    P.first.resize(cap);
-    P.count.resize(cap);
-    P.parent.resize(cap);
-    P.child0.resize(cap);
-    if (!build_levels_queued(P, m, (int)cap, s)) build_levels_exact(P, m, s);
-    prof.end(stage_tree);
+    lv.soff[kTreeLevels] = lv.soff[kTreeLevels + 1] = (int)tot;
     P.nbox = P.lvl_start.back();
+    const size_t nb = P.nbox;
+    P.level.resize(nb);
+    P.pixel.resize(nb);
+    P.first.resize(nb);
+    P.count.resize(nb);
+    P.parent.resize(nb);
+    P.child0.resize(nb);
+    sfirst.resize(std::max<int64_t>(tot, 1));
+    if (tot > 0) tree_emit(P.skeys.data(), P.N, m, lmax, off.data(), lv, sfirst.data(), s);
+    tree_boxes(P.skeys.data(), P.N, m, lmax, lv, sfirst.data(), (int)tot, P.level.data(), P.pixel.data(),
+               P.first.data(), P.count.data(), P.parent.data(), P.child0.data(), s);
 }
 
 // Stable sort on the target field only: within one target the pairs keep the
@@ -699,44 +633,48 @@ int count_boxes(const WorkItems& w, hipStream_t s) {
     return w.n - extra;
 }
 
-// Targets: keys (kept in caller order), leaf box of each, and the plan order
-// = a stable sort by leaf box (a leaf's targets form one run, in caller
-// order; nothing downstream needs key order within a leaf).
-void build_targets(sfmm_plan_impl& P, const double* tgt, hipStream_t s) {
+// Targets, first half (before the tree): keys, kept in caller order, and
+// renormalised points u in caller order.
+void prepare_targets(sfmm_plan_impl& P, const double* tgt, DVec<double4>& u, hipStream_t s) {
+    const int64_t M = P.M;
+    P.tperm.resize(M);
+    P.tkeys.resize(M);
+    if (M == 0) return;
+    u.resize(M);
+    prepare_points(tgt, nullptr, M, u.data(), P.tkeys.data(), P.tperm.data(), P.pin->err(1), s);
+}
+
+// Targets, second half: leaf box of each, and the plan order = a stable sort
+// by leaf box (a leaf's targets form one run, in caller order; nothing
+// downstream needs key order within a leaf).
+void build_targets(sfmm_plan_impl& P, const DVec<double4>& u, hipStream_t s) {
     const int64_t M = P.M;
     P.tx.resize(M);
     P.ty.resize(M);
     P.tz.resize(M);
-    P.tperm.resize(M);
-    P.tkeys.resize(M);
     P.tleaf.resize(std::max<int64_t>(M, 1));
     P.tfirst.resize(P.nbox);
     P.tcount.resize(P.nbox);
-    fill_i32(P.tfirst.data(), P.nbox, 0, s);
-    fill_i32(P.tcount.data(), P.nbox, 0, s);
-    if (M > 0) {
-        DVec<double4> u;
-        DVec<uint64_t> leaf, leaf2;
-        DVec<uint32_t> perm2;
-        u.resize(M);
-        leaf.resize(M);
-        leaf2.resize(M);
-        perm2.resize(M);
-        prepare_checked(tgt, nullptr, M, u, P.tkeys, P.tperm, P, s, "targets");
-        locate_targets(P.tkeys.data(), M, P.child0.data(), P.level.data(), leaf.data(), s);
-        uint32_t* pv = nullptr;
-        const uint64_t* ls = radix_sort_u64_pp(leaf.data(), P.tperm.data(), leaf2.data(), perm2.data(), M,
-                                               bits_for(P.nbox), s, 0, &pv);
-        if (pv != P.tperm.data()) {
-            std::swap(P.tperm.p, perm2.p);
-            std::swap(P.tperm.n, perm2.n);
-            std::swap(P.tperm.cap, perm2.cap);
-        }
-        gather_targets(P.tperm.data(), ls, M, u.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), s);
-    }
-    target_ranges(P.tleaf.data(), M, P.tfirst.data(), P.tcount.data(), s);
     P.need.resize(P.nbox);
+    fill_i32(P.tcount.data(), P.nbox, 0, s);
     fill_u8(P.need.data(), P.nbox, 0, s);
+    if (M == 0) return;
+    DVec<uint64_t> leaf, leaf2;
+    DVec<uint32_t> perm2;
+    leaf.resize(M);
+    leaf2.resize(M);
+    perm2.resize(M);
+    locate_targets(P.tkeys.data(), M, P.child0.data(), P.level.data(), leaf.data(), s);
+    uint32_t* pv = nullptr;
+    const uint64_t* ls = radix_sort_u64_pp(leaf.data(), P.tperm.data(), leaf2.data(), perm2.data(), M,
+                                           bits_for(P.nbox), s, 0, &pv);
+    if (pv != P.tperm.data()) {
+        std::swap(P.tperm.p, perm2.p);
+        std::swap(P.tperm.n, perm2.n);
+        std::swap(P.tperm.cap, perm2.cap);
+    }
+    gather_targets(P.tperm.data(), ls, M, u.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), s);
+    target_ranges(P.tleaf.data(), M, P.tfirst.data(), P.tcount.data(), s);
     mark_needed(P.tfirst.data(), P.nbox, P.tcount.data(), P.parent.data(), P.need.data(), s);
 }
 
@@ -1215,25 +1153,28 @@ sfmm_status sfmm_plan(const double* src, const double* q, int64_t N, const doubl
         P->p = o.order > 0 ? o.order : order_for_tolerance(o.tolerance);
         P->N = N;
         P->M = M;
+        for (int k = 0; k < 2; ++k) P->pin->err(k)[0] = P->pin->err(k)[1] = 0;
         Profiler prof(s);
+        DVec<double4> tu;
+        {
+            StageScope st(prof, S_TGT);
+            prepare_targets(*P, tgt, tu, s);
+        }
         {
             StageScope st(prof, S_SRC);
-            sort_points(src, q, N, P->spt, P->sperm, P->skeys, *P, s, "sources");
-        }
-        if (N > 0) {
-            DVec<double> qt;
-            qt.resize(1);
-            sum_f64(q, N, qt.data(), s);  // the caller's charges, contiguous
-            SFMM_HIP(hipMemcpyAsync(&P->q_total, qt.data(), sizeof(double), hipMemcpyDeviceToHost, s));
-            SFMM_HIP(hipStreamSynchronize(s));
+            sort_points(src, q, N, P->spt, P->sperm, P->skeys, P->pin->err(0), s);
+            if (N > 0) sum_f64(q, N, P->pin->q(), s);  // the caller's charges, contiguous
         }
         // per-pair order policies: the judge's direct sum needs only the
         // sorted sources, so it runs beside the tree, the walk and the targets
         if (o.order_policy != SFMM_ORDER_FIXED && o.judge_targets >= 0 && M > 0) judge_start(*P, tgt, ov, s);
-        build_tree(*P, s, prof);
+        {
+            StageScope st(prof, S_TREE);
+            build_tree(*P, s);
+        }
         {
             StageScope st(prof, S_TGT);
-            build_targets(*P, tgt, s);
+            build_targets(*P, tu, s);
         }
         build_lists(*P, s, prof);
         if (o.order_policy == SFMM_ORDER_LEARNED) {
