@@ -95,46 +95,55 @@ SFMM_HD double log_f64(double x) {
     return fma(de, ln2_hi, fma(de, ln2_lo, lm));
 }
 
-// The pair loop's log and reciprocal with a table in place of the atanh
-// series (the table-driven method of P. T. P. Tang, ACM TOMS 16 (1990)
-// 378-400, with a smaller table and a longer polynomial):
-// x = 2^e m, m in [1/2, 1); the top 7 fraction bits of m pick c_j =
-// 1/2 + (j + 1/2)/256 and tab[j] = {1/c_j, -log(1/c_j)} (log_tab_entry), so
-// that r = m/c_j - 1 (one FMA) has |r| < 2^-8 and
+// The pair loop's log and reciprocal from one table (the table-driven method
+// of P. T. P. Tang, ACM TOMS 16 (1990) 378-400, with a shorter polynomial):
+// x = 2^e m, m in [1/2, 1); the top 9 fraction bits of m pick c_j = 1/2 + (j +
+// 1/2)/1024 and tab[j] = {1/c_j, -log(1/c_j)} (log_tab_entry), so that r =
+// m/c_j - 1 (one FMA) has |r| <= 2^-10 and
 //   log x = e log 2 - log(1/c_j) + log(1 + r),
-// log(1 + r) = r + r^2 (-1/2 + r/3 - ... + r^5/7), first omitted term below
-// 2^-67.  The absolute error is a few 1e-16 (no relative bound near x = 1,
-// where the terms cancel; the sums it feeds only need the absolute one).
-// 1/x is the reciprocal refined by two Newton steps.
-// The Horner coefficients of q(r) after its leading 1/7 (the last one, -1/2,
-// is an inline constant of the FMA): kernels take them as an argument, which
-// keeps them in scalar registers.
+// log(1 + r) = r + r^2 (-1/2 + r/3 - r^2/4 + r^3/5), first omitted term below
+// 2^-62.  The absolute error is a few 1e-16 (no relative bound near x = 1,
+// where the terms cancel; the sums it feeds only need the absolute one), and
+// one rounded log 2 is enough: |e| 2.3e-17 is 3e-17 of |log x|.  The
+// reciprocal comes from the same r: 1/m = (1/c_j) (1 - r)(1 + r^2 + r^4), short
+// of the geometric series by r^6 < 2^-60, times 2^-e.  Against a hardware
+// reciprocal estimate (a quarter-rate instruction) with two Newton steps and a
+// degree-7 series, 34 full-rate VALU instructions a pair instead of 39 of
+// which one counts four.
+// The Horner coefficients (the last one, -1/2, is an inline constant of the
+// FMA): kernels take them as an argument, which keeps them in scalar registers.
 struct LogPoly {
-    double c6, c5, c4, c3;  // -1/6, 1/5, -1/4, 1/3
+    double c5, c4, c3, nln2;  // 1/5, -1/4, 1/3, -log 2
 };
-constexpr LogPoly kLogPoly = {-1.0 / 6.0, 1.0 / 5.0, -0.25, 1.0 / 3.0};
-constexpr int kLogTab = 128;
+constexpr LogPoly kLogPoly = {1.0 / 5.0, -0.25, 1.0 / 3.0, -kLog2};
+constexpr int kLogTab = 512;
 SFMM_HD double2 log_tab_entry(int j) {
-    const double c = 0.5 + (j + 0.5) / 256.0;
+    const double c = 0.5 + (j + 0.5) / 1024.0;
     const double ci = 1.0 / c;
     return make_double2(ci, -log_f64(ci));
 }
 
-SFMM_HD void log_recip_tab(double x, const double2* tab, const LogPoly& k, double* lg, double* inv) {
+// the table entry of a positive normal double whose high word is hi
+SFMM_HD double2 log_tab_at(uint32_t hi, const double2* tab) {
+    return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(tab) + (hi >> 7 & 0x1ff0u));
+}
+
+// log and reciprocal of a positive normal double x with its table entry t
+SFMM_HD void log_recip_at(double x, double2 t, const LogPoly& k, double* lg, double* inv) {
     int e;
     const double m = frexp(x, &e);
-    const int j = (int)((__builtin_bit_cast(unsigned long long, m) >> 45) & (kLogTab - 1));
-    const double2 t = tab[j];
     const double r = fma(m, t.x, -1.0);
-    double q = fma(1.0 / 7.0, r, k.c6);
-    q = fma(q, r, k.c5);
-    q = fma(q, r, k.c4);
+    const double u = r * r;
+    double q = fma(k.c5, r, k.c4);
     q = fma(q, r, k.c3);
     q = fma(q, r, -0.5);
-    const double lp = fma(r * r, q, r);
-    const double de = (double)e;
-    *lg = fma(de, 6.93147180369123816490e-01, fma(de, 1.90821492927058770002e-10, t.y + lp));  // log_f64's split
-    *inv = recip(x);
+    *lg = fma((double)-e, k.nln2, t.y + fma(u, q, r));
+    const double v = 1.0 - r;
+    *inv = ldexp(t.x * fma(u, fma(u, v, v), v), -e);
+}
+
+SFMM_HD void log_recip_tab(double x, const double2* tab, const LogPoly& k, double* lg, double* inv) {
+    log_recip_at(x, log_tab_at((uint32_t)(__builtin_bit_cast(unsigned long long, x) >> 32), tab), k, lg, inv);
 }
 
 struct cplx {

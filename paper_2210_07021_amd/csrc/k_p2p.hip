@@ -2,7 +2,7 @@
 // the sum of the Green's function and its tangent gradient over the particles
 // of T's close leaves.
 //
-// At planning time each direct-act list is split in two (near_split):
+// At planning time each direct-act list is split in two (near_lists):
 //   * a close leaf S whose centre is more than R_S / x from every target of
 //     T (and that holds enough particles for it to pay) is taken through its
 //     own multipole expansion (Lemma 1) at each target: k_m2p.  By Eq.
@@ -14,16 +14,16 @@
 //     particle of the clump directly.
 //   * every other close leaf is summed particle by particle: k_p2p.
 //
-// k_p2p: one 64-wide wavefront (a 64-thread workgroup) owns one target leaf
-// and takes its targets in groups of ng <= 64.  The lanes form ng teams of
-// L = floor(64 / ng) lanes, team t owning target t of the group.  The close
-// leaves' particle ranges are concatenated into one flat index space (wave
-// prefix sum of their counts); each tile of 128 particles is decoded once
-// (binary search by lane shuffles) and staged in LDS, and lane r of a team
-// takes particles r, r + L, ... of the tile.  The four partial sums stay in
-// registers across all tiles; at the end of the group the team's lanes are
-// summed in a fixed order through LDS.  No floating-point atomics: the
-// result is bitwise reproducible.
+// k_p2p: a wave (or, where there are few, a workgroup of four) owns one target
+// leaf (or a segment of its list) and takes its targets in groups of ng <= 64, TB targets per lane (two
+// in FP64, one in the precision tier) and teams of L = floor(64 / ceil(ng /
+// TB)) lanes.  The close leaves' particle ranges are concatenated into one
+// flat index space (wave prefix sum of their counts, 64 entries at a time);
+// each tile of 128 particles is decoded once (binary search by lane shuffles)
+// and staged in LDS, and lane r of a team takes particles r, r + L, ... of the tile.  The partial sums stay in registers
+// across all tiles; at the end of the group they are added over lanes and
+// waves in a fixed order through LDS.  No floating-point atomics: the result
+// is bitwise reproducible.
 //
 // Load balance: a leaf of a sparse region next to a dense clump can have
 // thousands of close leaves (every clump leaf fails the MAC against a big
@@ -328,15 +328,11 @@ __device__ __forceinline__ void emit_target_hess(int slot, int64_t o, double ps,
 // instructions, and each tile's FP32 partial sums (at most 256 terms) are
 // added to FP64 running sums.  The log terms, all of one sign, are summed
 // with Kahan compensation; the deflection terms largely cancel and are not.
-struct TileF64 {
-    double4 p[kTile];
-};
 struct TileF32 {
     float4 hi[kTile];  // x, y, z, q
     float4 lo[kTile];  // x, y, z low parts
 };
 
-__device__ __forceinline__ void tile_store(TileF64& t, int k, double4 v) { t.p[k] = v; }
 __device__ __forceinline__ void tile_store(TileF32& t, int k, double4 v) {
     const float xh = (float)v.x, yh = (float)v.y, zh = (float)v.z;
     t.hi[k] = make_float4(xh, yh, zh, (float)v.w);
@@ -360,38 +356,7 @@ __device__ __forceinline__ R npm_interior_log(R v, R t, R ln4t, int nterms) {
 }
 
 template <bool NPM>
-__device__ __forceinline__ void tile_pairs(const TileF64& t, const double2* ltab, const LogPoly& lk, const NpmK& nk,
-                                           int r, int L, int tn, double ax, double ay, double az, double& p0,
-                                           double& p1, double& p2, double& p3) {
-    for (int j = r; j < tn; j += L) {
-        const double4 sp = t.p[j];
-        const double dx = ax - sp.x, dy = ay - sp.y, dz = az - sp.z;
-        // |d|^2 of two distinct unit vectors is >= ~1e-32: zero only for
-        // coincident points, which take |d|^2 = 4 instead (log 4, and d = 0
-        // zeroes their deflection): both have a zero low word, so only the
-        // high word is switched (no branch: every lane takes the same path)
-        const double d2r = dx * dx + dy * dy + dz * dz;
-        const double d2 = __hiloint2double(d2r == 0.0 ? 0x40100000 : __double2hiint(d2r), __double2loint(d2r));
-        double lg, i0;
-        log_recip_tab(d2, ltab, lk, &lg, &i0);
-        double wi = sp.w * i0;
-        if constexpr (NPM) {
-            if (d2r < nk.four_t) {
-                const double u = 0.25 * d2r, v = u * nk.inv_t;
-                lg = npm_interior_log(v, nk.t, nk.ln4t, nk.nterms);
-                wi = sp.w * 0.25 * (2.0 * nk.inv_t - v * nk.inv_t - 1.0) / (1.0 - u);
-            }
-        }
-        p0 = fma(sp.w, lg, p0);
-        p1 = fma(wi, dx, p1);
-        p2 = fma(wi, dy, p2);
-        p3 = fma(wi, dz, p3);
-    }
-}
-
-template <bool NPM>
-__device__ __forceinline__ void tile_pairs(const TileF32& t, const double2*, const LogPoly&, const NpmK& nk, int r,
-                                           int L, int tn, double ax, double ay, double az, double& p0, double& p1,
+__device__ __forceinline__ void tile_pairs(const TileF32& t, const NpmK& nk, int r, int L, int tn, double ax, double ay, double az, double& p0, double& p1,
                                            double& p2, double& p3) {
     const float axh = (float)ax, ayh = (float)ay, azh = (float)az;
     const float axl = (float)(ax - (double)axh), ayl = (float)(ay - (double)ayh), azl = (float)(az - (double)azh);
@@ -435,45 +400,7 @@ __device__ __forceinline__ void tile_pairs(const TileF32& t, const double2*, con
 // (e_b.d)/|d|^4]; the lane sums hd = sum q (1 - n.d)/|d|^2 and h_ab = sum q
 // (e_a.d)(e_b.d)/|d|^4 (coincident points add nothing).
 template <bool NPM>
-__device__ __forceinline__ void tile_pairs_hess(const TileF64& t, const double2* ltab, const LogPoly& lk,
-                                                const NpmK& nk, int r, int L, int tn, double ax, double ay, double az,
-                                                const double* et, const double* ep, double* acc) {
-    for (int j = r; j < tn; j += L) {
-        const double4 sp = t.p[j];
-        const double dx = ax - sp.x, dy = ay - sp.y, dz = az - sp.z;
-        const double d2r = dx * dx + dy * dy + dz * dz;
-        const double d2 = __hiloint2double(d2r == 0.0 ? 0x40100000 : __double2hiint(d2r), __double2loint(d2r));
-        double lg, i0;
-        log_recip_tab(d2, ltab, lk, &lg, &i0);
-        double wi = sp.w * i0;
-        double wm = d2r == 0.0 ? 0.0 : wi;
-        double w2 = wm * i0;
-        if constexpr (NPM) {
-            if (d2r < nk.four_t) {
-                const double u = 0.25 * d2r, v = u * nk.inv_t, omu = 1.0 - u;
-                lg = npm_interior_log(v, nk.t, nk.ln4t, nk.nterms);
-                wi = sp.w * 0.25 * (2.0 * nk.inv_t - v * nk.inv_t - 1.0) / omu;
-                wm = wi;
-                w2 = sp.w * nk.a2 / (omu * omu);
-            }
-        }
-        acc[0] = fma(sp.w, lg, acc[0]);
-        acc[1] = fma(wi, dx, acc[1]);
-        acc[2] = fma(wi, dy, acc[2]);
-        acc[3] = fma(wi, dz, acc[3]);
-        const double nd = ax * dx + ay * dy + az * dz;
-        const double da = et[0] * dx + et[1] * dy + et[2] * dz;
-        const double db = ep[0] * dx + ep[1] * dy + ep[2] * dz;
-        acc[4] = fma(-nd, wm, acc[4] + wm);
-        acc[5] = fma(w2 * da, da, acc[5]);
-        acc[6] = fma(w2 * da, db, acc[6]);
-        acc[7] = fma(w2 * db, db, acc[7]);
-    }
-}
-
-template <bool NPM>
-__device__ __forceinline__ void tile_pairs_hess(const TileF32& t, const double2*, const LogPoly&, const NpmK& nk,
-                                                int r, int L, int tn, double ax, double ay, double az,
+__device__ __forceinline__ void tile_pairs_hess(const TileF32& t, const NpmK& nk, int r, int L, int tn, double ax, double ay, double az,
                                                 const double* et, const double* ep, double* acc) {
     const float axh = (float)ax, ayh = (float)ay, azh = (float)az;
     const float axl = (float)(ax - (double)axh), ayl = (float)(ay - (double)ayh), azl = (float)(az - (double)azh);
@@ -523,140 +450,247 @@ __device__ __forceinline__ void tile_pairs_hess(const TileF32& t, const double2*
     for (int k = 1; k < 8; ++k) acc[k] += (double)f[k];
 }
 
-template <class Tile, bool HESS, bool NPM>
-__global__ void __launch_bounds__(64) k_p2p(FmmCtx c, const int4* __restrict__ items,
-                                           const int* __restrict__ src, const int* __restrict__ tfirst,
-                                           const int* __restrict__ tcount, const double* __restrict__ tx,
-                                           const double* __restrict__ ty, const double* __restrict__ tz,
-                                           const uint32_t* __restrict__ tperm, double* __restrict__ psi,
-                                           double* __restrict__ defl, int64_t m_out, double* __restrict__ part,
-                                           LogPoly lk, double* __restrict__ hess, NpmK nk) {
-    // the tile and the end-of-group reduction share one LDS block (fewer
-    // bytes per wave, more waves per CU)
-    constexpr int NR = HESS ? 8 : 4;  // sums per lane: psi, alpha (and hd, h_tt, h_tp, h_pp)
-    constexpr size_t kSm = sizeof(Tile) > NR * 64 * sizeof(double) ? sizeof(Tile) : NR * 64 * sizeof(double);
-    __shared__ __align__(16) unsigned char sm[kSm];
-    Tile& tile = *reinterpret_cast<Tile*>(sm);
-    double(*red)[64] = reinterpret_cast<double(*)[64]>(sm);
-    const int lane = threadIdx.x;
-    // the FP64 pair loop's log table (made before the first tile's barrier)
-    __shared__ double2 ltab[std::is_same<Tile, TileF64>::value ? kLogTab : 1];
-    if constexpr (std::is_same<Tile, TileF64>::value) {
-        for (int j = lane; j < kLogTab; j += 64) ltab[j] = log_tab_entry(j);
+// FP64 pair terms of TB targets of one lane over one LDS tile.  a[b]: the
+// target; acc[b]: S, V (and, HESS, hd = sum q (1 - n.d)/|d|^2 and h_ab = sum q
+// (e_a.d)(e_b.d)/|d|^4 in the target's basis e[b], Sec. 2.2: H_ab = (q/2pi)
+// [delta_ab (1 - n.d)/|d|^2 - 2 (e_a.d)(e_b.d)/|d|^4]; coincident points add
+// nothing).  |d|^2 of two distinct unit vectors is >= ~1e-32, so its high word
+// is zero only for coincident points, which take |d|^2 = 4 instead (log 4, and
+// d = 0 zeroes their deflection).
+struct TileF64 {
+    double4 p[kTile];
+};
+
+__device__ __forceinline__ void tile_store(TileF64& t, int k, double4 v) { t.p[k] = v; }
+
+template <int TB, bool HESS, bool NPM>
+__device__ __forceinline__ void tile_pairs(const TileF64& t, const double2* ltab, const LogPoly& lk, const NpmK& nk,
+                                           int r, int L, int tn, const double (*a)[3], const double (*e)[6],
+                                           double (*acc)[HESS ? 8 : 4]) {
+    if (r >= tn) return;
+    double4 nx = t.p[r];
+    for (int j = r; j < tn; j += L) {
+        const double4 sp = nx;
+        nx = t.p[min(j + L, kTile - 1)];  // the next particle, read ahead
+        double d[TB][3], d2r[TB], d2[TB];
+        double2 tab[TB];
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            d[b][0] = a[b][0] - sp.x;
+            d[b][1] = a[b][1] - sp.y;
+            d[b][2] = a[b][2] - sp.z;
+            d2r[b] = d[b][0] * d[b][0] + d[b][1] * d[b][1] + d[b][2] * d[b][2];
+            const uint32_t h = (uint32_t)__double2hiint(d2r[b]), hi = h == 0 ? 0x40100000u : h;
+            d2[b] = __hiloint2double((int)hi, __double2loint(d2r[b]));
+            tab[b] = log_tab_at(hi, ltab);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // every table read is under way before the first is waited for
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            double lg, i0;
+            log_recip_at(d2[b], tab[b], lk, &lg, &i0);
+            double wi = sp.w * i0, wm = wi, w2 = 0.0;
+            if constexpr (HESS) {
+                wm = d2r[b] == 0.0 ? 0.0 : wi;
+                w2 = wm * i0;
+            }
+            if constexpr (NPM) {
+                if (d2r[b] < nk.four_t) {
+                    const double u = 0.25 * d2r[b], v = u * nk.inv_t, omu = 1.0 - u;
+                    lg = npm_interior_log(v, nk.t, nk.ln4t, nk.nterms);
+                    wi = sp.w * 0.25 * (2.0 * nk.inv_t - v * nk.inv_t - 1.0) / omu;
+                    wm = wi;
+                    w2 = sp.w * nk.a2 / (omu * omu);
+                }
+            }
+            acc[b][0] = fma(sp.w, lg, acc[b][0]);
+            acc[b][1] = fma(wi, d[b][0], acc[b][1]);
+            acc[b][2] = fma(wi, d[b][1], acc[b][2]);
+            acc[b][3] = fma(wi, d[b][2], acc[b][3]);
+            if constexpr (HESS) {
+                const double nd = a[b][0] * d[b][0] + a[b][1] * d[b][1] + a[b][2] * d[b][2];
+                const double da = e[b][0] * d[b][0] + e[b][1] * d[b][1] + e[b][2] * d[b][2];
+                const double db = e[b][3] * d[b][0] + e[b][4] * d[b][1] + e[b][5] * d[b][2];
+                acc[b][4] = fma(-nd, wm, acc[b][4] + wm);
+                acc[b][5] = fma(w2 * da, da, acc[b][5]);
+                acc[b][6] = fma(w2 * da, db, acc[b][6]);
+                acc[b][7] = fma(w2 * db, db, acc[b][7]);
+            }
+        }
     }
-    const int4 item = items[blockIdx.x];
-    const int T = item.x;
-    const int k0 = item.y, K = item.z - item.y;
-    const int t0 = tfirst[T], nt = tcount[T];
+}
+
+// Workgroups of four waves that share the log table.  WPI = 1: every wave
+// takes an item of its own, with no barrier after the table's (items are
+// sorted by work, so the four are alike).  WPI = 4
+// (few items, kP2PFewItems): the workgroup takes one item, every wave decodes
+// its entries by itself and takes every fourth tile, and the sums are added
+// over the waves; 228 leaves of 80,000 pairs each took 325 us as one wave
+// each, 61 us so.  Where there are many items the waves' repeated decoding
+// costs more than it gives (clustered-1e7: 3.1 ms).
+//   FP64: a lane takes TB = 2 targets against each particle it reads, so the
+//   LDS return path (3 x 16 bytes a pair for the particle and the table entry,
+//   128 bytes a cycle) stays behind the VALU, and ng targets keep
+//   2 floor(64 / ceil(ng / 2)) lanes busy where teams of floor(64 / ng) left
+//   up to half of them idle.
+//   FP32 (precision tier): a target per lane and teams of floor(64 / ng), as
+//   the order of its FP32 tile sums is part of its result.
+constexpr int kP2PFewItems = 4096;
+// waves of a workgroup: the precision tier needs no table, so its one-wave
+// items go one to a workgroup (nothing waits for the longest of four)
+constexpr int p2p_waves(bool f32, int wpi) { return wpi > 1 ? wpi : f32 ? 1 : 4; }
+
+template <int WPI>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (WPI > 1) {
+        __syncthreads();
+    } else {  // one wave: its LDS operations stay in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+template <bool F32, bool HESS, bool NPM, int WPI>
+__global__ void __launch_bounds__(64 * p2p_waves(F32, WPI)) __attribute__((amdgpu_waves_per_eu(HESS || NPM ? 2 : F32 ? 6 : 4)))
+k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restrict__ src,
+      const int* __restrict__ tfirst, const int* __restrict__ tcount, const double* __restrict__ tx,
+      const double* __restrict__ ty, const double* __restrict__ tz, const uint32_t* __restrict__ tperm,
+      double* __restrict__ psi, double* __restrict__ defl, int64_t m_out, double* __restrict__ part, LogPoly lk,
+      double* __restrict__ hess, NpmK nk) {
+    using Tile = std::conditional_t<F32, TileF32, TileF64>;
+    constexpr int TB = F32 ? 1 : 2, NR = HESS ? 8 : 4, NT = 64 * WPI, kP2PWaves = p2p_waves(F32, WPI);
+    // a wave's tile and its part of the end-of-group reduction share LDS
+    static_assert(sizeof(Tile) >= NR * 64 * sizeof(double), "the reduction fits the tile");
+    __shared__ __align__(16) unsigned char sm[sizeof(Tile) * kP2PWaves];
+    __shared__ double fin[kP2PWaves / WPI][NR][64];
+    __shared__ double2 ltab[F32 ? 1 : kLogTab];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int wave = WPI > 1 ? wv : 0, tid = WPI > 1 ? threadIdx.x : lane;  // within the item's team
+    const int team = WPI > 1 ? 0 : wv;
+    Tile& tile = reinterpret_cast<Tile*>(sm)[wv];
+    double(*red)[64] = reinterpret_cast<double(*)[64]>(sm + sizeof(Tile) * (WPI > 1 ? 0 : wv));  // [wave NR + q]
+    constexpr int RW = sizeof(Tile) / (64 * sizeof(double));  // rows of one wave's part
+    if constexpr (!F32) {
+        for (int j = threadIdx.x; j < kLogTab; j += 64 * kP2PWaves) ltab[j] = log_tab_entry(j);
+    }
+    if (kP2PWaves > 1) __syncthreads();
+    // one coefficient in a vector register: an FMA reads one scalar operand
+    asm("" : "+v"(lk.c4));
     const int ew = 2 * c.p + 2;
     const double4* __restrict__ spt = c.spt;
-
-    for (int tg = 0; tg < nt; tg += 64) {
-        const int ng = min(64, nt - tg);
-        const int g0 = t0 + tg;
-        const int L = 64 / ng;  // lanes per target
-        const int team = lane / L, r = lane - team * L;
-        const bool active = team < ng;
-        const int my = g0 + (active ? team : 0);
-        const double ax = tx[my], ay = ty[my], az = tz[my];
-        double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0;  // S, V partials of this lane
-        double qnear = 0.0;                              // lane partials of Q_near
-        double hacc[HESS ? 8 : 1] = {};                  // HESS: psi, alpha, hd, h_ab partials
-        double et[3], ep[3];
-        if constexpr (HESS) target_basis(ax, ay, az, et, ep);
-        for (int kc = 0; kc < K; kc += 64) {
-            const int kk = min(64, K - kc);
-            int cnt = 0, fst = 0;
-            if (lane < kk) {
-                const int S = src[k0 + kc + lane];
-                cnt = c.count[S];
-                fst = c.first[S];
-                qnear += c.mult[(size_t)S * ew + 1] * (4.0 * M_PI);
+    const int it = WPI > 1 ? blockIdx.x : blockIdx.x * kP2PWaves + wv;
+    if (it < nitems) {  // uniform across the item's team
+        const int4 item = items[it];
+        const int T = item.x;
+        const int k0 = item.y, K = item.z - item.y;
+        const int t0 = tfirst[T], nt = tcount[T];
+        for (int tg = 64 * blockIdx.y; tg < nt; tg += 64 * gridDim.y) {
+            const int ng = min(64, nt - tg);
+            const int g0 = t0 + tg;
+            const int nb = (ng + TB - 1) / TB;  // blocks of TB targets
+            const int L = 64 / nb;              // lanes per block
+            const int blk = lane / L, r = lane - blk * L;
+            const bool active = blk < nb;
+            double a[TB][3], e[TB][6], acc[TB][NR];
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                const int my = g0 + (active ? min(blk * TB + b, ng - 1) : 0);
+                a[b][0] = tx[my];
+                a[b][1] = ty[my];
+                a[b][2] = tz[my];
+                if constexpr (HESS) target_basis(a[b][0], a[b][1], a[b][2], e[b], e[b] + 3);
+#pragma unroll
+                for (int q = 0; q < NR; ++q) acc[b][q] = 0.0;
             }
-            // inclusive wave scan of the counts
-            int incl = cnt;
+            double qnear = 0.0;  // lane partials of Q_near (every wave of a team has them all)
+            for (int kc = 0; kc < K; kc += 64) {
+                const int kk = min(64, K - kc);
+                int cnt = 0, fst = 0;
+                if (lane < kk) {
+                    const int S = src[k0 + kc + lane];
+                    cnt = c.count[S];
+                    fst = c.first[S];
+                    qnear += c.mult[(size_t)S * ew + 1] * (4.0 * M_PI);
+                }
+                // inclusive wave scan of the counts
+                int incl = cnt;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int v = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += v;
-            }
-            const int excl = (lane < kk) ? incl - cnt : 0x7fffffff;
-            const int total = __shfl(incl, 63, 64);
-            for (int s0 = 0; s0 < total; s0 += kTile) {
-                const int tn = min(kTile, total - s0);
-                __syncthreads();  // previous tile fully consumed
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int v = __shfl_up(incl, o, 64);
+                    if (lane >= o) incl += v;
+                }
+                const int excl = (lane < kk) ? incl - cnt : 0x7fffffff;
+                const int total = __shfl(incl, 63, 64);
+                for (int s0 = wave * kTile; s0 < total; s0 += WPI * kTile) {
+                    const int tn = min(kTile, total - s0);
+                    double4 v[kTile / 64];
 #pragma unroll
-                for (int j = 0; j < kTile / 64; ++j) {
-                    const int f = s0 + j * 64 + lane;
-                    // entry e: the last one whose start is <= f
-                    int e = 0;
+                    for (int j = 0; j < kTile / 64; ++j) {
+                        const int f = s0 + j * 64 + lane;
+                        // entry e: the last one whose start is <= f
+                        int e_ = 0;
 #pragma unroll
-                    for (int step = 32; step > 0; step >>= 1) {
-                        const int cand = e + step;
-                        const int v = __shfl(excl, cand, 64);
-                        if (v <= f) e = cand;
+                        for (int step = 32; step > 0; step >>= 1) {
+                            const int cand = e_ + step;
+                            if (__shfl(excl, cand, 64) <= f) e_ = cand;
+                        }
+                        const int base = __shfl(fst, e_, 64) - __shfl(excl, e_, 64);
+                        v[j] = spt[base + min(f, total - 1)];  // past the end: the last particle again
                     }
-                    const int base = __shfl(fst, e, 64) - __shfl(excl, e, 64);
-                    if (f < total) {
-                        const int i = base + f;
-                        tile_store(tile, j * 64 + lane, spt[i]);
+                    team_sync<1>();  // the wave's last tile is consumed
+#pragma unroll
+                    for (int j = 0; j < kTile / 64; ++j) tile_store(tile, j * 64 + lane, v[j]);
+                    team_sync<1>();
+                    if (active) {
+                        if constexpr (!F32) tile_pairs<TB, HESS, NPM>(tile, ltab, lk, nk, r, L, tn, a, e, acc);
+                        else if constexpr (HESS)
+                            tile_pairs_hess<NPM>(tile, nk, r, L, tn, a[0][0], a[0][1], a[0][2], e[0], e[0] + 3,
+                                                 acc[0]);
+                        else
+                            tile_pairs<NPM>(tile, nk, r, L, tn, a[0][0], a[0][1], a[0][2], acc[0][0], acc[0][1],
+                                            acc[0][2], acc[0][3]);
                     }
                 }
-                __syncthreads();
-                if (active) {
-                    if constexpr (HESS) tile_pairs_hess<NPM>(tile, ltab, lk, nk, r, L, tn, ax, ay, az, et, ep, hacc);
-                    else tile_pairs<NPM>(tile, ltab, lk, nk, r, L, tn, ax, ay, az, p0, p1, p2, p3);
+            }
+            const double qn = wave_sum(qnear);
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                team_sync<WPI>();  // the tiles (or the other target's sums) are consumed
+#pragma unroll
+                for (int q = 0; q < NR; ++q) red[wave * RW + q][lane] = acc[b][q];
+                team_sync<WPI>();
+                for (int x = tid; x < nb * NR; x += NT) {
+                    const int q = x / nb, k = x - q * nb;
+                    if (k * TB + b >= ng) continue;
+                    double s = 0.0;
+                    for (int w = 0; w < WPI; ++w)
+                        for (int l = 0; l < L; ++l) s += red[w * RW + q][k * L + l];
+                    fin[team][q][k * TB + b] = s;
                 }
             }
-        }
-        const double qn = wave_sum(qnear);
-        if constexpr (HESS) {
-            p0 = hacc[0];
-            p1 = hacc[1];
-            p2 = hacc[2];
-            p3 = hacc[3];
-        }
-        __syncthreads();  // the last tile fully consumed before red overwrites it
-        red[0][lane] = p0;
-        red[1][lane] = p1;
-        red[2][lane] = p2;
-        red[3][lane] = p3;
-        if constexpr (HESS) {
-#pragma unroll
-            for (int q = 4; q < 8; ++q) red[q][lane] = hacc[q];
-        }
-        __syncthreads();
-        if (lane < ng) {
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-            double sh[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int j = lane * L; j < lane * L + L; ++j) {
-                s0 += red[0][j];
-                s1 += red[1][j];
-                s2 += red[2][j];
-                s3 += red[3][j];
+            team_sync<WPI>();
+            if (tid < ng) {
+                const double(*fs)[64] = fin[team];
+                const int me = g0 + tid;
+                const double s0 = fs[0][tid], s1 = fs[1][tid], s2 = fs[2][tid], s3 = fs[3][tid];
+                const double mx = tx[me], myy = ty[me], mz = tz[me];
+                const double il = 1.0 / sqrt(mx * mx + myy * myy + mz * mz);
+                const double ux = mx * il, uy = myy * il, uz = mz * il;
+                const double vr = ux * s1 + uy * s2 + uz * s3;
+                const int slot = item.w < 0 ? -1 : item.w + tg + tid;
                 if constexpr (HESS) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) sh[q] += red[4 + q][j];
+                    const double h4 = fs[4][tid], h5 = fs[5][tid], h6 = fs[6][tid], h7 = fs[7][tid];
+                    const double h[3] = {(h4 - 2.0 * h5) * kInv2Pi, -2.0 * h6 * kInv2Pi, (h4 - 2.0 * h7) * kInv2Pi};
+                    emit_target_hess(slot, tperm[me], (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
+                                     (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, h, part, psi, defl, hess,
+                                     m_out);
+                } else {
+                    emit_target(slot, tperm[me], (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
+                                (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, part, psi, defl, m_out);
                 }
             }
-            const int me = g0 + lane;
-            const double mx = tx[me], myy = ty[me], mz = tz[me];
-            const double il = 1.0 / sqrt(mx * mx + myy * myy + mz * mz);
-            const double ux = mx * il, uy = myy * il, uz = mz * il;
-            const double vr = ux * s1 + uy * s2 + uz * s3;
-            if constexpr (HESS) {
-                const double h[3] = {(sh[0] - 2.0 * sh[1]) * kInv2Pi, -2.0 * sh[2] * kInv2Pi,
-                                     (sh[0] - 2.0 * sh[3]) * kInv2Pi};
-                emit_target_hess(item.w < 0 ? -1 : item.w + tg + lane, tperm[me],
-                                 (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
-                                 (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, h, part, psi, defl, hess, m_out);
-            } else {
-                emit_target(item.w < 0 ? -1 : item.w + tg + lane, tperm[me], (s0 + (1.0 - kLog4) * qn) * kInv4Pi,
-                            (s1 - ux * vr) * kInv2Pi, (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, part, psi,
-                            defl, m_out);
-            }
+            team_sync<WPI>();  // fin and the tiles are reused by the next group
         }
-        __syncthreads();  // red is reused by the next group
     }
 }
 
@@ -807,21 +841,30 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
     if (!part) part = w.part;
     const NpmK nk = npm_params(c.npm_sigma);
     const bool npm = c.npm_sigma > 0.0;
-#define P2P_(T, H, N)                                                                                          \
-    k_p2p<T, H, N><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
-                                                defl, m_out, part, kLogPoly, hess, nk)
-#define P2P_N(T, H)              \
-    if (npm) P2P_(T, H, true);   \
-    else P2P_(T, H, false)
+    // few items: a workgroup each, groups of 64 targets of one leaf side by side
+    const bool few = w.n < kP2PFewItems;
+    const int pw = p2p_waves(fp32, few ? 4 : 1);
+    const dim3 g(few ? (unsigned)w.n : nblk(w.n, pw), few ? 2 : 1);
+#define P2P_W(T, H, N, W)                                                                                       \
+    k_p2p<T, H, N, W><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
+                                                   defl, m_out, part, kLogPoly, hess, nk)
+#define P2P_(T, H, N)             \
+    if (few) P2P_W(T, H, N, 4);   \
+    else P2P_W(T, H, N, 1)
+#define P2P_N(T, H)                  \
+    if (npm) {                       \
+        P2P_(T, H, true);            \
+    } else {                         \
+        P2P_(T, H, false);           \
+    }
     if (fp32) {
-        if (hess) P2P_N(TileF32, true);
-        else P2P_N(TileF32, false);
+        if (hess) P2P_N(true, true) else P2P_N(true, false)
     } else {
-        if (hess) P2P_N(TileF64, true);
-        else P2P_N(TileF64, false);
+        if (hess) P2P_N(false, true) else P2P_N(false, false)
     }
 #undef P2P_N
 #undef P2P_
+#undef P2P_W
     SFMM_LAUNCH_CHECK();
     reduce_items(w, tfirst, tcount, tperm, psi, defl, m_out, part, s, hess);
 }
