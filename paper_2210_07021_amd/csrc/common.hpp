@@ -209,12 +209,17 @@ constexpr int kWalkDtrig = 14;
 void walk_boxes(int nb, const double* cen, const double* rad, const double* gdd, const int* child0, const int* count,
                 double c_s, double c_t, double sigma, double4* geo, double2* strig, double4* ttrig, int2* cc,
                 double* dtrig, hipStream_t s);
-// Lanes per target box of the FP64 team M2L over n boxes: two
-// (k_m2l_team2) when two-lane teams still fill the chip (two waves per SIMD
-// on 256 CUs: 131072 lanes), four (k_m2l_team) below that; and of the
-// precision tier's FP32 team M2L (k_m2l_team_f32).
-constexpr int64_t kM2LTeam2MinBoxes = 65536;
-inline int m2l_team_width(int64_t n) { return n >= kM2LTeam2MinBoxes ? 2 : 4; }
+// Lanes per target box of the FP64 team M2L over n boxes (k_m2l_team,
+// k_m2l_team2).  A translation is ~10 us of one lane's time, so the pass takes
+// its longest list's rounds as long as the chip has room: a whole wave a box
+// up to 6144 boxes, 16 lanes up to 81920, and two where those fill the chip
+// (fewest idle lanes in a list's last round).  Measured at p = 38, us with
+// 4 / 16 / 64 lanes: 304 boxes 137 / 39 / 18; 38,000 boxes 299 / 211 / 427; at
+// p = 28, 6,600 boxes 151 / 56 / 54; with 4 or 2 / 16 lanes: 45,000 boxes 318 /
+// 235, 60,000 boxes 352 / 287, 87,000 boxes 566 / 555, 238,000 boxes 1128 / 1505.
+// And of the precision tier's FP32 team M2L (k_m2l_team_f32).
+constexpr int64_t kM2LWaveMaxBoxes = 6144, kM2LRowMaxBoxes = 81920;
+inline int m2l_team_width(int64_t n) { return n <= kM2LWaveMaxBoxes ? 64 : n <= kM2LRowMaxBoxes ? 16 : 2; }
 constexpr int kM2LTeamF32 = 4;
 // One walk round in three launches (classify + per-chunk scans, scan of the
 // chunk totals into tot[3]: children pairs, M2L pairs, P2P pairs; emit),

@@ -476,52 +476,6 @@ SFMM_HD void translate_add_f32_d(const float* __restrict__ A, double C, double Q
     accCQ[1] += Q;
 }
 
-// Lemma 1 for a set of particles about centre f with scale rho; C carries the
-// zero-mean gauge's share sum q / (4 pi) (Eq. STAND_CONDITION).
-template <int P>
-struct P2MAcc {
-    double sre[P], sim[P];
-    double slog, sq;
-};
-
-template <int P>
-SFMM_HD void p2m_init(P2MAcc<P>& a) {
-#pragma unroll
-    for (int l = 0; l < P; ++l) a.sre[l] = a.sim[l] = 0.0;
-    a.slog = 0.0;
-    a.sq = 0.0;
-}
-
-template <int P>
-SFMM_HD void p2m_add(P2MAcc<P>& a, const Frame& f, double inv_rho, double x, double y, double z, double q) {
-    double opc;
-    cplx w = stereo(f, x, y, z, &opc);
-    w.re *= inv_rho;
-    w.im *= inv_rho;
-    cplx pw = w;
-#pragma unroll
-    for (int l = 0; l < P; ++l) {
-        a.sre[l] = fma(q, pw.re, a.sre[l]);
-        a.sim[l] = fma(q, pw.im, a.sim[l]);
-        pw = cmul(pw, w);
-    }
-    a.slog = fma(q, log_f64(0.5 * opc), a.slog);  // 2 log cos(theta/2) = log((1 + cos)/2)
-    a.sq += q;
-}
-
-template <int P>
-SFMM_HD void p2m_finish(const P2MAcc<P>& a, double* out) {
-    const double Q = a.sq * kInv4Pi;
-    out[0] = a.slog * kInv4Pi - Q * kLog2 + Q;
-    out[1] = Q;
-#pragma unroll
-    for (int l = 1; l <= P; ++l) {
-        const double s = -kInv4Pi / l;
-        out[2 * l] = s * a.sre[l - 1];
-        out[2 * l + 1] = s * a.sim[l - 1];
-    }
-}
-
 // Local expansion at a point (Sec. 3.6), pole-free: psi_e and the tangent
 // vector alpha_e = grad psi_e in global axes.  With f(w) = sum A_l w^l,
 // psi_e = C + Q log(1 + cos theta) + 2 Re f and, in the orthonormal basis of

@@ -30,6 +30,18 @@ __device__ __forceinline__ double quad_sum(double v) {
     return v + dpp_quad<0x4E>(v);  // quad_perm [2, 3, 0, 1]: lane ^ 2
 }
 
+// Sum over the quads of a team of TW lanes (one quad, or the four of a DPP
+// row: row_ror:4 and row_ror:8)
+template <int TW>
+__device__ __forceinline__ double row_sum(double v) {
+    static_assert(TW == 4 || TW == 16, "a quad or a row");
+    if constexpr (TW == 16) {
+        v += dpp_quad<0x124>(v);
+        v += dpp_quad<0x128>(v);
+    }
+    return v;
+}
+
 static unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b > 0 ? (n + b - 1) / b : 1); }
 
 __device__ __forceinline__ Frame box_frame(const double* cen, int b, double* rho) {
@@ -39,76 +51,130 @@ __device__ __forceinline__ Frame box_frame(const double* cen, int b, double* rho
 }
 
 // Lemma 1 on every leaf (an empty leaf gets a zero record: with the split
-// boxes written by k_m2m, every record is written and needs no clearing)
-template <int P>
+// boxes written by k_m2m, every record is written and needs no clearing), TW
+// lanes per leaf in quads.  A quad takes four particles at a time: each lane
+// forms the local coordinate w and the log of one, and of all four (w and q
+// from its neighbours by lane exchanges) it sums the powers l = r + 1, r + 5,
+// .. only (w^(r + 1), then steps of w^4): a quarter of the accumulators, and
+// the quad's sums need no reduction.  C carries the zero-mean gauge's share
+// sum q / (4 pi) (Eq. STAND_CONDITION).
+// Bound by FP64 VALU issue (~470 instructions for a quad's four particles) and
+// the spread of the leaf sizes over a wave; one lane per leaf held all the sums
+// (160 registers, one wave a SIMD) and read its particles alone.  p = 38: 1e7
+// particles 385 -> 337 us (TW = 4), 1e6 109 -> 54 and 1e4 59 -> 9 (TW = 16).
+// Measured with TW = 4 / 16: 77,000 boxes 69 / 54 us, 124,000 98 / 91, 140,000
+// 94 / 96, 620,000 337 / 398.
+constexpr int kP2MRowMaxBoxes = 131072;
+template <int P, int TW>
 __global__ void __launch_bounds__(128) k_p2m(FmmCtx c, int nb) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb || c.child0[b] >= 0) return;
-    if (c.count[b] == 0) {
-        double* out = c.mult + (size_t)b * (2 * P + 2);
-        for (int k = 0; k < 2 * P + 2; ++k) out[k] = 0.0;
+    constexpr int NL = (P + 3) / 4;
+    const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int b = (int)(gid / TW), lane = threadIdx.x & (TW - 1), r = threadIdx.x & 3;
+    if (b >= nb || c.child0[b] >= 0) return;  // the lanes of a team leave together
+    double* out = c.mult + (size_t)b * (2 * P + 2);
+    const int i0 = c.first[b], n = c.count[b];
+    if (n == 0) {
+        for (int k = lane; k < 2 * P + 2; k += TW) out[k] = 0.0;
         return;
     }
     double rho;
     const Frame f = box_frame(c.cen, b, &rho);
     const double inv_rho = 1.0 / rho;
-    P2MAcc<P> a;
-    p2m_init<P>(a);
-    const int i0 = c.first[b], i1 = i0 + c.count[b];
-    for (int i = i0; i < i1; ++i) {
-        const double4 v = c.spt[i];
-        p2m_add<P>(a, f, inv_rho, v.x, v.y, v.z, v.w);
+    cplx acc[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) acc[k] = {0.0, 0.0};
+    double slog = 0.0, sq = 0.0;
+    for (int i = 0; i < n; i += TW) {  // past the end: the leaf's first particle with charge zero
+        const bool live = i + lane < n;
+        const double4 v = c.spt[live ? i0 + i + lane : i0];
+        const double q = live ? v.w : 0.0;
+        double opc;
+        cplx w = stereo(f, v.x, v.y, v.z, &opc);
+        w.re *= inv_rho;
+        w.im *= inv_rho;
+        slog = fma(q, log_f64(0.5 * opc), slog);  // 2 log cos(theta/2) = log((1 + cos)/2)
+        sq += q;
+        auto add = [&](double wre, double wim, double qj) {
+            const cplx w1 = {wre, wim}, w2 = cmul(w1, w1), w3 = cmul(w2, w1), w4 = cmul(w2, w2);
+            const cplx lo = (r & 1) ? w2 : w1, hi = (r & 1) ? w4 : w3;
+            cplx pw = (r & 2) ? hi : lo;
+            pw = {qj * pw.re, qj * pw.im};
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+                acc[k].re += pw.re;
+                acc[k].im += pw.im;
+                pw = cmul(pw, w4);
+            }
+        };
+        add(dpp_quad<0x00>(w.re), dpp_quad<0x00>(w.im), dpp_quad<0x00>(q));  // quad_perm [j, j, j, j]
+        add(dpp_quad<0x55>(w.re), dpp_quad<0x55>(w.im), dpp_quad<0x55>(q));
+        add(dpp_quad<0xAA>(w.re), dpp_quad<0xAA>(w.im), dpp_quad<0xAA>(q));
+        add(dpp_quad<0xFF>(w.re), dpp_quad<0xFF>(w.im), dpp_quad<0xFF>(q));
     }
-    p2m_finish<P>(a, c.mult + (size_t)b * (2 * P + 2));
+    slog = row_sum<TW>(quad_sum(slog));
+    sq = row_sum<TW>(quad_sum(sq));
+    if (lane == 0) {
+        const double Q = sq * kInv4Pi;
+        out[0] = slog * kInv4Pi - Q * kLog2 + Q;
+        out[1] = Q;
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int l = 4 * k + r + 1;
+        const cplx a = {row_sum<TW>(acc[k].re), row_sum<TW>(acc[k].im)};
+        if (lane < 4 && l <= P) {
+            const double s = -kInv4Pi / l;
+            out[2 * l] = s * a.re;
+            out[2 * l + 1] = s * a.im;
+        }
+    }
 }
 
-// Lemma 3 with four lanes per target box (a team): in each round lane r of
-// the team translates entry k0 + 4 round + r of the box's list (a zero
-// record past the end); every output entry is summed over the team by two
-// lane exchanges as it is formed and added by the lane that owns it (entry
-// k by lane k mod 4), so no lane holds the whole accumulator and two waves
-// fit on a SIMD.
-// Lemma 3 with four lanes per target box (a team): in each round lane r of
-// the team translates entry k0 + 4 round + r of the box's list (a zero
-// record past the end).  Every output entry is summed over the team as it
-// is formed (quad_sum); the accumulator is shared out: lane r owns entries
+// Lemma 3 with NQ quads of lanes per target box (a team): in each round lane
+// r of quad h translates entry k0 + 4 (NQ round + h) + r of the box's list (a
+// zero record past the end).  Every output entry is summed over the quad as it
+// is formed (quad_sum); the quad's accumulator is shared out: lane r owns entries
 // 2 + 4q + r (slot q) and, for r < 2, entry r (slot NG), in LDS.  The sums
 // of entries 2 + 4q .. 5 + 4q are held until the group is complete and then
 // each lane adds its own with one LDS add (single writer per slot, so the
-// sums keep their round order).  No lane holds the whole accumulator: two
-// waves fit on a SIMD.  Target boxes are taken in `order` (most rounds
+// sums keep their round order); at the end the quads' accumulators are added
+// in quad order.  No lane holds the whole accumulator: two waves fit on a
+// SIMD.  Target boxes are taken in `order` (most rounds
 // first, so the teams of a wave carry the same work).  P is the order of the
 // translation, c.p that of the records (P <= c.p: a per-pair order policy
 // runs one pass per order with the pairs of that order, adding to the
 // records' first 2P + 2 entries, acc_in = true; a first pass, acc_in =
 // false, writes whole records).
-template <int P>
+// Bound by FP64 FMA issue (~3000 a translation at p = 38) where the boxes fill
+// the chip and by the longest list's rounds where they do not.
+template <int P, int NQ>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
 k_m2l_team(FmmCtx c, const int* order, int n, const int* off, const int* src, bool acc_in) {
     constexpr int EW = 2 * P + 2, NG = (2 * P + 3) / 4, NA = NG + 1;
     __shared__ double sacc[NA * 128];
     double* acc = sacc + threadIdx.x;  // slot q at acc[q * 128]
     const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = gid >> 2, r = gid & 3;
-    if (i >= n) return;  // the four lanes of a team leave together
+    constexpr int TW = 4 * NQ;  // lanes of the team, within one wave
+    const int i = gid / TW, r = gid & 3, h = (gid & (TW - 1)) >> 2;
+    if (i >= n) return;  // the lanes of a team leave together
     const int t = order ? order[i] : i;
     const int k0 = off[t], k1 = off[t + 1];
     const size_t ew = 2 * (size_t)c.p + 2;
     double* out = c.local + (size_t)t * ew;
     if (k0 == k1) {
         if (!acc_in)
-            for (size_t k = r; k < ew; k += 4) out[k] = 0.0;
+            for (size_t k = gid & (TW - 1); k < ew; k += TW) out[k] = 0.0;
         return;
     }
     auto entry = [&](int q) { return q < NG ? 2 + 4 * q + r : r; };  // entry held in slot q (r < 2 for slot NG)
     for (int q = 0; q < NA; ++q) {
         const int e = entry(q);
-        acc[q * 128] = (acc_in && e < EW && (q < NG || r < 2)) ? out[e] : 0.0;
+        acc[q * 128] = (acc_in && h == 0 && e < EW && (q < NG || r < 2)) ? out[e] : 0.0;
     }
     double rho_t;
     const Frame ft = box_frame(c.cen, t, &rho_t);
-    for (int kb = k0; kb < k1; kb += 4) {
-        const int k = kb + r;
+    for (int kb = k0; kb < k1; kb += TW) {  // the quads of a team keep together: the last rounds may be idle
+        const int k = kb + 4 * h + r;
         const bool live = k < k1;
         const int s = live ? src[k] : src[k0];
         double rho_s;
@@ -134,12 +200,17 @@ k_m2l_team(FmmCtx c, const int* order, int n, const int* off, const int* src, bo
         if (r < 2) __hip_atomic_fetch_add(acc + NG * 128, r == 0 ? cq[0] : cq[1], __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    for (int q = 0; q < NA; ++q) {
+    // quad h finishes slots h, h + NQ, ..
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const double* first = sacc + (threadIdx.x & ~(TW - 1)) + r;
+    for (int q = h; q < NA; q += NQ) {
         const int e = entry(q);
-        if (e < EW && (q < NG || r < 2)) out[e] = acc[q * 128];
+        double v = first[q * 128];
+        for (int j = 1; j < NQ; ++j) v += first[q * 128 + 4 * j];
+        if (e < EW && (q < NG || r < 2)) out[e] = v;
     }
     if (!acc_in)
-        for (size_t k = EW + r; k < ew; k += 4) out[k] = 0.0;
+        for (size_t k = EW + (gid & (TW - 1)); k < ew; k += TW) out[k] = 0.0;
 }
 
 // Lemma 3 with two lanes per target box (a team): in each round lane r of
@@ -150,11 +221,10 @@ k_m2l_team(FmmCtx c, const int* order, int n, const int* off, const int* src, bo
 // NG), in LDS.  The sums of entries 2 + 2q and 3 + 2q are held until both
 // are formed and then each lane adds its own with one LDS add (single
 // writer per slot, so the sums keep their round order).  No lane holds the
-// whole accumulator: two waves fit on a SIMD.  Against k_m2l_team (four
-// lanes, two DPP steps a sum, lists padded to rounds of four) this runs ~7 %
-// faster at p = 38 with fewer spilled registers, when there are enough boxes
-// to fill the chip with half as many lanes (m2l_team_width).  Order, P and
-// acc_in as in k_m2l_team.
+// whole accumulator: two waves fit on a SIMD.  Against k_m2l_team (whole quads,
+// two DPP steps a sum, lists padded to its rounds) it leaves the fewest lanes
+// idle, where there are enough boxes to fill the chip with two lanes each
+// (m2l_team_width).  Order, P and acc_in as in k_m2l_team.
 template <int P>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2)))
 k_m2l_team2(FmmCtx c, const int* order, int n, const int* off, const int* src, bool acc_in) {
@@ -423,9 +493,15 @@ __global__ void __launch_bounds__(128) k_l2p_hess(FmmCtx c, const double* tx, co
 
 void fmm_p2m(const FmmCtx& c, int nb, hipStream_t s) {
     if (nb <= 0) return;
-#define L_(P) case P: k_p2m<P><<<nblk(nb, 128), 128, 0, s>>>(c, nb); break;
-    SFMM_DISPATCH(c.p, L_)
+    if (nb <= kP2MRowMaxBoxes) {
+#define L_(P) case P: k_p2m<P, 16><<<nblk(16 * (int64_t)nb, 128), 128, 0, s>>>(c, nb); break;
+        SFMM_DISPATCH(c.p, L_)
 #undef L_
+    } else {
+#define L_(P) case P: k_p2m<P, 4><<<nblk(4 * (int64_t)nb, 128), 128, 0, s>>>(c, nb); break;
+        SFMM_DISPATCH(c.p, L_)
+#undef L_
+    }
     SFMM_LAUNCH_CHECK();
 }
 
@@ -433,15 +509,22 @@ void fmm_m2l(const FmmCtx& c, int p, bool acc_in, const int* order, int n, const
              hipStream_t s) {
     if (n <= 0) return;
     if (p < 1 || p > c.p) throw Error(ST_INTERNAL, "M2L order above the record order");
-    if (m2l_team_width(n) == 2) {
-#define L_(P) case P: k_m2l_team2<P><<<nblk(2 * (int64_t)n, 128), 128, 0, s>>>(c, order, n, off, src, acc_in); break;
-        SFMM_DISPATCH(p, L_)
-#undef L_
+    const int tw = m2l_team_width(n);
+#define LAUNCH_TEAM_(NAME) NAME<<<nblk((int64_t)tw * n, 128), 128, 0, s>>>(c, order, n, off, src, acc_in)
+#define L2_(P) case P: LAUNCH_TEAM_(k_m2l_team2<P>); break;
+#define L16_(P) case P: LAUNCH_TEAM_((k_m2l_team<P, 4>)); break;
+#define L64_(P) case P: LAUNCH_TEAM_((k_m2l_team<P, 16>)); break;
+    if (tw == 2) {
+        SFMM_DISPATCH(p, L2_)
+    } else if (tw == 16) {
+        SFMM_DISPATCH(p, L16_)
     } else {
-#define L_(P) case P: k_m2l_team<P><<<nblk(4 * (int64_t)n, 128), 128, 0, s>>>(c, order, n, off, src, acc_in); break;
-        SFMM_DISPATCH(p, L_)
-#undef L_
+        SFMM_DISPATCH(p, L64_)
     }
+#undef LAUNCH_TEAM_
+#undef L2_
+#undef L16_
+#undef L64_
     SFMM_LAUNCH_CHECK();
 }
 
