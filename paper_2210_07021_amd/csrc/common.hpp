@@ -154,6 +154,19 @@ void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bits, hipStre
 uint64_t* radix_sort_u64_pp(uint64_t* keys, uint32_t* vals, uint64_t* kalt, uint32_t* valt, int64_t n, int bits,
                             hipStream_t s, int begin_bit, uint32_t** vout, uint32_t* lo_out = nullptr,
                             uint32_t* hi_out = nullptr);
+// exclusive scan of each of nrow rows of n ints (rs ints apart, rs a multiple
+// of 4); the rows' sums to tot
+void scan_rows(const int* hist, int nrow, int n, int rs, int* offs, int* tot, hipStream_t s);
+// Which sort takes (key, value) pairs (k_sort.hip): one workgroup, in place; a
+// split by sampled quantiles and one workgroup a bucket (kalt / valt: scratch,
+// the result in keys / vals); the radix sort takes the rest.
+constexpr int64_t kSampleSortMax = 10 << 20;
+constexpr int kSampleMinBits = 24;
+bool sort_in_lds(int64_t n);
+bool sort_by_sample(int64_t n, int bits);
+void block_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bits, hipStream_t s);
+void sample_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* kalt, uint32_t* valt, int64_t n, int bits,
+                     hipStream_t s);
 void sum_f64(const double* x, int64_t n, double* out, hipStream_t s, int stride = 1);  // sum of x[i * stride]
 void sum_i64(const long long* x, int64_t n, long long* out, hipStream_t s);
 

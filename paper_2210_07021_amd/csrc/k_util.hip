@@ -409,6 +409,11 @@ __global__ void __launch_bounds__(kScanThreads) k_rs_rowscan(const int* __restri
     if (threadIdx.x == 0) dtot[d] = carry;
 }
 
+void scan_rows(const int* hist, int nrow, int n, int rs, int* offs, int* tot, hipStream_t s) {
+    k_rs_rowscan<<<nrow, kScanThreads, 0, s>>>(hist, n, rs, offs, tot);
+    SFMM_LAUNCH_CHECK();
+}
+
 // Stable scatter of one tile of kRsTile keys.  Wave w owns the tile's w-th
 // quarter and walks it in rounds of 64 keys: lanes with equal digits find
 // each other by ballots over the digit's bits, and a wave-private count per
@@ -511,6 +516,17 @@ uint64_t* radix_sort_u64_pp(uint64_t* keys, uint32_t* vals, uint64_t* kalt, uint
                             hipStream_t s, int begin_bit, uint32_t** vout, uint32_t* lo_out, uint32_t* hi_out) {
     if (vout) *vout = vals;
     if (n <= 1 || bits <= begin_bit) return keys;
+    bits = begin_bit + (bits - begin_bit + 7) / 8 * 8;  // whole digits
+    if (vals && !lo_out && begin_bit == 0) {
+        if (sort_in_lds(n)) {
+            block_sort_u64(keys, vals, n, bits, s);
+            return keys;
+        }
+        if (sort_by_sample(n, bits)) {
+            sample_sort_u64(keys, vals, kalt, valt, n, bits, s);
+            return keys;
+        }
+    }
     const int nblk = (int)((n + kRsTile - 1) / kRsTile);
     const int rs = (nblk + 3) & ~3;  // histogram row stride: 16-byte aligned rows
     int* hist = (int*)pool_alloc(sizeof(int) * 256 * (size_t)rs);
@@ -524,8 +540,7 @@ uint64_t* radix_sort_u64_pp(uint64_t* keys, uint32_t* vals, uint64_t* kalt, uint
         const int shift = begin_bit + 8 * pass;
         k_rs_hist<<<nblk, kRsThreads, 0, s>>>(ka, n, shift, rs, hist);
         SFMM_LAUNCH_CHECK();
-        k_rs_rowscan<<<256, kScanThreads, 0, s>>>(hist, nblk, rs, offs, dtot);
-        SFMM_LAUNCH_CHECK();
+        scan_rows(hist, 256, nblk, rs, offs, dtot, s);
         const bool last = pass == npass - 1;
         k_rs_scatter<<<nblk, kRsThreads, 0, s>>>(ka, va, kb, vb, n, shift, rs, offs, dtot, last ? lo_out : nullptr,
                                                  last ? hi_out : nullptr);
@@ -543,6 +558,10 @@ uint64_t* radix_sort_u64_pp(uint64_t* keys, uint32_t* vals, uint64_t* kalt, uint
 
 void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int bits, hipStream_t s, int begin_bit) {
     if (n <= 1 || bits <= begin_bit) return;
+    if (vals && begin_bit == 0 && sort_in_lds(n)) {
+        radix_sort_u64_pp(keys, vals, nullptr, nullptr, n, bits, s, 0, nullptr);
+        return;
+    }
     uint64_t* k2 = (uint64_t*)pool_alloc(sizeof(uint64_t) * n);
     uint32_t* v2 = vals ? (uint32_t*)pool_alloc(sizeof(uint32_t) * n) : nullptr;
     uint32_t* vr = nullptr;
