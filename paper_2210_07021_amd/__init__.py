@@ -487,8 +487,8 @@ class _PlanView(Plan):
 
 class Batch:
     """Several independent spheres (shells) planned together; execute() runs
-    all of them, replaying a recorded HIP graph after the first call
-    (sfmm_batch_plan / sfmm_batch_execute)."""
+    all of them, from the second call with the same outputs as a recorded HIP
+    graph (sfmm_batch_plan / sfmm_batch_execute)."""
 
     def __init__(self, srcs, qs, tgts, **options):
         import torch
@@ -518,7 +518,8 @@ class Batch:
 
     def execute(self, psi=None, defl=None):
         """Returns lists of psi (M_i,) and defl (3, M_i) CUDA float64 tensors;
-        pass the same output tensors again to replay the recorded graph."""
+        pass the same output tensors again to record the work in a graph and
+        replay it."""
         t = self._torch
         if psi is None:
             psi = [t.empty(m, dtype=t.float64, device="cuda") for m in self.M]

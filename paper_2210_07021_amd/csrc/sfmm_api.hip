@@ -761,7 +761,7 @@ struct sfmm_batch_impl {
     hipStream_t own = nullptr;  // used when the caller passes the null stream
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    std::vector<double*> g_psi, g_defl;  // outputs the graph was recorded with
+    std::vector<double*> g_psi, g_defl;  // outputs of the last direct pass, and of the graph if there is one
     hipStream_t g_stream = nullptr;
     bool capturable = true;
     hipEvent_t done = nullptr;  // end of the last sfmm_batch_execute
@@ -1879,17 +1879,38 @@ sfmm_status sfmm_batch_execute(sfmm_batch_t batch, double* const* psi, double* c
                 SFMM_HIP(hipStreamWaitEvent(s, B.join[w], 0));
             }
         };
-        bool same = B.exec && B.g_stream == s;
+        bool same = B.g_stream == s && B.g_psi.size() == n;
         for (size_t i = 0; same && i < n; ++i) same = B.g_psi[i] == psi[i] && B.g_defl[i] == defl[i];
-        if (same) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (caller) SFMM_HIP(hipStreamIsCapturing(s, &cap));
+        if (same && B.exec) {
             SFMM_HIP(hipGraphLaunch(B.exec, s));
         } else if (!B.capturable) {
             run_all();
-        } else {
+        } else if (cap != hipStreamCaptureStatusNone) {
+            if (!same) throw Error(ST_INVALID_ARG, "the first call of a batch with these outputs cannot be captured");
+            g_capturing = true;  // the caller's graph takes the pass itself
+            try {
+                run_par();
+            } catch (...) {
+                g_capturing = false;
+                throw;
+            }
+            g_capturing = false;
+        } else if (!same) {
+            // the first call with these outputs: a direct pass (it sizes every
+            // buffer that a recorded one needs).  Recording the pass as well and
+            // launching what was recorded, as this call did, made 15.9 ms
+            // of 10.1 (plans included) for eight shells of 1e5 .. 1e6 points,
+            // which a batch executed once never uses.
             B.drop_graph();
-            // one direct pass (sizes every buffer a pass needs), then the same
-            // pass recorded in a graph, which this call also launches
             run_par();
+            B.g_psi.assign(psi, psi + n);
+            B.g_defl.assign(defl, defl + n);
+            B.g_stream = s;
+        } else {
+            // the second: the same pass recorded in a graph, which is launched
+            // now and by every later call
             SFMM_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
             g_capturing = true;
             try {
@@ -1904,9 +1925,6 @@ sfmm_status sfmm_batch_execute(sfmm_batch_t batch, double* const* psi, double* c
             g_capturing = false;
             SFMM_HIP(hipStreamEndCapture(s, &B.graph));
             SFMM_HIP(hipGraphInstantiate(&B.exec, B.graph, nullptr, nullptr, 0));
-            B.g_psi.assign(psi, psi + n);
-            B.g_defl.assign(defl, defl + n);
-            B.g_stream = s;
             SFMM_HIP(hipGraphLaunch(B.exec, s));
         }
         if (!B.done) SFMM_HIP(hipEventCreateWithFlags(&B.done, hipEventDisableTiming));
