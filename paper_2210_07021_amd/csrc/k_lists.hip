@@ -152,18 +152,21 @@ __device__ __forceinline__ uint8_t group_action(const GroupCtx& w, const WalkRec
     return split_side(s.child0 < 0, t.child0 < 0, s.r, s.rlo, t.r, t.rlo);
 }
 
-// the double-double decision of a near-tie of the MAC
-__device__ __noinline__ uint8_t group_action_tie(const GroupCtx& w, int S, int T) {
-    const WalkRec s = w.rec[S], t = w.rec[T];
-    const double* a = w.gdd + 8 * (size_t)S;
-    const double* b = w.gdd + 8 * (size_t)T;
+// the double-double decision of a near-tie of the MAC (the context's pointers
+// by value: a reference put the whole context into every lane's scratch memory
+// at the kernel's start: a level kernel of 1e6 sources took 13 us instead of 9)
+__device__ __noinline__ uint8_t group_action_tie(const WalkRec* rec, const double* gdd, const double* dtrig, double c_t,
+                                                 int S, int T) {
+    const WalkRec s = rec[S], t = rec[T];
+    const double* a = gdd + 8 * (size_t)S;
+    const double* b = gdd + 8 * (size_t)T;
     const dd csd[3] = {{a[0], a[1]}, {a[2], a[3]}, {a[4], a[5]}};
     const dd ctd[3] = {{b[0], b[1]}, {b[2], b[3]}, {b[4], b[5]}};
-    const double* ta = w.dtrig + kWalkDtrig * (size_t)S;
-    const double* tb = w.dtrig + kWalkDtrig * (size_t)T;
+    const double* ta = dtrig + kWalkDtrig * (size_t)S;
+    const double* tb = dtrig + kWalkDtrig * (size_t)T;
     const dd ts[2] = {{ta[0], ta[1]}, {ta[2], ta[3]}};
     const dd tt[4] = {{tb[4], tb[5]}, {tb[6], tb[7]}, {tb[8], tb[9]}, {tb[10], tb[11]}};
-    if (mac_far_dd_trig(csd, ctd, dd{ta[12], ta[13]}, dd{b[6], b[7]}, ts, tt, 1.0, w.c_t)) return A_M2L;
+    if (mac_far_dd_trig(csd, ctd, dd{ta[12], ta[13]}, dd{b[6], b[7]}, ts, tt, 1.0, c_t)) return A_M2L;
     return split_side(s.child0 < 0, t.child0 < 0, s.r, s.rlo, t.r, t.rlo);
 }
 
@@ -217,7 +220,7 @@ __device__ __forceinline__ void group_walk(const GroupCtx& w, int G, int only, c
         }
         if (SINGLE) want = want && tid == only;
         if (want) {
-            GroupTarget t;
+            GroupTarget& t = tgt[tid];
             t.x = r.x;
             t.y = r.y;
             t.z = r.z;
@@ -225,7 +228,6 @@ __device__ __forceinline__ void group_walk(const GroupCtx& w, int G, int only, c
             t.rlo = r.rlo;
             t.trig = w.ttrig[T0 + tid];
             t.child0 = ch;
-            tgt[tid] = t;
         }
         if (MODE == G_LEVEL && want) {
             // the box with itself splits: its own children come down first
@@ -295,7 +297,7 @@ __device__ __forceinline__ void group_walk(const GroupCtx& w, int G, int only, c
                 act = sch < 0 ? A_P2P : A_NONE;
             } else {
                 act = group_action(w, r, tgt[q]);
-                if (TIE && act == A_TIE) act = group_action_tie(w, S, T0 + q);
+                if (TIE && act == A_TIE) act = group_action_tie(w.rec, w.gdd, w.dtrig, w.c_t, S, T0 + q);
             }
         }
         if (!TIE && (__ballot(act == A_TIE) || step == kGroupSteps)) {  // uniform (one wave)
