@@ -105,7 +105,8 @@ typedef struct {
                                   by sfmm_plan when order_policy is LEARNED  */
     int32_t near_segment;      /* close leaves per near-field work item: direct
                                   sums (0 = 128); 8..4096                     */
-    int32_t far_segment;       /* the same for the multipole evaluations     */
+    int32_t far_segment;       /* the same for the multipole evaluations (0 =
+                                  16 to 128 by the number of target leaves)  */
     int32_t judge_targets;     /* per-pair order policies: targets of the
                                   judge's direct sum (0 = 32; < 0: no judge);
                                   at most 4096                               */

@@ -412,7 +412,8 @@ struct NearWork {
     WorkItems near, far;
 };
 constexpr int kSegNear = 128;  // close leaves per direct-sum item
-constexpr int kSegFar = 128;   // close leaves per expansion item
+constexpr int kSegFar = 128;   // close leaves per expansion item, at most by default
+int far_segment(int leaves, int64_t m);  // that length for a plan of m targets in so many leaves
 // Work items of the ntl leaves tl: the first nn[T] entries of each list (CSR
 // off) in segments of seg_near, the others in segments of seg_far; pin: host
 // memory for 6 totals (one read-back)

@@ -28,7 +28,7 @@
 // Load balance: a leaf of a sparse region next to a dense clump can have
 // thousands of close leaves (every clump leaf fails the MAC against a big
 // leaf).  Each leaf's two lists are cut into segments of at most kSegNear /
-// kSegFar entries; a workgroup takes one (leaf, segment) item, items are
+// far_segment() entries; a workgroup takes one (leaf, segment) item, items are
 // launched heaviest first, and a leaf cut into several segments writes its
 // per-segment results to a partial buffer that k_near_reduce adds up in
 // segment order (so the result stays bitwise reproducible).
@@ -72,6 +72,34 @@ double m2p_ratio(int p) {
     return 1.0 / x;
 }
 int m2p_min_count(int p) { return (p + 8 + 3) / 4; }  // ceil(p/4 + 2)
+
+// Expansions per item when the caller sets no length.  A lane evaluates its
+// target's expansions one after another, so a launch lasts at least as long
+// as its longest segment: 128 expansions are 100-190 us at p = 20-38, where
+// all items of a small plan together are a few us of work.  Short segments
+// cost partial sums and their addition, which a launch that fills the chip
+// many times over does not get back.  k_m2p + k_near_reduce, us, segments of
+// 128 / 64 / 32 / 16:
+//   5e4 sources, 3,200 leaves, p = 20   118 /  103 /  60 /  40
+//   3e5, 6,900 leaves, p = 20           130 /  73 /  49 /  40
+//   2.5e5, 6,100 leaves, p = 38         193 / 105 /  68 /  62   (with the Hessian)
+//   1e6, 27,000 leaves, p = 38          240 / 192 / 207 / 218
+//   1e7, 174,000 leaves, p = 38        1069 / 1156 / 1232 / 1345
+// Many targets to a leaf fill the chip with groups of 64 instead
+// (target_groups), and their partial slots would grow with them: long
+// segments from 64 targets a leaf up.
+int far_segment(int leaves, int64_t m) {
+    if (m > 64 * (int64_t)leaves) return kSegFar;
+    return leaves < 16384 ? 16 : leaves < 65536 ? 64 : kSegFar;
+}
+
+// Workgroups that share an item's groups of 64 targets (the grid's y): as
+// many as the average item has groups.  With the groups one after another a
+// plan of few leaves and many targets ran on few waves: 10,000 sources and 1e6 targets
+// 9.9 -> 0.9 ms of direct sums and 1.65 -> 0.10 of expansions (p = 38)
+static unsigned target_groups(int64_t m, int items) {
+    return (unsigned)std::min<int64_t>(64, m / (64 * (int64_t)items) + 1);
+}
 
 // ------------------------------------------------------------ list split
 // Target box of every direct-act entry: the last box whose list starts at
@@ -724,7 +752,7 @@ __global__ void __launch_bounds__(64) k_m2p(FmmCtx c, const int4* __restrict__ i
     const int T = item.x;
     const int k0 = item.y, K = item.z - item.y;
     const int t0 = tfirst[T], nt = tcount[T];
-    for (int tg = 0; tg < nt; tg += 64) {
+    for (int tg = 64 * blockIdx.y; tg < nt; tg += 64 * gridDim.y) {
         const int ng = min(64, nt - tg);
         const int g0 = t0 + tg;
         const int L = 64 / ng;
@@ -844,7 +872,7 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
     // few items: a workgroup each, groups of 64 targets of one leaf side by side
     const bool few = w.n < kP2PFewItems;
     const int pw = p2p_waves(fp32, few ? 4 : 1);
-    const dim3 g(few ? (unsigned)w.n : nblk(w.n, pw), few ? 2 : 1);
+    const dim3 g(few ? (unsigned)w.n : nblk(w.n, pw), std::max(few ? 2u : 1u, target_groups(m_out, w.n)));
 #define P2P_W(T, H, N, W)                                                                                       \
     k_p2p<T, H, N, W><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
                                                    defl, m_out, part, kLogPoly, hess, nk)
@@ -875,13 +903,14 @@ void fmm_m2p(const FmmCtx& c, const WorkItems& w, const int* src, const int* tfi
     if (w.n <= 0 || c.p < kM2PMinOrder) return;
     if (hess && !part && w.nred > 0) throw Error(ST_INTERNAL, "the Hessian needs partial slots of 8 doubles");
     if (!part) part = w.part;
+    const dim3 g((unsigned)w.n, target_groups(m_out, w.n));
 #define L_(P)                                                                                                 \
     case P:                                                                                                   \
         if (hess)                                                                                             \
-            k_m2p<P, true><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz,  \
+            k_m2p<P, true><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz,  \
                                                         tperm, psi, defl, m_out, part, hess);                 \
         else                                                                                                  \
-            k_m2p<P, false><<<(unsigned)w.n, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, \
+            k_m2p<P, false><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, \
                                                          tperm, psi, defl, m_out, part, nullptr);             \
         break;
     SFMM_DISPATCH(c.p, L_)

@@ -603,7 +603,7 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
                      P.tcount.data(), P.tx.data(),    P.ty.data(),    P.tz.data(),    hfar.data()};
     near_lists(nc, P.opt.precision == SFMM_FP32_MIXED, P.tl.data(), P.ntl_all, n_p2p, P.p2p_off.data(), praw.data(), P.p2p_src.data(), P.nn.data(), s);
     const int segn = P.opt.near_segment > 0 ? P.opt.near_segment : kSegNear;
-    const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : kSegFar;
+    const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : far_segment(P.ntl_all, P.M);
     build_items(P.tl.data(), P.ntl_all, P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.count.data(),
                 P.tcount.data(), segn, segf, P.work, h, s);
     P.ntl = -1;  // counted by the statistics: a read-back the plan itself does not need
