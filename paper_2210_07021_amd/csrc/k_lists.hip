@@ -33,6 +33,44 @@ static unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b > 0 ?
 // scale, radius, the double-double forms for near-ties, and one 64-byte record
 // (WalkRec) per source box, so that a lane's look at a source is one aligned
 // segment.
+// One lane a box is a serial chain of five pixel points, an angle and three
+// sines in double-double, 27 us however few boxes there are.  kBoxLanes lanes
+// share a box up to kBoxTeamMax boxes (three times the instructions, which
+// the idle chip has room for): 27 -> 12 us up to 2,000 boxes, 28 -> 20 at
+// 9,000, 27 -> 22 at 11,000, but 28 -> 32 at 17,000 and 45 -> 70 at 62,000.
+constexpr int kBoxLanes = 8, kBoxTeamMax = 12288;
+
+__device__ __forceinline__ dd shfl_dd(dd v, int lane, int width) {
+    return {__shfl(v.hi, lane, width), __shfl(v.lo, lane, width)};
+}
+
+// box_geometry by the kBoxLanes lanes of one box (r: the lane's place among
+// them): lanes 0 to 3 a vertex each, the others the centre, and the farthest
+// vertex by comparisons in box_geometry's order, so the values are the same.
+__device__ __forceinline__ BoxGeomDD box_geometry_team(int level, uint64_t pix, int r) {
+    BoxGeomDD g;
+    const double fx = r > 3 ? 0.5 : r == 1 || r == 2 ? 1.0 : 0.0, fy = r > 3 ? 0.5 : r >= 2 ? 1.0 : 0.0;
+    dd v[3], far[3], ch = dd_from(0.0), best = dd_from(-1.0);
+    pix_point_dd(level, pix, fx, fy, v);
+    for (int i = 0; i < 3; ++i) {
+        g.c[i] = shfl_dd(v[i], 4, kBoxLanes);
+        const dd e = dd_sub(v[i], g.c[i]);
+        ch = dd_add(ch, dd_mul(e, e));
+    }
+    int at = 0;
+    for (int k = 0; k < 4; ++k) {
+        const dd o = shfl_dd(ch, k, kBoxLanes);
+        if (dd_lt(best, o)) {
+            best = o;
+            at = k;
+        }
+    }
+    for (int i = 0; i < 3; ++i) far[i] = shfl_dd(v[i], at, kBoxLanes);
+    g.r = angdist_dd(g.c, far);
+    return g;
+}
+
+template <int LB>
 __global__ void __launch_bounds__(128) k_box_records(int nb, const int* __restrict__ level,
                                                      const uint64_t* __restrict__ pixel,
                                                      const int* __restrict__ child0, const int* __restrict__ count,
@@ -41,11 +79,31 @@ __global__ void __launch_bounds__(128) k_box_records(int nb, const int* __restri
                                                      double* __restrict__ rad, double* __restrict__ gdd,
                                                      WalkRec* __restrict__ rec, double4* __restrict__ ttrig,
                                                      double* __restrict__ dtrig, double* __restrict__ hfar) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int b = i / LB, r8 = i % LB;
+    if (b >= nb) return;  // uniform across a box's lanes
     const int L = level[b];
-    const BoxGeomDD g = box_geometry(L, pixel[b]);
+    BoxGeomDD g;
+    if constexpr (LB == 1) g = box_geometry(L, pixel[b]);
+    else g = box_geometry_team(L, pixel[b], r8);
     const double r = g.r.hi;
+    const bool widen = sigma > 0.0 && r + sigma > c_s * r;
+    const dd prot = widen ? dd_add(g.r, dd_from(sigma)) : dd_mul_d(g.r, c_s);
+    const dd ang[3] = {prot, g.r, dd_div(g.r, dd_from(c_t))};
+    double* t = dtrig + kWalkDtrig * (size_t)b;
+    if constexpr (LB > 1) {
+        // lanes 0 to 2 an angle each, the last lane what is left
+        if (r8 < 3) {
+            const dd x = r8 == 0 ? ang[0] : r8 == 1 ? ang[1] : ang[2];
+            dd sn, cs;
+            dd_sincos(x, &sn, &cs);
+            t[4 * r8 + 0] = cs.hi;
+            t[4 * r8 + 1] = cs.lo;
+            t[4 * r8 + 2] = sn.hi;
+            t[4 * r8 + 3] = sn.lo;
+        }
+        if (r8 != LB - 1) return;
+    }
     cen[4 * (size_t)b + 0] = g.c[0].hi;
     cen[4 * (size_t)b + 1] = g.c[1].hi;
     cen[4 * (size_t)b + 2] = g.c[2].hi;
@@ -76,19 +134,17 @@ __global__ void __launch_bounds__(128) k_box_records(int nb, const int* __restri
     // (4: never): ratio R, and beyond every particle's profile
     const double a = fmax(ratio * r, r + sigma);
     hfar[b] = w.count >= min_count && a < 3.0 ? 2.0 * sin(0.5 * a) : 4.0;
-    const bool widen = sigma > 0.0 && r + sigma > c_s * r;
-    const dd prot = widen ? dd_add(g.r, dd_from(sigma)) : dd_mul_d(g.r, c_s);
-    const dd ang[3] = {prot, g.r, dd_div(g.r, dd_from(c_t))};
-    double* t = dtrig + kWalkDtrig * (size_t)b;
     t[12] = prot.hi;
     t[13] = prot.lo;
-    for (int k = 0; k < 3; ++k) {
-        dd sn, cs;
-        dd_sincos(ang[k], &sn, &cs);
-        t[4 * k + 0] = cs.hi;
-        t[4 * k + 1] = cs.lo;
-        t[4 * k + 2] = sn.hi;
-        t[4 * k + 3] = sn.lo;
+    if constexpr (LB == 1) {
+        for (int k = 0; k < 3; ++k) {
+            dd sn, cs;
+            dd_sincos(ang[k], &sn, &cs);
+            t[4 * k + 0] = cs.hi;
+            t[4 * k + 1] = cs.lo;
+            t[4 * k + 2] = sn.hi;
+            t[4 * k + 3] = sn.lo;
+        }
     }
 }
 
@@ -96,8 +152,12 @@ void box_records(int nb, const int* level, const uint64_t* pixel, const int* chi
                  double c_s, double c_t, double sigma, double ratio, int min_count, double* cen, double* rad,
                  double* gdd, WalkRec* rec, double4* ttrig, double* dtrig, double* hfar, hipStream_t s) {
     if (nb <= 0) return;
-    k_box_records<<<nblk(nb, 128), 128, 0, s>>>(nb, level, pixel, child0, count, c_s, c_t, sigma, ratio, min_count,
-                                                cen, rad, gdd, rec, ttrig, dtrig, hfar);
+    if (nb <= kBoxTeamMax)
+        k_box_records<kBoxLanes><<<nblk((int64_t)kBoxLanes * nb, 128), 128, 0, s>>>(
+            nb, level, pixel, child0, count, c_s, c_t, sigma, ratio, min_count, cen, rad, gdd, rec, ttrig, dtrig, hfar);
+    else
+        k_box_records<1><<<nblk(nb, 128), 128, 0, s>>>(nb, level, pixel, child0, count, c_s, c_t, sigma, ratio,
+                                                       min_count, cen, rad, gdd, rec, ttrig, dtrig, hfar);
     SFMM_LAUNCH_CHECK();
 }
 
