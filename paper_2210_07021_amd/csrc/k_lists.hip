@@ -619,10 +619,12 @@ __device__ __forceinline__ double lane_f64(double v, int j) {
 // S (live lanes) goes through its expansion at every target of T: all of them
 // farther (as chords) than hfar[S] from its centre.  Every target lies within
 // R_T of T's centre, so a centre distance beyond hfar + R_T settles it, and
-// one below hfar - R_T settles the opposite; for the lanes in between the wave
-// goes over the targets together, 64 of them in its registers at a time (a
-// lane's own loop over them in memory took up to 20 us a step; the short lists
-// of clustered-1e7 222 -> 175 us, the longest ones 138 -> below 40).
+// one below hfar - R_T settles the opposite.  Of the entries in between and the
+// targets, the fewer are taken one after another and the others by the lanes:
+// few targets each against all entries, or an entry against 64 targets a step
+// until one is too close.  (Targets one after another at any number of them:
+// 2,001 sources at 1.5e6 targets 2,364 us instead of 180; entries at any
+// number: the longest lists of clustered-1e7 106 -> 125 us.)
 __device__ __forceinline__ bool act_far(const NearCtx& c, bool live, int S, const WalkRec& t, int t0, int nt) {
     const double h = live ? c.hfar[S] : 4.0;
     bool far = false, open = false;
@@ -636,15 +638,34 @@ __device__ __forceinline__ bool act_far(const NearCtx& c, bool live, int S, cons
         open = !far && !(lo > 0.0 && d2 < lo * lo * (1.0 - 1e-12));
     }
     const double thr = h * h;
-    for (int b = 0; b < nt && __ballot(open); b += 64) {  // uniform across the wave
-        const int m = min(64, nt - b), i = t0 + b + min((int)(threadIdx.x & 63), m - 1);
-        const double x = c.tx[i], y = c.ty[i], z = c.tz[i];
-        for (int k = 0; k < m; ++k) {
-            const double dx = lane_f64(x, k) - s.x, dy = lane_f64(y, k) - s.y, dz = lane_f64(z, k) - s.z;
+    uint64_t left = __ballot(open);
+    if (left == 0) return far;
+    const int lane = threadIdx.x & 63;
+    double nx = 0.0, ny = 0.0, nz = 0.0;
+    auto load = [&](int b) {
+        const int i = t0 + min(b + lane, nt - 1);
+        nx = c.tx[i];
+        ny = c.ty[i];
+        nz = c.tz[i];
+    };
+    if (nt > 0) load(0);
+    if (nt < __popcll(left)) {  // below 64
+        for (int k = 0; k < nt; ++k) {
+            const double dx = lane_f64(nx, k) - s.x, dy = lane_f64(ny, k) - s.y, dz = lane_f64(nz, k) - s.z;
             open = open && dx * dx + dy * dy + dz * dz > thr;
         }
+        return far || open;
     }
-    return far || open;
+    for (int b = 0; b < nt && left; b += 64) {  // uniform across the wave
+        const double x = nx, y = ny, z = nz;
+        if (b + 64 < nt) load(b + 64);
+        for (uint64_t w = left; w; w &= w - 1) {
+            const int j = __builtin_ctzll(w);
+            const double dx = x - lane_f64(s.x, j), dy = y - lane_f64(s.y, j), dz = z - lane_f64(s.z, j);
+            if (__ballot(!(dx * dx + dy * dy + dz * dz > lane_f64(thr, j)))) left &= ~(1ull << j);
+        }
+    }
+    return far || (left >> lane & 1);
 }
 
 // Lists of up to kShortRanked (ordered) or kShortPlain entries: a wave each.
