@@ -471,9 +471,12 @@ int fp64_level(const sfmm_plan_impl& P) {
 }
 
 // Room of a hand-down list.  The lists of clustered-1e7 hold at most ~100
-// sources at the default MACs; a plan with a longer one (looser MACs) makes
-// them once more with exact sizes.
-constexpr int kHandDown = 256;
+// sources at the default MACs, those of a halo of smoothed particles more
+// than 256 (every box within sigma of its target splits on); a plan with a
+// longer one makes them once more with exact sizes and a read-back a level.
+// Plans of few split boxes have room for longer ones (128 MB of it): the halo of
+// 1e5 particles of the shear cases 1.18 -> 1.02 ms a call.
+constexpr int kHandDown = 256, kHandDownMax = 4096, kHandDownRoom = 1 << 25;
 
 // Box records and the lists of the boxes with targets.
 void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
@@ -501,7 +504,8 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     // SFMM_WALK_RATIO also shrinks the hand-down lists: tests use it to drive
     // the fallback
     const char* forced = std::getenv("SFMM_WALK_RATIO");
-    const int cd = forced ? std::max(1, (int)std::atof(forced)) : kHandDown;
+    const int cd = forced ? std::max(1, (int)std::atof(forced))
+                          : std::clamp(kHandDownRoom / std::max(nsplit, 1), kHandDown, kHandDownMax);
     DVec<int> dlist, dcnt, cnt, off, tot;
     DVec<int64_t> doff;
     DVec<int> big;
