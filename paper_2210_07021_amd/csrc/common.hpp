@@ -388,7 +388,7 @@ void fmm_l2l(const FmmCtx& c, int c0, int c1, hipStream_t s);
 // (kappa - kappa_bar, gamma_1, gamma_2, mu) [4][m] from the Hessian [3][m]
 void lensing_from_hessian(const double* hess, int64_t m, double* out, hipStream_t s);
 // hess [3][m_out] (may be null): also the Hessian of Sec. 2.2 in the
-// targets' e_theta, e_phi basis (written, like psi and defl)
+// targets' e_theta, e_phi basis (added, like psi and defl)
 void fmm_l2p(const FmmCtx& c, const double* tx, const double* ty, const double* tz, const int* tleaf,
              const uint32_t* tperm, int64_t m, double psi_shift, double* psi, double* defl, int64_t m_out,
              hipStream_t s, double* hess = nullptr);

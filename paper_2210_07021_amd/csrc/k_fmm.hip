@@ -444,7 +444,7 @@ void fmm_m2l_f64_classes(const FmmCtx& c, const int* order, int n, const int* bo
     SFMM_LAUNCH_CHECK();
 }
 
-// Local expansion at each target (sorted by leaf); writes psi and alpha in
+// Local expansion at each target (sorted by leaf), added to psi and alpha in
 // the caller's target order
 template <int P>
 __global__ void __launch_bounds__(128) k_l2p(FmmCtx c, const double* tx, const double* ty, const double* tz,
@@ -458,13 +458,13 @@ __global__ void __launch_bounds__(128) k_l2p(FmmCtx c, const double* tx, const d
     double p, ax, ay, az;
     l2p_eval<P>(c.local + (size_t)L * (2 * P + 2), f, rho, tx[i], ty[i], tz[i], &p, &ax, &ay, &az);
     const int64_t o = tperm[i];
-    psi[o] = p + psi_shift;
-    defl[o] = ax;
-    defl[m_out + o] = ay;
-    defl[2 * m_out + o] = az;
+    psi[o] += p + psi_shift;
+    defl[o] += ax;
+    defl[m_out + o] += ay;
+    defl[2 * m_out + o] += az;
 }
 
-// k_l2p that also writes the local expansion's Hessian (Sec. 2.2) to hess
+// k_l2p that also adds the local expansion's Hessian (Sec. 2.2) to hess
 // [3][m_out] (H_tt, H_tp, H_pp in the target's e_theta, e_phi)
 template <int P>
 __global__ void __launch_bounds__(128) k_l2p_hess(FmmCtx c, const double* tx, const double* ty, const double* tz,
@@ -482,13 +482,13 @@ __global__ void __launch_bounds__(128) k_l2p_hess(FmmCtx c, const double* tx, co
     double p, ax, ay, az, h[3];
     l2p_eval_hess<P>(c.local + (size_t)L * (2 * P + 2), f, rho, nx, ny, nz, et, ep, &p, &ax, &ay, &az, h);
     const int64_t o = tperm[i];
-    psi[o] = p + psi_shift;
-    defl[o] = ax;
-    defl[m_out + o] = ay;
-    defl[2 * m_out + o] = az;
-    hess[o] = h[0];
-    hess[m_out + o] = h[1];
-    hess[2 * m_out + o] = h[2];
+    psi[o] += p + psi_shift;
+    defl[o] += ax;
+    defl[m_out + o] += ay;
+    defl[2 * m_out + o] += az;
+    hess[o] += h[0];
+    hess[m_out + o] += h[1];
+    hess[2 * m_out + o] += h[2];
 }
 
 void fmm_p2m(const FmmCtx& c, int nb, hipStream_t s) {

@@ -248,6 +248,7 @@ __device__ __forceinline__ Frame box_frame(const double* cen, int b, double* rho
 // four) gather their children.  An empty child has a zero record.
 template <int P>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_m2m(FmmCtx c, int c0, int c1) {
+    __builtin_amdgcn_s_setprio(3);  // before the direct sums' waves that run beside it
     constexpr int NT = P / 4 + 1;
     const int lane = threadIdx.x, kq = lane >> 4;
     const int base = c0 + 16 * blockIdx.x, ch = min(base + (lane & 15), c1 - 1);
@@ -275,6 +276,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_
 // expansions (boxes without targets below: left out)
 template <int P>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_l2l(FmmCtx c, int c0, int c1) {
+    __builtin_amdgcn_s_setprio(3);  // before the direct sums' waves that run beside it
     constexpr int NT = P / 4 + 1;
     const int lane = threadIdx.x, kq = lane >> 4;
     const int base = c0 + 16 * blockIdx.x, ch = min(base + (lane & 15), c1 - 1);

@@ -881,6 +881,82 @@ void m2l_stage(sfmm_plan_impl& P, const FmmCtx& c, const FarView& v, float* mult
     }
 }
 
+// Second streams for the judge's direct sum during planning: created on
+// first use per device (non-blocking, default priority) and kept for the
+// life of the process; a plan takes one and gives it back when it ends.
+struct SideStream {
+    int dev = -1;
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+};
+std::mutex g_side_mu;
+std::vector<SideStream*> g_side_free;
+
+SideStream* side_acquire() {
+    int dev = 0;
+    SFMM_HIP(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> lk(g_side_mu);
+        for (size_t k = 0; k < g_side_free.size(); ++k)
+            if (g_side_free[k]->dev == dev) {
+                SideStream* w = g_side_free[k];
+                g_side_free.erase(g_side_free.begin() + k);
+                return w;
+            }
+    }
+    std::unique_ptr<SideStream> w(new SideStream());
+    w->dev = dev;
+    SFMM_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
+    SFMM_HIP(hipEventCreateWithFlags(&w->fork, hipEventDisableTiming));
+    SFMM_HIP(hipEventCreateWithFlags(&w->join, hipEventDisableTiming));
+    return w.release();
+}
+
+// Work forked from a stream to a second one.  end() makes the first wait for
+// it; after that the second can be lent again, as its next user queues behind.
+// The destructor before end() (an error in between) waits for the second
+// stream before the plan's buffers can go.
+struct Beside {
+    SideStream* w = nullptr;
+    bool joined = false;
+    hipStream_t fork(hipStream_t s) {
+        w = side_acquire();
+        SFMM_HIP(hipEventRecord(w->fork, s));
+        SFMM_HIP(hipStreamWaitEvent(w->stream, w->fork, 0));
+        return w->stream;
+    }
+    void end(hipStream_t s) {
+        if (!w || joined) return;
+        SFMM_HIP(hipEventRecord(w->join, w->stream));
+        SFMM_HIP(hipStreamWaitEvent(s, w->join, 0));
+        joined = true;
+    }
+    ~Beside() {
+        if (!w) return;
+        if (!joined) (void)hipStreamSynchronize(w->stream);
+        std::lock_guard<std::mutex> lk(g_side_mu);
+        g_side_free.push_back(w);
+    }
+};
+
+// The direct acts run on a second stream beside Lemmas 2 to 4: those go level by
+// level and each level's few workgroups leave most of the chip idle, which the
+// direct sums' thousands fill (the level kernels' waves go first where they
+// share a SIMD).  One stream takes all of it, in the same order of additions,
+// where it is being captured, where a batch runs its shells side by side
+// and where stages are timed.  Calls, us, one stream -> two: 3e5 sources (17
+// levels) 1058 -> 967, 1e6 2269 -> 2114, its shear 1837 -> 1699, four traced
+// planes 4791 -> 4366, 1e7 8817 -> 8669; 1e4 sources (4 levels) 641 -> 641 and
+// 1e3 (2 levels) 452 -> 512: the fork and the join cost more than that.
+constexpr int kBesideLevels = 5;
+thread_local bool g_alone = false;  // a batch's shells on its own streams
+bool near_beside(int nlev, hipStream_t s) {
+    if (nlev < kBesideLevels || g_capturing || g_alone) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s) SFMM_HIP(hipStreamIsCapturing(s, &cap));  // the null stream never is
+    return cap == hipStreamCaptureStatusNone;
+}
+
 // The five stages of Sec. 3.7 on a plan; xs = null: the plan's own buffers.
 // fixed: every FMM act at the plan order whatever the order policy.
 // hess [3][M] (may be null): also the Hessian of Sec. 2.2.
@@ -906,6 +982,31 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
         StageScope st(prof, S_P2M);
         fmm_p2m(c, P.nbox, s);
     }
+    // the Hessian's partial slots hold 8 doubles instead of 4
+    double* far_part = xs ? xs->far_part : nullptr;
+    double* near_part = xs ? xs->near_part : nullptr;
+    if (hess) {
+        P.hess_part.resize(8 * ((size_t)std::max(P.work.far.nslot, 1) + (size_t)std::max(P.work.near.nslot, 1)));
+        far_part = P.hess_part.data();
+        near_part = P.hess_part.data() + 8 * (size_t)std::max(P.work.far.nslot, 1);
+    }
+    // the direct acts need no more than Lemma 1
+    auto near_field = [&](hipStream_t ns) {
+        fill_f64(psi, P.M, 0.0, ns);
+        fill_f64(defl, 3 * P.M, 0.0, ns);
+        if (hess) fill_f64(hess, 3 * P.M, 0.0, ns);
+        {
+            StageScope st(prof, S_M2P);
+            fmm_m2p(c, P.work.far, P.p2p_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(), P.ty.data(),
+                    P.tz.data(), P.tperm.data(), psi, defl, P.M, ns, far_part, hess);
+        }
+        StageScope st(prof, S_P2P);
+        fmm_p2p(c, P.opt.precision == SFMM_FP32_MIXED, P.work.near, P.p2p_src.data(), P.tfirst.data(),
+                P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, ns, near_part,
+                hess);
+    };
+    Beside ov;
+    near_field(!xs && !prof.on && near_beside(nlev, s) ? ov.fork(s) : s);
     {
         StageScope st(prof, S_M2M);
         for (int L = nlev - 2; L >= 0; --L)
@@ -925,30 +1026,12 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
         StageScope st(prof, S_L2L);
         for (int L = 1; L < nlev; ++L) fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1], s);
     }
-    // far field at the targets, then the direct acts
+    // far field at the targets, added to the near one
+    ov.end(s);
     {
         StageScope st(prof, S_L2P);
         fmm_l2p(c, P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), P.tperm.data(), P.M, shift, psi,
                 defl, P.M, s, hess);
-    }
-    // the Hessian's partial slots hold 8 doubles instead of 4
-    double* far_part = xs ? xs->far_part : nullptr;
-    double* near_part = xs ? xs->near_part : nullptr;
-    if (hess) {
-        P.hess_part.resize(8 * ((size_t)std::max(P.work.far.nslot, 1) + (size_t)std::max(P.work.near.nslot, 1)));
-        far_part = P.hess_part.data();
-        near_part = P.hess_part.data() + 8 * (size_t)std::max(P.work.far.nslot, 1);
-    }
-    {
-        StageScope st(prof, S_M2P);
-        fmm_m2p(c, P.work.far, P.p2p_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(),
-                P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, s, far_part, hess);
-    }
-    {
-        StageScope st(prof, S_P2P);
-        fmm_p2p(c, P.opt.precision == SFMM_FP32_MIXED, P.work.near, P.p2p_src.data(), P.tfirst.data(),
-                P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, s,
-                near_part, hess);
     }
     prof.flush();
 }
@@ -989,57 +1072,10 @@ std::vector<int> judge_positions(int64_t N, int64_t M, int S) {
     return pos;
 }
 
-// Second streams for the judge's direct sum during planning: created on
-// first use per device (non-blocking, default priority) and kept for the
-// life of the process; a plan takes one and gives it back when it ends.
-struct SideStream {
-    int dev = -1;
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-};
-std::mutex g_side_mu;
-std::vector<SideStream*> g_side_free;
-
-SideStream* side_acquire() {
-    int dev = 0;
-    SFMM_HIP(hipGetDevice(&dev));
-    {
-        std::lock_guard<std::mutex> lk(g_side_mu);
-        for (size_t k = 0; k < g_side_free.size(); ++k)
-            if (g_side_free[k]->dev == dev) {
-                SideStream* w = g_side_free[k];
-                g_side_free.erase(g_side_free.begin() + k);
-                return w;
-            }
-    }
-    std::unique_ptr<SideStream> w(new SideStream());
-    w->dev = dev;
-    SFMM_HIP(hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking));
-    SFMM_HIP(hipEventCreateWithFlags(&w->fork, hipEventDisableTiming));
-    SFMM_HIP(hipEventCreateWithFlags(&w->join, hipEventDisableTiming));
-    return w.release();
-}
-
-// Holds a plan's second stream: end() makes the plan's stream wait for the
-// judge's sum; the destructor (also on an error inside the plan) waits for
-// the second stream before the plan's buffers can go, and returns it.
-struct JudgeOverlap {
-    SideStream* w = nullptr;
-    void end(hipStream_t s) {
-        if (w) SFMM_HIP(hipStreamWaitEvent(s, w->join, 0));
-    }
-    ~JudgeOverlap() {
-        if (!w) return;
-        (void)hipStreamSynchronize(w->stream);
-        std::lock_guard<std::mutex> lk(g_side_mu);
-        g_side_free.push_back(w);
-    }
-};
-
 // Plan-time half of the judge (per-pair order policies): its targets, and
 // their direct sum over the sorted sources on a second stream beside the
 // rest of the plan.
-void judge_start(sfmm_plan_impl& P, const double* tgt, JudgeOverlap& ov, hipStream_t s) {
+void judge_start(sfmm_plan_impl& P, const double* tgt, Beside& ov, hipStream_t s) {
     const int S = (int)std::min<int64_t>(P.M, P.opt.judge_targets > 0 ? P.opt.judge_targets : kJudgeDefault);
     P.judge_S = S;
     if (S <= 0) return;
@@ -1049,11 +1085,7 @@ void judge_start(sfmm_plan_impl& P, const double* tgt, JudgeOverlap& ov, hipStre
     P.judge_part.resize(judge_part_doubles(P.N, S));
     SFMM_HIP(hipMemcpyAsync(P.judge_pos.data(), pos.data(), sizeof(int) * S, hipMemcpyHostToDevice, s));
     judge_targets(P.judge_pos.data(), S, tgt, P.M, P.judge_tsel.data(), s);
-    ov.w = side_acquire();
-    SFMM_HIP(hipEventRecord(ov.w->fork, s));
-    SFMM_HIP(hipStreamWaitEvent(ov.w->stream, ov.w->fork, 0));
-    judge_sum(P.spt.data(), P.N, P.judge_tsel.data(), S, P.judge_part.data(), ov.w->stream);
-    SFMM_HIP(hipEventRecord(ov.w->join, ov.w->stream));
+    judge_sum(P.spt.data(), P.N, P.judge_tsel.data(), S, P.judge_part.data(), ov.fork(s));
     P.judge_ready = true;
 }
 
@@ -1151,7 +1183,7 @@ sfmm_status sfmm_plan(const double* src, const double* q, int64_t N, const doubl
         hipStream_t s = (hipStream_t)stream;
         PoolStream ps(s);
         std::unique_ptr<sfmm_plan_impl> P(new sfmm_plan_impl());
-        JudgeOverlap ov;  // after P: on any exit it waits for the judge's stream before P goes
+        Beside ov;  // after P: on any exit it waits for the judge's stream before P goes
         P->pin.reset(new Pinned());
         P->opt = o;
         P->p = o.order > 0 ? o.order : order_for_tolerance(o.tolerance);
@@ -1873,6 +1905,10 @@ sfmm_status sfmm_batch_execute(sfmm_batch_t batch, double* const* psi, double* c
         auto run_par = [&]() {
             if (B.ws.empty()) return run_all();
             SFMM_HIP(hipEventRecord(B.fork, s));
+            struct Alone {
+                Alone() { g_alone = true; }
+                ~Alone() { g_alone = false; }
+            } alone;
             for (size_t w = 0; w < B.ws.size(); ++w) {
                 SFMM_HIP(hipStreamWaitEvent(B.ws[w], B.fork, 0));
                 for (int i : B.groups[w]) {
