@@ -416,9 +416,11 @@ constexpr int kSegFar = 128;   // close leaves per expansion item, at most by de
 int far_segment(int leaves, int64_t m);  // that length for a plan of m targets in so many leaves
 // Work items of the ntl leaves tl: the first nn[T] entries of each list (CSR
 // off) in segments of seg_near, the others in segments of seg_far; pin: host
-// memory for 6 totals (one read-back)
+// memory for 6 totals (one read-back); more than slots_room partial slots: the
+// others in segments of kSegFar after all
 void build_items(const int* tl, int ntl, const int* off, const int* nn, const int* src, const int* count,
-                 const int* tcount, int seg_near, int seg_far, NearWork& out, int* pin, hipStream_t s);
+                 const int* tcount, int seg_near, int seg_far, int64_t slots_room, NearWork& out, int* pin,
+                 hipStream_t s);
 // per box: pairs[b] = targets x particles of the near leaves, evals[b] =
 // targets x far leaves
 void near_work(const int* count, const int* off, const int* nn, const int* src, const int* tcount, int nbox,

@@ -223,17 +223,25 @@ __global__ void k_gather_items(const int4* __restrict__ in, const uint32_t* __re
 }
 
 void build_items(const int* tl, int ntl, const int* off, const int* nn, const int* src, const int* count,
-                 const int* tcount, int seg_near, int seg_far, NearWork& out, int* pin, hipStream_t s) {
+                 const int* tcount, int seg_near, int seg_far, int64_t slots_room, NearWork& out, int* pin,
+                 hipStream_t s) {
     out.near = WorkItems();
     out.far = WorkItems();
     if (ntl <= 0) return;
     DVec<int> cnt, pos;
     cnt.resize(6 * (size_t)ntl);
     pos.resize(6 * (size_t)ntl);
-    k_item_count<<<nblk(ntl, 256), 256, 0, s>>>(tl, ntl, off, nn, tcount, seg_near, seg_far, cnt.data());
-    SFMM_LAUNCH_CHECK();
-    scan_excl_i32_n(cnt.data(), pos.data(), 6, ntl, pin, s);
-    SFMM_HIP(hipStreamSynchronize(s));
+    auto tally = [&]() {
+        k_item_count<<<nblk(ntl, 256), 256, 0, s>>>(tl, ntl, off, nn, tcount, seg_near, seg_far, cnt.data());
+        SFMM_LAUNCH_CHECK();
+        scan_excl_i32_n(cnt.data(), pos.data(), 6, ntl, pin, s);
+        SFMM_HIP(hipStreamSynchronize(s));
+    };
+    tally();
+    if (seg_far < kSegFar && (pin[4] < 0 || pin[1] + (int64_t)pin[4] > slots_room)) {
+        seg_far = kSegFar;
+        tally();
+    }
     const int n_near = pin[0], n = pin[0] + pin[3], red_near = pin[2];
     out.items.resize(std::max(n, 1));
     out.red.resize(std::max(pin[2] + pin[5], 1));

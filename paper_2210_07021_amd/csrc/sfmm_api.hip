@@ -470,6 +470,9 @@ int fp64_level(const sfmm_plan_impl& P) {
     return v ? (int)std::max(-1L, std::min(29L, std::strtol(v, nullptr, 10))) : kFp32CoarseLevel;
 }
 
+// Scratch of an execute that does not allocate, a GPU
+constexpr size_t kNoallocScratchBytes = (size_t)256 << 20;
+
 // Room of a hand-down list.  The lists of clustered-1e7 hold at most ~100
 // sources at the default MACs, those of a halo of smoothed particles more
 // than 256 (every box within sigma of its target splits on); a plan with a
@@ -608,8 +611,13 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     near_lists(nc, P.opt.precision == SFMM_FP32_MIXED, P.tl.data(), P.ntl_all, n_p2p, P.p2p_off.data(), praw.data(), P.p2p_src.data(), P.nn.data(), s);
     const int segn = P.opt.near_segment > 0 ? P.opt.near_segment : kSegNear;
     const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : far_segment(P.ntl_all, P.M);
+    // short segments of our own choice stay within 64 MB of partial slots and
+    // within the scratch of the no-allocation execute (its alignment: 1 KB)
+    const int64_t multf = P.tier() ? 8 * (int64_t)P.p * nb : 0;
+    const int64_t room = P.opt.far_segment > 0 ? INT64_MAX
+                                               : std::min((int64_t)2 << 20, ((int64_t)kNoallocScratchBytes - 1024 - multf) / 32);
     build_items(P.tl.data(), P.ntl_all, P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.count.data(),
-                P.tcount.data(), segn, segf, P.work, h, s);
+                P.tcount.data(), segn, segf, room, P.work, h, s);
     P.ntl = -1;  // counted by the statistics: a read-back the plan itself does not need
     // M2L work order: boxes with the most team rounds first, so that the
     // lanes of a wave carry the same work (the precision tier's FP64 levels
@@ -1127,7 +1135,6 @@ void run_judge(sfmm_plan_impl& P, const double* psi, const double* defl, hipStre
 // runs on holds its own copy for the life of the process.  Host code never
 // uses the array's name as an address (on the host it is only a stand-in for
 // the symbol): the device address is looked up once per device and kept.
-constexpr size_t kNoallocScratchBytes = (size_t)256 << 20;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

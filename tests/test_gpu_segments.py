@@ -40,3 +40,31 @@ def test_segment_lengths(n, leaf, m, tier, oracle_lib):
         ref_p, ref_a = oracle.direct(src, q, np.ascontiguousarray(tgt[:, k]))
         assert np.linalg.norm(got[0][0][k] - ref_p) < 1e-10 * np.linalg.norm(ref_p)
         assert np.linalg.norm(got[0][1][:, k] - ref_a) < 1e-10 * np.linalg.norm(ref_a)
+
+
+@pytest.mark.parametrize("tier", [False, True])
+def test_no_allocation_scratch(tier, oracle_lib):
+    """Short segments never take a plan beyond the no-allocation scratch (64 MB
+    of partial slots at most), and that entry gives the same bits."""
+    import ctypes
+    import torch
+    import paper_2210_07021_amd as sf
+    rng = skies.rng_for(172)
+    src = skies.clustered(300000, rng)
+    q = skies.masses_lognormal(300000, rng)
+    tgt = torch.from_numpy(skies.uniform(1000000, rng)).cuda()
+    kw = dict(order=20, leaf_size=30, precision=sf.SFMM_FP32_MIXED if tier else sf.SFMM_FP64)
+    plan = sf.Plan(src, q, tgt, **kw)
+    long = sf.Plan(src, q, tgt, far_segment=128, **kw)
+    short, most = plan.stats()["execute_scratch_bytes"], long.stats()["execute_scratch_bytes"]
+    print(f"[segments] scratch {short} (segments of 128: {most})", flush=True)
+    assert most <= 256 << 20 and short <= 256 << 20 and short <= max(most, 65 << 20) + 8 * 20 * 10**6
+    psi, defl = plan.execute()
+    p2, d2 = torch.empty_like(psi), torch.empty_like(defl)
+    lib = sf.load_library()
+    assert lib.sfmm_execute_noalloc(plan._h, ctypes.c_void_p(p2.data_ptr()), ctypes.c_void_p(d2.data_ptr()),
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(psi, p2) and torch.equal(defl, d2)
+    plan.close()
+    long.close()
