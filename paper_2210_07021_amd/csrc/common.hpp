@@ -137,7 +137,11 @@ constexpr int kMlpWeights = kMlpHidden * kMlpIn + kMlpHidden + kMlpHidden * kMlp
 void fill_f64(double* p, size_t n, double v, hipStream_t s);
 void fill_f32(float* p, size_t n, float v, hipStream_t s);
 void fill_i32(int* p, size_t n, int v, hipStream_t s);
-void fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s);
+struct ZeroRun {
+    void* p;  // 4-byte aligned
+    size_t bytes;
+};
+void zero_runs(ZeroRun a, ZeroRun b, ZeroRun c, hipStream_t s);
 // exclusive scan of n ints; the total goes to *total (device)
 void scan_excl_i32(const int* in, int* out, int64_t n, int* total, hipStream_t s);
 // na scans of n ints in one set of launches: array j at in + j n, its scan at

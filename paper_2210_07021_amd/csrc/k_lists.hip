@@ -827,8 +827,7 @@ void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, 
     queue.resize(2 * ((size_t)ntl + 1));
     int* qmid = queue.data();
     int* qlong = qmid + ntl + 1;
-    fill_i32(qmid, 1, 0, s);
-    fill_i32(qlong, 1, 0, s);
+    zero_runs({qmid, sizeof(int)}, {qlong, sizeof(int)}, {nullptr, 0}, s);
     const unsigned g = nblk(64 * (int64_t)ntl, 256);
     if (ordered) {
         gkeys.resize(np);

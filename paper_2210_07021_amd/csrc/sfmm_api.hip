@@ -542,7 +542,6 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     int* h = P.pin->p;
     // the totals of the lists, once every hand-down list is made
     auto count = [&]() {
-        fill_i32(big.data(), 1, 0, s);
         group_walk_count(w, o, nb, s);
         scan_excl_i32_n(cnt.data(), off.data(), 4, nb, tot.data(), s);
         SFMM_HIP(hipMemcpyAsync(P.m2l_off.data(), off.data(), sizeof(int) * nb, hipMemcpyDeviceToDevice, s));
@@ -551,7 +550,7 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
                       P.m2l_off.data(), P.p2p_off.data(), h, s);
         SFMM_HIP(hipStreamSynchronize(s));
     };
-    fill_i32(tot.data(), 5, 0, s);
+    zero_runs({tot.data(), 5 * sizeof(int)}, {big.data(), sizeof(int)}, {nullptr, 0}, s);
     for (int L = 0; L + 1 < nlev; ++L) group_walk_level(w, o, P.lvl_start[L], P.lvl_start[L + 1], s);
     count();
     if (h[4] > 0) {
@@ -582,7 +581,7 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
             o.dcap = 0x7fffffff;
             group_walk_level(w, o, P.lvl_start[L], P.lvl_start[L + 1], s);
         }
-        fill_i32(tot.data(), 5, 0, s);
+        zero_runs({tot.data(), 5 * sizeof(int)}, {big.data(), sizeof(int)}, {nullptr, 0}, s);
         count();
     }
     P.n_m2l = h[0];
@@ -668,8 +667,7 @@ void build_targets(sfmm_plan_impl& P, const DVec<double4>& u, hipStream_t s) {
     P.tfirst.resize(P.nbox);
     P.tcount.resize(P.nbox);
     P.need.resize(P.nbox);
-    fill_i32(P.tcount.data(), P.nbox, 0, s);
-    fill_u8(P.need.data(), P.nbox, 0, s);
+    zero_runs({P.tcount.data(), sizeof(int) * (size_t)P.nbox}, {P.need.data(), (size_t)P.nbox}, {nullptr, 0}, s);
     if (M == 0) return;
     DVec<uint64_t> leaf, leaf2;
     DVec<uint32_t> perm2;
@@ -975,9 +973,8 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     const double shift = ((P.opt.psi_gauge == SFMM_GAUGE_RAW) ? -P.q_total : 0.0) * 0.079577471545947667884 +
                          P.q_total * 0.079577471545947667884 * npm_constant(P.opt.npm_sigma);
     if (P.N == 0) {
-        fill_f64(psi, P.M, 0.0, s);
-        fill_f64(defl, 3 * P.M, 0.0, s);
-        if (hess) fill_f64(hess, 3 * P.M, 0.0, s);
+        zero_runs({psi, sizeof(double) * (size_t)P.M}, {defl, 3 * sizeof(double) * (size_t)P.M},
+                  {hess, hess ? 3 * sizeof(double) * (size_t)P.M : 0}, s);
         return;
     }
     // every multipole record is written by Lemma 1 (leaves) or Lemma 2
@@ -1000,9 +997,8 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     }
     // the direct acts need no more than Lemma 1
     auto near_field = [&](hipStream_t ns) {
-        fill_f64(psi, P.M, 0.0, ns);
-        fill_f64(defl, 3 * P.M, 0.0, ns);
-        if (hess) fill_f64(hess, 3 * P.M, 0.0, ns);
+        zero_runs({psi, sizeof(double) * (size_t)P.M}, {defl, 3 * sizeof(double) * (size_t)P.M},
+                  {hess, hess ? 3 * sizeof(double) * (size_t)P.M : 0}, ns);
         {
             StageScope st(prof, S_M2P);
             fmm_m2p(c, P.work.far, P.p2p_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(), P.ty.data(),
