@@ -142,7 +142,13 @@ struct ZeroRun {
     size_t bytes;
 };
 void zero_runs(ZeroRun a, ZeroRun b, ZeroRun c, hipStream_t s);
-// exclusive scan of n ints; the total goes to *total (device)
+// a + b of two counts held as 32-bit unsigned numbers; past 2^32 - 1 it stays there
+__host__ __device__ inline int add_sat(int a, int b) {
+    const uint32_t s = (uint32_t)a + (uint32_t)b;
+    return (int)(s < (uint32_t)a ? 0xffffffffu : s);
+}
+// exclusive scan of n ints; the total goes to *total (device).  The scans sum
+// with add_sat: a total of more than 2^31 - 1 reads as an unsigned number above that
 void scan_excl_i32(const int* in, int* out, int64_t n, int* total, hipStream_t s);
 // na scans of n ints in one set of launches: array j at in + j n, its scan at
 // out + j n, its sum in total[j]

@@ -215,14 +215,17 @@ constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
 // block-wide exclusive scan of one value per thread (256 threads = 4 waves):
-// inclusive scan inside each wave by shuffles, then the wave totals
+// inclusive scan inside each wave by shuffles, then the wave totals.  Sums of
+// counts that pass 2^32 - 1 stay there (add_sat), so that a total is never
+// taken for a smaller one; the scanned values are of use where the total, as
+// an unsigned number, is at most 2^31 - 1.
 __device__ int block_excl_scan(int v, int* sh, int* total) {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     int x = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+        if (lane >= o) x = add_sat(x, y);
     }
     if (lane == 63) sh[wv] = x;
     __syncthreads();
@@ -230,12 +233,12 @@ __device__ int block_excl_scan(int v, int* sh, int* total) {
 #pragma unroll
     for (int w = 0; w < kScanThreads / 64; ++w) {
         const int ws = sh[w];
-        before += (w < wv) ? ws : 0;
-        all += ws;
+        before = w < wv ? add_sat(before, ws) : before;
+        all = add_sat(all, ws);
     }
     *total = all;
     __syncthreads();  // sh may be reused by the caller
-    return before + x - v;
+    return (int)((uint32_t)before + (uint32_t)x - (uint32_t)v);
 }
 
 __global__ void k_scan_tiles(const int* in, int* out, int64_t n, int* bsum) {
@@ -246,14 +249,14 @@ __global__ void k_scan_tiles(const int* in, int* out, int64_t n, int* bsum) {
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         v[k] = (base + k < n) ? in[base + k] : 0;
-        s += v[k];
+        s = add_sat(s, v[k]);
     }
     int tot;
     int run = block_excl_scan(s, sh, &tot);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (base + k < n) out[base + k] = run;
-        run += v[k];
+        run = add_sat(run, v[k]);
     }
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
@@ -262,7 +265,7 @@ __global__ void k_scan_add(int* out, int64_t n, const int* boff) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     const int add = boff[blockIdx.x];
     for (int k = threadIdx.x; k < kScanTile; k += kScanThreads)
-        if (base + k < n) out[base + k] += add;
+        if (base + k < n) out[base + k] = add_sat(out[base + k], add);
 }
 
 // na scans of n ints at once (blockIdx.y picks the array): the same tile scan
@@ -280,14 +283,14 @@ __global__ void k_scan_tiles_n(const int* __restrict__ in, int* __restrict__ out
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         v[k] = (base + k < n) ? in[base + k] : 0;
-        s += v[k];
+        s = add_sat(s, v[k]);
     }
     int tot;
     int run = block_excl_scan(s, sh, &tot);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (base + k < n) out[base + k] = run;
-        run += v[k];
+        run = add_sat(run, v[k]);
     }
     if (threadIdx.x == 0) aux[j * au + blockIdx.x] = tot;
 }
@@ -298,7 +301,7 @@ __global__ void k_scan_add_n(int* out, int64_t n, const int* boff, int64_t nb) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     const int add = boff[j * nb + blockIdx.x];
     for (int k = threadIdx.x; k < kScanTile; k += kScanThreads)
-        if (base + k < n) out[base + k] += add;
+        if (base + k < n) out[base + k] = add_sat(out[base + k], add);
 }
 
 void scan_excl_i32_n(const int* in, int* out, int na, int64_t n, int* total, hipStream_t s) {

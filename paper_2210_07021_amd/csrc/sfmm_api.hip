@@ -473,6 +473,13 @@ int fp64_level(const sfmm_plan_impl& P) {
 // Scratch of an execute that does not allocate, a GPU
 constexpr size_t kNoallocScratchBytes = (size_t)256 << 20;
 
+// Most entries of a plan's list of FMM acts, and of its direct acts: offsets
+// are 32-bit.  SFMM_LIST_LIMIT lowers it (for tests of the refusal).
+uint32_t list_limit() {
+    const char* v = std::getenv("SFMM_LIST_LIMIT");
+    return v ? (uint32_t)std::max(0L, std::min(0x7fffffffL, std::strtol(v, nullptr, 10))) : 0x7fffffffu;
+}
+
 // Room of a hand-down list.  The lists of clustered-1e7 hold at most ~100
 // sources at the default MACs, those of a halo of smoothed particles more
 // than 256 (every box within sigma of its target splits on); a plan with a
@@ -584,6 +591,10 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
         zero_runs({tot.data(), 5 * sizeof(int)}, {big.data(), sizeof(int)}, {nullptr, 0}, s);
         count();
     }
+    // before anything is sized by them: the totals stay above the limit where
+    // the lists pass it (add_sat)
+    const uint32_t lim = list_limit();
+    if ((uint32_t)h[0] > lim || (uint32_t)h[1] > lim) throw Error(ST_INVALID_ARG, "interaction lists too large");
     P.n_m2l = h[0];
     const int n_p2p = h[1];
     P.ntl_all = h[2];

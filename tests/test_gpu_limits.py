@@ -1,0 +1,47 @@
+"""What a plan refuses because a list would not fit its 32-bit offsets, with the
+limits lowered by environment values: an error before anything is written, and
+good plans afterwards."""
+import numpy as np
+import pytest
+
+from paper_2210_07021_amd import skies
+
+pytestmark = pytest.mark.gpu
+
+
+def _sky(n=6000):
+    rng = skies.rng_for(190)
+    src = skies.uniform(n, rng)
+    return src, skies.masses_lognormal(n, rng), np.ascontiguousarray(np.concatenate([src, skies.grid(32)], axis=1))
+
+
+def _lists(sf, sky, **opt):
+    """Entries of Algorithm 1's two lists, and the outputs"""
+    plan = sf.Plan(*sky, **opt)
+    m2l, p2p = plan.export_lists()
+    out = [x.cpu().numpy() for x in plan.execute()]
+    plan.close()
+    return m2l.shape[0], p2p.shape[0], out
+
+
+@pytest.mark.parametrize("kind", ["direct", "fmm"])
+def test_lists_beyond_the_limit_are_refused(kind, monkeypatch, oracle_lib):
+    """More FMM acts, or more direct acts, than the offsets can hold."""
+    import paper_2210_07021_amd as sf
+    sky = _sky()
+    # point masses make more FMM acts than direct ones, smoothed particles the other way round
+    opt = dict(order=8, leaf_size=32) if kind == "fmm" else dict(order=8, leaf_size=32, npm_sigma=0.3)
+    n_m2l, n_p2p, ref = _lists(sf, sky, **opt)
+    lim = n_m2l if kind == "fmm" else n_p2p
+    assert (n_m2l > n_p2p) == (kind == "fmm") and lim > 1000
+    monkeypatch.setenv("SFMM_LIST_LIMIT", str(lim // 4))
+    with pytest.raises(sf.SfmmError, match="interaction lists too large") as e:
+        sf.Plan(*sky, **opt)
+    assert e.value.status == sf.SFMM_ERR_INVALID_ARG
+    with pytest.raises(sf.SfmmError, match="interaction lists too large"):
+        sf.Batch([sky[0]] * 3, [sky[1]] * 3, [sky[2]] * 3, **opt)
+    monkeypatch.setenv("SFMM_LIST_LIMIT", str(lim))
+    again = _lists(sf, sky, **opt)
+    assert again[:2] == (n_m2l, n_p2p)
+    for a, b in zip(ref, again[2]):
+        assert np.array_equal(a, b)

@@ -1,0 +1,46 @@
+"""Rules of the library compiled for the host (tests/host_rules.cpp, the same
+headers as the HIP code)."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def host_rules(tmp_path_factory):
+    if not (os.path.exists(HIPCC) or shutil.which("hipcc")):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("host_rules") / "host_rules")
+    cmd = [HIPCC, "-O2", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-Xclang", "-target-feature",
+           "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+           os.path.join(HERE, "host_rules.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return exe
+
+
+def _run(exe, mode, text=""):
+    r = subprocess.run([exe, mode], input=text, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    return r.stdout.split("\n")
+
+
+@pytest.mark.parametrize("total", [0, 5, 2**31 - 1, 2**31, 2**32 - 1, 2**32, 2**32 + 5, 3 * 2**32 + 7])
+def test_list_totals_do_not_wrap(host_rules, total):
+    """The totals of an interaction list, from per-box counts of up to 2^30: exact
+    up to 2^32 - 1, which is as far as a refusal needs them, and never less
+    than that beyond (a wrapped total of 2^32 + 5 entries read as 5)."""
+    rng = random.Random(total)
+    left, counts = total, [0]
+    while left > 0:
+        c = min(left, rng.choice([rng.randint(1, 1000), rng.randint(1, 2**30), 2**30]) if total > 10**6 else 1)
+        counts.append(c)
+        left -= c
+    rng.shuffle(counts)
+    got = [int(x) for x in _run(host_rules, "sums", " ".join(map(str, counts)) + "\n")[0].split()]
+    assert got == [min(total, 2**32 - 1)] * 3
