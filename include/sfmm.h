@@ -175,7 +175,8 @@ void sfmm_default_options(sfmm_options* opt);
  * pointers with a nonzero size, options out of range, non-finite input
  * coordinates or points off the unit sphere by more than 1e-6 (points off by
  * more than 1e-14 are renormalised), FMM acts or direct acts of the boxes with
- * targets below them beyond 2^31 - 1 entries. */
+ * targets below them beyond 2^31 - 1 entries, or lists cut into segments with
+ * beyond 2^31 - 1 partial sums of either kind (targets x segments). */
 sfmm_status sfmm_plan(const double* src, const double* q, int64_t N, const double* tgt, int64_t M,
                       const sfmm_options* opt, void* stream, sfmm_plan_t* out);
 

@@ -44,6 +44,7 @@
 #include "common.hpp"
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <type_traits>
 #include "expand.hpp"
 
@@ -151,8 +152,8 @@ void near_work(const int* count, const int* off, const int* nn, const int* src, 
 // Leaf i of the list tl has two lists in one CSR run: nn[T] entries for the
 // direct sum, then the entries for the expansions.  Per kind: ceil(K / seg)
 // items, and for a leaf cut into several of them as many times tcount partial
-// slots and one reduce record.  cnt [6][ntl]: items, slots, reduce records of
-// the first kind, then of the second.
+// slots (2^31 stands for more) and one reduce record.  cnt [6][ntl]: items,
+// slots, reduce records of the first kind, then of the second.
 __global__ void k_item_count(const int* __restrict__ tl, int ntl, const int* __restrict__ off,
                              const int* __restrict__ nn, const int* __restrict__ tcount, int seg_near, int seg_far,
                              int* __restrict__ cnt) {
@@ -164,7 +165,7 @@ __global__ void k_item_count(const int* __restrict__ tl, int ntl, const int* __r
     for (int q = 0; q < 2; ++q) {
         const int ns = (k[q] + seg[q] - 1) / seg[q];
         cnt[(size_t)(3 * q + 0) * ntl + i] = ns;
-        cnt[(size_t)(3 * q + 1) * ntl + i] = ns > 1 ? ns * nt : 0;
+        cnt[(size_t)(3 * q + 1) * ntl + i] = ns > 1 ? (int)min((int64_t)ns * nt, (int64_t)1 << 31) : 0;
         cnt[(size_t)(3 * q + 2) * ntl + i] = ns > 1 ? 1 : 0;
     }
 }
@@ -222,6 +223,13 @@ __global__ void k_gather_items(const int4* __restrict__ in, const uint32_t* __re
     if (i < n) out[i] = in[idx[i]];
 }
 
+// Most partial slots of either kind.  SFMM_SLOT_LIMIT lowers it (for tests of
+// the refusal).
+static int64_t slot_limit() {
+    const char* v = std::getenv("SFMM_SLOT_LIMIT");
+    return v ? std::max(0L, std::min(0x7fffffffL, std::strtol(v, nullptr, 10))) : 0x7fffffffL;
+}
+
 void build_items(const int* tl, int ntl, const int* off, const int* nn, const int* src, const int* count,
                  const int* tcount, int seg_near, int seg_far, int64_t slots_room, NearWork& out, int* pin,
                  hipStream_t s) {
@@ -238,14 +246,20 @@ void build_items(const int* tl, int ntl, const int* off, const int* nn, const in
         SFMM_HIP(hipStreamSynchronize(s));
     };
     tally();
-    if (seg_far < kSegFar && (pin[4] < 0 || pin[1] + (int64_t)pin[4] > slots_room)) {
+    // the totals as they are, also past 2^31 - 1 (add_sat)
+    auto slots = [&](int q) { return (int64_t)(uint32_t)pin[3 * q + 1]; };
+    if (seg_far < kSegFar && slots(0) + slots(1) > slots_room) {
         seg_far = kSegFar;
         tally();
     }
+    // a slot's number is a 32-bit one; items and reduce records are no more
+    // than the lists' entries
+    const int64_t lim = slot_limit();
+    if (slots(0) > lim || slots(1) > lim) throw Error(ST_INVALID_ARG, "near-field partial sums too large");
     const int n_near = pin[0], n = pin[0] + pin[3], red_near = pin[2];
     out.items.resize(std::max(n, 1));
     out.red.resize(std::max(pin[2] + pin[5], 1));
-    out.part.resize(4 * (size_t)std::max(pin[1] + pin[4], 1));
+    out.part.resize(4 * (size_t)std::max<int64_t>(slots(0) + slots(1), 1));
     out.near.items = out.items.data();
     out.near.red = out.red.data();
     out.near.part = out.part.data();

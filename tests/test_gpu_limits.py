@@ -45,3 +45,32 @@ def test_lists_beyond_the_limit_are_refused(kind, monkeypatch, oracle_lib):
     assert again[:2] == (n_m2l, n_p2p)
     for a, b in zip(ref, again[2]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["near", "far"])
+def test_partial_sums_beyond_the_limit_are_refused(kind, monkeypatch, oracle_lib):
+    """Lists cut into segments take a partial sum per target and segment: more of
+    either kind than can be numbered.  Every leaf's lists are cut here (segments
+    of 8 entries); the sum of both kinds may pass the limit."""
+    import paper_2210_07021_amd as sf
+    rng = skies.rng_for(191)
+    src = skies.clustered(6000, rng, n_clumps=20)
+    sky = (src, skies.masses_lognormal(6000, rng), skies.uniform(2500, rng))
+    opt = dict(order=20, leaf_size=16, near_segment=8, far_segment=8)
+    if kind == "near":
+        opt["order"] = 8  # no expansions at the targets at this order: every list entry is summed directly
+    plan = sf.Plan(*sky, **opt)
+    ref = [x.cpu().numpy() for x in plan.execute()]
+    scratch = plan.stats()["execute_scratch_bytes"]  # 32 bytes a slot, either kind rounded up to 256
+    plan.close()
+    assert scratch > 32 * 1000
+    monkeypatch.setenv("SFMM_SLOT_LIMIT", "100")
+    with pytest.raises(sf.SfmmError, match="partial sums too large") as e:
+        sf.Plan(*sky, **opt)
+    assert e.value.status == sf.SFMM_ERR_INVALID_ARG
+    # a limit on each kind, not on their sum
+    monkeypatch.setenv("SFMM_SLOT_LIMIT", str(scratch // 32 - (0 if kind == "near" else 16)))
+    plan = sf.Plan(*sky, **opt)
+    for a, b in zip(ref, plan.execute()):
+        assert np.array_equal(a, b.cpu().numpy())
+    plan.close()
