@@ -285,6 +285,25 @@ static_assert(sizeof(WalkRec) == 64, "one aligned segment");
 void box_records(int nb, const int* level, const uint64_t* pixel, const int* child0, const int* count, double c_s,
                  double c_t, double sigma, double ratio, int min_count, double* cen, double* rad, double* gdd,
                  WalkRec* rec, double4* ttrig, double* dtrig, double* hfar, hipStream_t s);
+// Items that a step of the list walk takes: s from the top of its stack (size of
+// them there) and i of the left ones of the hand-down list, at most step.  An
+// item that splits pushes four.  Full steps go on while all of theirs could
+// split and leave kGroupSpare places; the smaller ones keep to those places
+// too, and one item at a time, depth first, grows the stack by at most 3 a
+// level, 87 in all.
+constexpr int kGroupSpare = 96;
+struct GroupTake {
+    int s, i;
+};
+__host__ __device__ inline GroupTake group_take(int size, int left, int step, int stack) {
+    const int room = stack - kGroupSpare - size;
+    if (room >= 4 * step) {
+        const int s = size < step ? size : step, i = step - s < left ? step - s : left;
+        return {s, i};
+    }
+    const int s = room / 3 < step ? room / 3 : step;
+    return {s > 1 ? s : 1, 0};
+}
 struct GroupCtx {
     const WalkRec* rec;
     const double4* ttrig;  // [nb] cos, sin of R and of R / c_t

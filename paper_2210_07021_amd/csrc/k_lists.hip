@@ -250,7 +250,7 @@ __device__ __noinline__ uint8_t group_action_tie(const WalkRec* rec, const doubl
 // up to 7,300 direct acts on clustered-1e7, which kept single waves busy for
 // 0.5 ms after all others had ended), and those with an undecided MAC, whose
 // double-double code (TIE) would cost the one-wave kernels half their waves.
-constexpr int kGroupSpare = 96, kGroupSteps = 40, kGroupWide = 4096;
+constexpr int kGroupSteps = 40, kGroupWide = 4096;
 enum { G_LEVEL = 0, G_COUNT = 1, G_FILL = 2 };
 
 template <int MODE, int NW, bool TIE, bool SINGLE>
@@ -325,14 +325,8 @@ __device__ __forceinline__ void group_walk(const GroupCtx& w, int G, int only, c
     int size = 0, pos = 0;
     const uint64_t lt = (1ull << lane) - 1;
     for (int step = 0; size > 0 || pos < n_in; ++step) {  // uniform across the workgroup
-        const int avail = kStack - size;
-        int take_s, take_i = 0;
-        if (avail >= 4 * kStep) {
-            take_s = min(size, kStep);
-            take_i = min(kStep - take_s, n_in - pos);
-        } else {
-            take_s = max(1, min(kStep, (avail - kGroupSpare) / 3));
-        }
+        const GroupTake take = group_take(size, n_in - pos, kStep, kStack);
+        const int take_s = take.s, take_i = take.i;
         int S = 0, q = 0;
         const bool on = tid < take_s + take_i;
         if (tid < take_s) {

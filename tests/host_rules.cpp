@@ -3,7 +3,14 @@
 //   sums   : reads counts (decimal, up to 2^30), prints their total as the
 //            scans form it (add_sat over any grouping: one by one, in pairs
 //            of halves, in tiles of 256 threads of 16), as unsigned numbers
+//   stack  : every state of the list walk's stack in LDS, for its one, four and
+//            eight waves: prints the states, those from which a step could
+//            leave less than the spare places without being a depth-first
+//            one, and the most places that a schedule of splits takes which
+//            steers for the largest stack and then goes depth first (per
+//            number of waves)
 #include "../paper_2210_07021_amd/csrc/common.hpp"
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <vector>
@@ -33,6 +40,34 @@ int main(int argc, char** argv) {
         std::vector<int> t = v;
         while (t.size() > 1) t = tiles(tiles(t, 16), 256);
         printf("%u %u %u\n", one, halves(v, 0, v.size()), (uint32_t)t[0]);
+        return 0;
+    }
+    if (!strcmp(argv[1], "stack")) {
+        for (int nw : {1, 4, 8}) {
+            const int step = 64 * nw, stack = 1024 * nw, deepest = 29;
+            long states = 0, bad = 0;
+            int most = 0;
+            for (int size = 0; size <= stack - kGroupSpare; ++size) {
+                for (int left : {0, 1, step / 2, step, 1 << 30}) {
+                    if (size == 0 && left == 0) continue;  // the walk has ended
+                    ++states;
+                    const GroupTake t = group_take(size, left, step, stack);
+                    const int after = size - t.s + 4 * (t.s + t.i);  // all of them split
+                    if (t.s > size || t.i > left || t.s + t.i > step || t.s + t.i < 1) ++bad;
+                    if (after > stack - kGroupSpare && !(t.s == 1 && t.i == 0)) ++bad;
+                    // from here depth first: one level a step, each item splitting
+                    int at = std::max(after, size), lev = 1;
+                    for (int sz = after; lev < deepest; ++lev) {
+                        const GroupTake d = group_take(sz, 0, step, stack);
+                        if (d.s != 1) break;
+                        sz += 3;
+                        at = std::max(at, sz);
+                    }
+                    most = std::max(most, at);
+                }
+            }
+            printf("%d %ld %ld %d %d\n", nw, states, bad, most, stack);
+        }
         return 0;
     }
     return 2;

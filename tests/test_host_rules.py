@@ -44,3 +44,14 @@ def test_list_totals_do_not_wrap(host_rules, total):
     rng.shuffle(counts)
     got = [int(x) for x in _run(host_rules, "sums", " ".join(map(str, counts)) + "\n")[0].split()]
     assert got == [min(total, 2**32 - 1)] * 3
+
+
+def test_walk_stack_stays_in_bounds(host_rules):
+    """The stack of the list walk (LDS): no step from any state leaves it fewer
+    than the spare places, except the depth-first ones that the spare is for, and
+    those stay within it to the deepest level.  (One wave with 768 of 1,024
+    places taken took 64 items, which left 64 places for up to 87.)"""
+    for line in _run(host_rules, "stack"):
+        if line:
+            waves, states, bad, most, stack = (int(x) for x in line.split())
+            assert states > 4000 * waves and bad == 0 and most <= stack, line
