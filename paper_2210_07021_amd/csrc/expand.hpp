@@ -102,25 +102,28 @@ SFMM_HD double log_f64(double x) {
 // m/c_j - 1 (one FMA) has |r| <= 2^-10 and
 //   log x = e log 2 - log(1/c_j) + log(1 + r),
 // log(1 + r) = r + r^2 (-1/2 + r/3 - r^2/4 + r^3/5), first omitted term below
-// 2^-62.  The absolute error is a few 1e-16 (no relative bound near x = 1,
-// where the terms cancel; the sums it feeds only need the absolute one), and
-// one rounded log 2 is enough: |e| 2.3e-17 is 3e-17 of |log x|.  The
-// reciprocal comes from the same r: 1/m = (1/c_j) (1 - r)(1 + r^2 + r^4), short
-// of the geometric series by r^6 < 2^-60, times 2^-e.  Against a hardware
-// reciprocal estimate (a quarter-rate instruction) with two Newton steps and a
-// degree-7 series, 34 full-rate VALU instructions a pair instead of 39 of
-// which one counts four.
+// 2^-62; e log 2 in log_f64's two words.  The error is absolute (near x = 1 the
+// terms cancel; the sums it feeds only need that): at most 1.96e-16 of max(1,
+// |log x|), 4.9e-17 in the mean square over (0, 4).  The reciprocal starts from
+// the same r, 1/m = (1/c_j)(1 - r) to r^2 <= 2^-20, and one step of third order
+// (d = 1 - m y, y (1 + d + d^2)) makes it 1.11e-16 at most and 4.9e-17 in the
+// mean square, as two Newton steps on a hardware estimate do.  (Without that
+// step, as table entry times a series in r, it was 3.3e-16 and 8.7e-17, and a
+// log 2 in one word made the logs' mean square 5.8e-17.)  35 full-rate VALU
+// instructions a pair; with the hardware estimate and a degree-7 series from a
+// quarter of the table 39, one of which counts four.
 // The Horner coefficients (the last one, -1/2, is an inline constant of the
 // FMA): kernels take them as an argument, which keeps them in scalar registers.
 struct LogPoly {
-    double c5, c4, c3, nln2;  // 1/5, -1/4, 1/3, -log 2
+    double c5, c4, c3, ln2_hi, ln2_lo;  // 1/5, -1/4, 1/3, log 2
 };
-constexpr LogPoly kLogPoly = {1.0 / 5.0, -0.25, 1.0 / 3.0, -kLog2};
+constexpr LogPoly kLogPoly = {1.0 / 5.0, -0.25, 1.0 / 3.0, 6.93147180369123816490e-01, 1.90821492927058770002e-10};
 constexpr int kLogTab = 512;
+// (log, not log_f64: an error of the entry is one of every value near c_j)
 SFMM_HD double2 log_tab_entry(int j) {
     const double c = 0.5 + (j + 0.5) / 1024.0;
     const double ci = 1.0 / c;
-    return make_double2(ci, -log_f64(ci));
+    return make_double2(ci, -log(ci));
 }
 
 // the table entry of a positive normal double whose high word is hi
@@ -133,13 +136,14 @@ SFMM_HD void log_recip_at(double x, double2 t, const LogPoly& k, double* lg, dou
     int e;
     const double m = frexp(x, &e);
     const double r = fma(m, t.x, -1.0);
-    const double u = r * r;
     double q = fma(k.c5, r, k.c4);
     q = fma(q, r, k.c3);
     q = fma(q, r, -0.5);
-    *lg = fma((double)-e, k.nln2, t.y + fma(u, q, r));
-    const double v = 1.0 - r;
-    *inv = ldexp(t.x * fma(u, fma(u, v, v), v), -e);
+    const double de = (double)e;
+    *lg = fma(de, k.ln2_hi, fma(de, k.ln2_lo, t.y + fma(r * r, q, r)));
+    const double y = fma(t.x, -r, t.x);
+    const double d = fma(-m, y, 1.0);
+    *inv = ldexp(fma(y, fma(d, d, d), y), -e);
 }
 
 SFMM_HD void log_recip_tab(double x, const double2* tab, const LogPoly& k, double* lg, double* inv) {

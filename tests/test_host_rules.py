@@ -55,3 +55,18 @@ def test_walk_stack_stays_in_bounds(host_rules):
         if line:
             waves, states, bad, most, stack = (int(x) for x in line.split())
             assert states > 4000 * waves and bad == 0 and most <= stack, line
+
+
+# Errors (log: largest, root mean square; reciprocal: the same) of the pair loop
+# with the 128-entry table, the degree-7 series and a reciprocal refined by two
+# Newton steps, measured over the same arguments: what holds must not be worse.
+# (The largest of 2e6 varies with the table's own errors: 1 % room.)
+PAIR_ERRORS = [(2.292e-16, 5.31e-17, 1.111e-16, 4.90e-17), (2.266e-16, 4.79e-17, 1.111e-16, 4.72e-17),
+               (1.346e-16, 3.79e-17, 1.111e-16, 4.92e-17)]
+
+
+def test_pair_log_and_reciprocal_keep_their_accuracy(host_rules):
+    lines = _run(host_rules, "logerr")
+    for line, was in zip(lines, PAIR_ERRORS):
+        now = [float(x) for x in line.split()]
+        assert all(a <= 1.01 * b for a, b in zip(now, was)), (now, was)
