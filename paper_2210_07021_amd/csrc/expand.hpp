@@ -126,15 +126,14 @@ SFMM_HD double2 log_tab_entry(int j) {
     return make_double2(ci, -log(ci));
 }
 
-// the table entry of a positive normal double whose high word is hi
+// the table entry of a mantissa m in [1/2, 1) whose high word is hi (of the
+// argument itself it would be another one's where that is subnormal)
 SFMM_HD double2 log_tab_at(uint32_t hi, const double2* tab) {
     return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(tab) + (hi >> 7 & 0x1ff0u));
 }
 
-// log and reciprocal of a positive normal double x with its table entry t
-SFMM_HD void log_recip_at(double x, double2 t, const LogPoly& k, double* lg, double* inv) {
-    int e;
-    const double m = frexp(x, &e);
+// log and reciprocal of a positive double m 2^e, m in [1/2, 1), with m's table entry t
+SFMM_HD void log_recip_at(double m, int e, double2 t, const LogPoly& k, double* lg, double* inv) {
     const double r = fma(m, t.x, -1.0);
     double q = fma(k.c5, r, k.c4);
     q = fma(q, r, k.c3);
@@ -147,7 +146,9 @@ SFMM_HD void log_recip_at(double x, double2 t, const LogPoly& k, double* lg, dou
 }
 
 SFMM_HD void log_recip_tab(double x, const double2* tab, const LogPoly& k, double* lg, double* inv) {
-    log_recip_at(x, log_tab_at((uint32_t)(__builtin_bit_cast(unsigned long long, x) >> 32), tab), k, lg, inv);
+    int e;
+    const double m = frexp(x, &e);
+    log_recip_at(m, e, log_tab_at((uint32_t)(__builtin_bit_cast(unsigned long long, m) >> 32), tab), k, lg, inv);
 }
 
 struct cplx {

@@ -504,9 +504,10 @@ __device__ __forceinline__ void tile_pairs_hess(const TileF32& t, const NpmK& nk
 // target; acc[b]: S, V (and, HESS, hd = sum q (1 - n.d)/|d|^2 and h_ab = sum q
 // (e_a.d)(e_b.d)/|d|^4 in the target's basis e[b], Sec. 2.2: H_ab = (q/2pi)
 // [delta_ab (1 - n.d)/|d|^2 - 2 (e_a.d)(e_b.d)/|d|^4]; coincident points add
-// nothing).  |d|^2 of two distinct unit vectors is >= ~1e-32, so its high word
-// is zero only for coincident points, which take |d|^2 = 4 instead (log 4, and
-// d = 0 zeroes their deflection).
+// nothing).  Coincident points, |d|^2 = 0, take |d|^2 = 4 instead (log 4, and
+// d = 0 zeroes their deflection): both have a zero low word, so only the high
+// word is switched.  |d|^2 may be subnormal (two points beside a pole or an
+// axis, 1e-155 apart).
 struct TileF64 {
     double4 p[kTile];
 };
@@ -522,7 +523,8 @@ __device__ __forceinline__ void tile_pairs(const TileF64& t, const double2* ltab
     for (int j = r; j < tn; j += L) {
         const double4 sp = nx;
         nx = t.p[min(j + L, kTile - 1)];  // the next particle, read ahead
-        double d[TB][3], d2r[TB], d2[TB];
+        double d[TB][3], d2r[TB], m[TB];
+        int ex[TB];
         double2 tab[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
@@ -530,15 +532,15 @@ __device__ __forceinline__ void tile_pairs(const TileF64& t, const double2* ltab
             d[b][1] = a[b][1] - sp.y;
             d[b][2] = a[b][2] - sp.z;
             d2r[b] = d[b][0] * d[b][0] + d[b][1] * d[b][1] + d[b][2] * d[b][2];
-            const uint32_t h = (uint32_t)__double2hiint(d2r[b]), hi = h == 0 ? 0x40100000u : h;
-            d2[b] = __hiloint2double((int)hi, __double2loint(d2r[b]));
-            tab[b] = log_tab_at(hi, ltab);
+            m[b] = frexp(__hiloint2double(d2r[b] == 0.0 ? 0x40100000 : __double2hiint(d2r[b]), __double2loint(d2r[b])),
+                         &ex[b]);
+            tab[b] = log_tab_at((uint32_t)__double2hiint(m[b]), ltab);
         }
         __builtin_amdgcn_sched_barrier(0);  // every table read is under way before the first is waited for
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
             double lg, i0;
-            log_recip_at(d2[b], tab[b], lk, &lg, &i0);
+            log_recip_at(m[b], ex[b], tab[b], lk, &lg, &i0);
             double wi = sp.w * i0, wm = wi, w2 = 0.0;
             if constexpr (HESS) {
                 wm = d2r[b] == 0.0 ? 0.0 : wi;

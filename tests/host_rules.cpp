@@ -9,6 +9,7 @@
 //            one, and the most places that a schedule of splits takes which
 //            steers for the largest stack and then goes depth first (per
 //            number of waves)
+//   log    : reads x, prints the pair loop's log of x and 1/x
 //   logerr : largest and root mean square errors of the pair loop's log (in
 //            max(1, |log x|)) and reciprocal (relative), against long double,
 //            over 2e6 arguments each uniform in (0, 4), spread over 1e-32 ..
@@ -74,6 +75,16 @@ int main(int argc, char** argv) {
                 }
             }
             printf("%d %ld %ld %d %d\n", nw, states, bad, most, stack);
+        }
+        return 0;
+    }
+    if (!strcmp(argv[1], "log")) {
+        double2 tab[kLogTab];
+        for (int j = 0; j < kLogTab; ++j) tab[j] = log_tab_entry(j);
+        double x, lg, inv;
+        while (scanf("%lf", &x) == 1) {
+            log_recip_tab(x, tab, kLogPoly, &lg, &inv);
+            printf("%a %a\n", lg, inv);
         }
         return 0;
     }

@@ -74,3 +74,23 @@ def test_partial_sums_beyond_the_limit_are_refused(kind, monkeypatch, oracle_lib
     for a, b in zip(ref, plan.execute()):
         assert np.array_equal(a, b.cpu().numpy())
     plan.close()
+
+
+@pytest.mark.parametrize("hessian", [False, True])
+def test_points_closer_than_1e_150(hessian, oracle_lib):
+    """A source is left out of a target's sum only where both are the same point
+    bit for bit; points beside a pole may be 1e-150 to 1e-161 apart, where |d|^2
+    is subnormal and its reciprocal no longer finite (psi only)."""
+    import paper_2210_07021_amd as sf
+    gap = np.array([0.0, 1e-100, 1e-150, 3e-154, 1.6e-154, 1e-155, 7e-156, 1e-156, 3e-157, 1.2e-157, 1e-158, 1e-160])
+    src = np.array([[0.0], [0.0], [1.0]])
+    tgt = np.stack([gap, np.zeros_like(gap), np.ones_like(gap)])
+    plan = sf.Plan(src, np.array([2.0]), tgt, order=8, psi_gauge=sf.SFMM_GAUGE_RAW)
+    out = [x.cpu().numpy() for x in (plan.execute_hessian() if hessian else plan.execute())]
+    plan.close()
+    d2 = gap * gap
+    ref = np.where(gap == 0.0, 0.0, 2.0 / (4 * np.pi) * (np.log(np.where(d2 > 0, d2, 1.0)) - np.log(4.0)))
+    print(f"[gaps] {out[0]} {ref}", flush=True)
+    assert np.abs(out[0] - ref).max() <= 4 * np.spacing(np.abs(ref).max())
+    ok = d2 > 1e-307
+    assert np.allclose(out[1][0][ok], 2.0 / (2 * np.pi) / gap[ok], rtol=1e-14) and not out[1][:, gap == 0.0].any()

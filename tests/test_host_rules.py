@@ -1,5 +1,6 @@
 """Rules of the library compiled for the host (tests/host_rules.cpp, the same
 headers as the HIP code)."""
+import math
 import os
 import random
 import shutil
@@ -70,3 +71,14 @@ def test_pair_log_and_reciprocal_keep_their_accuracy(host_rules):
     for line, was in zip(lines, PAIR_ERRORS):
         now = [float(x) for x in line.split()]
         assert all(a <= 1.01 * b for a, b in zip(now, was)), (now, was)
+
+
+def test_pair_log_of_subnormal_arguments(host_rules):
+    """|d|^2 below 2.2e-308 is a subnormal number: its mantissa, not its own bits,
+    picks the table entry.  (The reciprocal is finite down to 5.6e-309.)"""
+    rng = random.Random(5)
+    xs = [10 ** rng.uniform(-323, -307) for _ in range(2000)] + [5e-324, 2.0**-1022, 2.0**-1022 - 2.0**-1074]
+    for x, line in zip(xs, _run(host_rules, "log", "".join(x.hex() + "\n" for x in xs))):
+        lg, inv = (float.fromhex(t) for t in line.split())
+        assert abs(lg - math.log(x)) <= 2.5e-16 * abs(math.log(x)), x
+        assert inv == math.inf or abs(inv * x - 1.0) <= 4 * 2.0**-52, x
