@@ -1561,15 +1561,22 @@ sfmm_status sfmm_export_expansions(sfmm_plan_t plan, double* multipole, double* 
         sfmm_plan_impl& P = *plan;
         P.wait();
         if (!P.executed) throw Error(ST_INVALID_ARG, "plan has not been executed");
-        if (local && P.N > 0 && P.n_order < P.nbox) {
-            // the execute made the local expansions of the boxes with targets
-            // only: here those of every box, at the same orders
+        // the execute made the local expansions of the boxes with targets only:
+        // those of every box, at the same orders, are made here, in buffers of
+        // their own (a batch's graph may be working on the plan's)
+        DVec<double> full_local;
+        DVec<float> full_multf;
+        const bool full = local && P.N > 0 && P.n_order < P.nbox;
+        if (full) {
             ensure_full(P, nullptr);
             DVec<int> order;
             const FarView v = full_view(P, &order);
+            full_local.resize((size_t)P.nbox * (2 * P.p + 2));
+            if (v.n_fp64 < v.n) full_multf.resize((size_t)P.nbox * 2 * P.p);
             FmmCtx c = P.ctx();
+            c.local = full_local.data();
             c.need = nullptr;
-            m2l_stage(P, c, v, nullptr, !P.ran_policy, nullptr);
+            m2l_stage(P, c, v, full_multf.data(), !P.ran_policy, nullptr);
             for (int L = 1; L + 1 < (int)P.lvl_start.size(); ++L)
                 fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1], nullptr);
             SFMM_HIP(hipStreamSynchronize(nullptr));
@@ -1595,7 +1602,7 @@ sfmm_status sfmm_export_expansions(sfmm_plan_t plan, double* multipole, double* 
             }
         };
         unscale(P.mult, multipole, false);
-        unscale(P.local, local, true);
+        unscale(full ? full_local : P.local, local, true);
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
