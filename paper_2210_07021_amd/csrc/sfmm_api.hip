@@ -127,6 +127,9 @@ struct sfmm_plan_impl {
     int n_order = 0;     // boxes in m2l_order (those with targets)
     int n_m2l_fp64 = 0;  // the first n_m2l_fp64 boxes of m2l_order take the FP64 M2L
     int lc = 29;         // last FP64 level (the precision tier's; 29: every box)
+    // pairs per box that SFMM_WALK_RATIO forced when the plan was made (0: not
+    // set): room of the hand-down lists and, later, of the frontier walk's buffers
+    double forced_ratio = 0.0;
     // Algorithm 1's lists of every box, made when the exports or the
     // statistics ask
     struct FullLists {
@@ -331,15 +334,15 @@ bool walk(sfmm_plan_impl& P, const WalkCtx& w, bool exact, DVec<uint64_t>& m2l, 
     for (int i = 0; i < 12; ++i)
         for (int j = 0; j < 12; ++j) f0.push_back(make_int2(i, j));
     const int n0 = (int)f0.size();
-    // SFMM_WALK_RATIO (pairs per box, all three capacities, no lower bound)
-    // overrides the capacities: tests use it to drive the overflow path
-    const char* forced = std::getenv("SFMM_WALK_RATIO");
+    // a forced ratio (all three capacities, no lower bound) overrides the
+    // capacities: tests use it to drive the overflow path
+    const bool forced = P.forced_ratio > 0.0;
     WalkCaps cap;
     {
         std::lock_guard<std::mutex> lk(g_walk_mu);
         const double lo = forced ? 1.0 : 65536.0;
         auto c = [&](double r) { return (int)std::min(2.0e9, std::max(lo, r * P.nbox)); };
-        const double f = forced ? std::atof(forced) : 0.0;
+        const double f = P.forced_ratio;
         cap.frontier = exact ? n0 : c(forced ? f : g_walk_ratio[0]);
         cap.m2l = exact ? 1 : c(forced ? f : g_walk_ratio[1]);
         cap.p2p = exact ? 1 : c(forced ? f : g_walk_ratio[2]);
@@ -511,11 +514,12 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     }
     const int stage_walk = prof.begin(S_WALK);
     const int nlev = (int)P.lvl_start.size() - 1, nsplit = (nb - 12) / 4;
-    // SFMM_WALK_RATIO also shrinks the hand-down lists: tests use it to drive
-    // the fallback
-    const char* forced = std::getenv("SFMM_WALK_RATIO");
-    const int cd = forced ? std::max(1, (int)std::atof(forced))
-                          : std::clamp(kHandDownRoom / std::max(nsplit, 1), kHandDown, kHandDownMax);
+    // SFMM_WALK_RATIO shrinks the hand-down lists (and the frontier walk's room
+    // when the full lists are asked for): tests use it to drive the fallbacks
+    if (const char* v = std::getenv("SFMM_WALK_RATIO")) P.forced_ratio = std::max(1e-6, std::atof(v));
+    const int cd = P.forced_ratio > 0.0
+                       ? std::max(1, (int)P.forced_ratio)
+                       : std::clamp(kHandDownRoom / std::max(nsplit, 1), kHandDown, kHandDownMax);
     DVec<int> dlist, dcnt, cnt, off, tot;
     DVec<int64_t> doff;
     DVec<int> big;

@@ -94,3 +94,29 @@ def test_points_closer_than_1e_150(hessian, oracle_lib):
     assert np.abs(out[0] - ref).max() <= 4 * np.spacing(np.abs(ref).max())
     ok = d2 > 1e-307
     assert np.allclose(out[1][0][ok], 2.0 / (2 * np.pi) / gap[ok], rtol=1e-14) and not out[1][:, gap == 0.0].any()
+
+
+@pytest.mark.parametrize("ratio", ["0.05", "1", "7"])
+def test_exact_reruns_of_both_walks(ratio, monkeypatch, oracle_lib):
+    """A plan made with too little room (SFMM_WALK_RATIO) makes its hand-down
+    lists once more with exact sizes, and the full lists that its statistics and
+    exports ask for later too: the same lists, sums and local expansions."""
+    import paper_2210_07021_amd as sf
+    rng = skies.rng_for(192)
+    src = skies.clustered(20000, rng, n_clumps=30)
+    q = skies.masses_lognormal(20000, rng)
+    tgt = np.ascontiguousarray(src[:, ::29])
+    got = []
+    for forced in (False, True):
+        if forced:
+            monkeypatch.setenv("SFMM_WALK_RATIO", ratio)
+        plan = sf.Plan(src, q, tgt, order=10, leaf_size=8)
+        monkeypatch.delenv("SFMM_WALK_RATIO", raising=False)
+        out = [x.cpu().numpy() for x in plan.execute()]
+        stats = plan.stats()
+        lists = plan.export_lists()
+        assert (stats["n_m2l"], stats["n_p2p"]) == (lists[0].shape[0], lists[1].shape[0])
+        got.append(out + list(lists) + list(plan.export_expansions()) + [np.array(stats["m2l_order_sq"])])
+        plan.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
