@@ -280,11 +280,19 @@ sfmm_status sfmm_batch_execute(sfmm_batch_t batch, double* const* psi, double* c
 sfmm_status sfmm_batch_plan_at(sfmm_batch_t batch, int32_t i, sfmm_plan_t* out);
 void sfmm_batch_destroy(sfmm_batch_t batch);
 
-/* Sizes of a plan. */
+/* Sizes of a plan.  n_m2l, n_p2p and m2l_order_sq count Algorithm 1's lists over
+ * all boxes, which a plan does not need (it makes those of the boxes with
+ * targets below them): the first sfmm_stats_get, export of lists, export of
+ * local expansions or draw of order samples makes them, for as long as the plan
+ * lives.  sfmm_plan_info gives all other fields without them (-1 in those
+ * three).  Errors of sfmm_stats_get: SFMM_ERR_INVALID_ARG for lists beyond 2^31
+ * - 1 entries, SFMM_ERR_OUT_OF_MEMORY. */
 sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out);
+sfmm_status sfmm_plan_info(sfmm_plan_t plan, sfmm_stats* out);
 
 /* Host copies of the tree for comparisons, in the library's box order
- * (level, then pixel).  Buffers are host memory of the sizes in sfmm_stats:
+ * (level, then pixel).  Buffers are host memory of the sizes in sfmm_stats
+ * (sfmm_plan_info is enough):
  *   level, pixel, first, count, parent, child0: [n_boxes] (child0 = -1 for a
  *   leaf, parent = -1 at level 0); centre [3][n_boxes]; radius [n_boxes]
  *   (radians).  Any pointer may be NULL to skip that array. */

@@ -100,6 +100,7 @@ SIGNATURES = {
     "sfmm_defl_to_thetaphi": (ctypes.c_int, [_P, _P, _P, _I64, _P]),
     "sfmm_raytrace": (ctypes.c_int, [ctypes.c_int32, _P, _P, _P, _P, _P, _I64, _P, ctypes.POINTER(Options), _P]),
     "sfmm_stats_get": (ctypes.c_int, [_P, ctypes.POINTER(Stats)]),
+    "sfmm_plan_info": (ctypes.c_int, [_P, ctypes.POINTER(Stats)]),
     "sfmm_export_boxes": (ctypes.c_int, [_P] * 9),
     "sfmm_export_lists": (ctypes.c_int, [_P] * 5),
     "sfmm_export_keys": (ctypes.c_int, [_P] * 6),
@@ -401,8 +402,15 @@ class Plan:
         _check(self._lib.sfmm_stats_get(self._h, ctypes.byref(s)))
         return s.as_dict()
 
+    def info(self) -> dict:
+        """stats() without the fields that count Algorithm 1's lists over all boxes
+        (n_m2l, n_p2p and m2l_order_sq are -1), which are made on request."""
+        s = Stats()
+        _check(self._lib.sfmm_plan_info(self._h, ctypes.byref(s)))
+        return s.as_dict()
+
     def export_boxes(self) -> dict:
-        nb = self.stats()["n_boxes"]
+        nb = self.info()["n_boxes"]
         out = dict(level=np.zeros(nb, np.int32), pixel=np.zeros(nb, np.int64), first=np.zeros(nb, np.int64),
                    count=np.zeros(nb, np.int64), parent=np.zeros(nb, np.int64), child0=np.zeros(nb, np.int64),
                    centre=np.zeros((3, nb)), radius=np.zeros(nb))
@@ -436,13 +444,13 @@ class Plan:
         return (f, l, pr) if with_pairs else (f, l)
 
     def export_work(self) -> dict:
-        nb = self.stats()["n_boxes"]
+        nb = self.info()["n_boxes"]
         out = dict(tgt_count=np.zeros(nb, np.int64), pairs=np.zeros(nb, np.int64), evals=np.zeros(nb, np.int64))
         _check(self._lib.sfmm_export_work(self._h, *[a.ctypes.data_as(_P) for a in out.values()]))
         return out
 
     def export_expansions(self):
-        st = self.stats()
+        st = self.info()
         w = 2 * st["order"] + 2
         mult = np.zeros((st["n_boxes"], w))
         loc = np.zeros((st["n_boxes"], w))

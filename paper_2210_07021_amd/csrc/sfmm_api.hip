@@ -160,9 +160,10 @@ struct sfmm_plan_impl {
     DVec<float4> decay;       // per-box multipole decay features
     DVec<uint8_t> m2l_ord;    // order of every FMM act (last execute)
     DVec<int> ord_off, ord_src;  // FMM acts split by order
-    // sum of p'^2 over Algorithm 1's FMM acts at the last execute's orders; -1:
-    // not summed yet (done when the statistics ask)
-    long long m2l_order_sq = -1;
+    // sum of p'^2 over Algorithm 1's FMM acts at the orders of the plan's policy
+    // (they depend on the plan's inputs alone); -1: not summed yet (done when the
+    // statistics ask)
+    long long policy_order_sq = -1;
     bool ran_policy = false;  // the last execute used the per-pair orders
     bool executed = false;
     // judge of the per-pair order policies (first execute of the plan)
@@ -426,6 +427,13 @@ bool walk(sfmm_plan_impl& P, const WalkCtx& w, bool exact, DVec<uint64_t>& m2l, 
     return true;
 }
 
+// Most entries of a plan's list of FMM acts, and of its direct acts: offsets
+// are 32-bit.  SFMM_LIST_LIMIT lowers it (for tests of the refusal).
+uint32_t list_limit() {
+    const char* v = std::getenv("SFMM_LIST_LIMIT");
+    return v ? (uint32_t)std::max(0L, std::min(0x7fffffffL, std::strtol(v, nullptr, 10))) : 0x7fffffffu;
+}
+
 // Algorithm 1's lists of every box (exports, statistics): the frontier walk
 // and a stable sort of its pairs by target.
 void ensure_full(sfmm_plan_impl& P, hipStream_t s) {
@@ -457,6 +465,7 @@ void ensure_full(sfmm_plan_impl& P, hipStream_t s) {
     DVec<uint64_t> m2l, p2p;
     if (!walk(P, w, false, m2l, p2p, &F.n_m2l, &F.n_p2p, s) && !walk(P, w, true, m2l, p2p, &F.n_m2l, &F.n_p2p, s))
         throw Error(ST_INTERNAL, "the interaction walk overflowed its exactly sized buffers");
+    if ((uint32_t)std::max(F.n_m2l, F.n_p2p) > list_limit()) throw Error(ST_INVALID_ARG, "interaction lists too large");
     m2l.grow(std::max(F.n_m2l, 1), s);
     p2p.grow(std::max(F.n_p2p, 1), s);
     sort_pairs_to_csr(m2l, F.n_m2l, P.nbox, F.m2l_off, F.m2l_src, &F.m2l_ent, s);
@@ -475,13 +484,6 @@ int fp64_level(const sfmm_plan_impl& P) {
 
 // Scratch of an execute that does not allocate, a GPU
 constexpr size_t kNoallocScratchBytes = (size_t)256 << 20;
-
-// Most entries of a plan's list of FMM acts, and of its direct acts: offsets
-// are 32-bit.  SFMM_LIST_LIMIT lowers it (for tests of the refusal).
-uint32_t list_limit() {
-    const char* v = std::getenv("SFMM_LIST_LIMIT");
-    return v ? (uint32_t)std::max(0L, std::min(0x7fffffffL, std::strtol(v, nullptr, 10))) : 0x7fffffffu;
-}
 
 // Room of a hand-down list.  The lists of clustered-1e7 hold at most ~100
 // sources at the default MACs, those of a halo of smoothed particles more
@@ -1038,7 +1040,6 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
                         P.n_order,        P.n_m2l_fp64,     P.n_m2l};
         m2l_stage(P, c, v, xs ? xs->multf : nullptr, fixed, s);
         P.ran_policy = !fixed && P.opt.order_policy != SFMM_ORDER_FIXED;
-        P.m2l_order_sq = -1;
     }
     // down-pass: Lemma 4 from level 1 down
     {
@@ -1106,6 +1107,44 @@ void judge_start(sfmm_plan_impl& P, const double* tgt, Beside& ov, hipStream_t s
     judge_targets(P.judge_pos.data(), S, tgt, P.M, P.judge_tsel.data(), s);
     judge_sum(P.spt.data(), P.N, P.judge_tsel.data(), S, P.judge_part.data(), ov.fork(s));
     P.judge_ready = true;
+}
+
+// What a plan holds by itself: every field of the statistics but those of
+// Algorithm 1's lists over all boxes (-1).  The direct-act pairs and the leaves
+// with direct sums are counted on the first request.
+void plan_info(const sfmm_plan_impl& P, sfmm_stats& out) {
+    std::memset(&out, 0, sizeof(out));
+    out.n_sources = P.N;
+    out.n_targets = P.M;
+    out.n_boxes = P.nbox;
+    out.n_levels = (int64_t)P.lvl_start.size() - 1;
+    out.n_leaves = P.nbox - (P.nbox - 12) / 4;  // every split box has four children
+    out.n_m2l = out.n_p2p = out.m2l_order_sq = -1;
+    if (P.ntl < 0) P.ntl = count_boxes(P.work.near, nullptr);
+    out.n_target_leaves = P.ntl;
+    if (P.n_p2p_pairs < 0 && P.nbox > 0) {
+        DVec<long long> w, tot;
+        w.resize(2 * (size_t)P.nbox);
+        tot.resize(2);
+        near_work(P.count.data(), P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.tcount.data(), P.nbox, w.data(),
+                  w.data() + P.nbox, nullptr);
+        sum_i64(w.data(), P.nbox, tot.data(), nullptr);
+        sum_i64(w.data() + P.nbox, P.nbox, tot.data() + 1, nullptr);
+        long long h[2];
+        SFMM_HIP(hipMemcpy(h, tot.data(), sizeof(h), hipMemcpyDeviceToHost));
+        P.n_p2p_pairs = h[0];
+        P.n_m2p_evals = h[1];
+    }
+    out.n_p2p_pairs = P.n_p2p_pairs < 0 ? 0 : P.n_p2p_pairs;
+    out.n_m2p_evals = P.n_m2p_evals < 0 ? 0 : P.n_m2p_evals;
+    out.order = P.p;
+    out.leaf_size = P.opt.leaf_size;
+    out.q_total = P.q_total;
+    out.execute_scratch_bytes = (int64_t)exec_scratch_bytes(P);
+    out.judge_psi = P.judged ? P.judge_psi : -1.0;
+    out.judge_alpha = P.judged ? P.judge_alpha : -1.0;
+    out.judge_targets = P.judged ? P.judge_S : 0;
+    out.fell_back = (P.judge_failed && !P.opt.no_fallback) ? 1 : 0;
 }
 
 // The judge: psi and alpha of the last execute at the plan's S judge
@@ -1406,69 +1445,49 @@ sfmm_status sfmm_execute_noalloc(sfmm_plan_t plan, double* psi, double* defl, vo
     }
 }
 
-sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
-    // (the exact direct-act pair count is computed here, outside planning)
-    if (!plan || !out) {
-        g_last_error = "plan or out is NULL";
-        return SFMM_ERR_INVALID_ARG;
-    }
+sfmm_status sfmm_plan_info(sfmm_plan_t plan, sfmm_stats* out) {
     try {
         PoolStream ps(nullptr);
-        sfmm_plan_impl& P = *plan;
-        P.wait();
-        ensure_full(P, nullptr);
-        std::memset(out, 0, sizeof(*out));
-        out->n_sources = P.N;
-        out->n_targets = P.M;
-        out->n_boxes = P.nbox;
-        out->n_levels = (int64_t)P.lvl_start.size() - 1;
-        std::vector<int> c0(P.nbox);
-        if (P.nbox) SFMM_HIP(hipMemcpy(c0.data(), P.child0.data(), sizeof(int) * P.nbox, hipMemcpyDeviceToHost));
-        out->n_leaves = std::count_if(c0.begin(), c0.end(), [](int v) { return v < 0; });
-        out->n_m2l = P.full.n_m2l;
-        out->n_p2p = P.full.n_p2p;
-        if (P.ntl < 0) P.ntl = count_boxes(P.work.near, nullptr);
-        out->n_target_leaves = P.ntl;
-        if (P.n_p2p_pairs < 0 && P.nbox > 0) {
-            DVec<long long> w, tot;
-            w.resize(2 * (size_t)P.nbox);
-            tot.resize(2);
-            near_work(P.count.data(), P.p2p_off.data(), P.nn.data(), P.p2p_src.data(), P.tcount.data(), P.nbox,
-                      w.data(), w.data() + P.nbox, nullptr);
-            sum_i64(w.data(), P.nbox, tot.data(), nullptr);
-            sum_i64(w.data() + P.nbox, P.nbox, tot.data() + 1, nullptr);
-            long long h[2];
-            SFMM_HIP(hipMemcpy(h, tot.data(), sizeof(h), hipMemcpyDeviceToHost));
-            P.n_p2p_pairs = h[0];
-            P.n_m2p_evals = h[1];
-        }
-        out->n_p2p_pairs = P.n_p2p_pairs < 0 ? 0 : P.n_p2p_pairs;
-        out->n_m2p_evals = P.n_m2p_evals < 0 ? 0 : P.n_m2p_evals;
-        if (P.executed && P.m2l_order_sq < 0) {
-            if (P.ran_policy && P.full.n_m2l > 0) {
-                const FarView v = full_view(P, nullptr);
-                DVec<int> bo, bs;
-                DVec<long long> osq;
-                osq.resize(1);
-                pair_orders(P, P.ctx(), v, nullptr);
-                order_split(v.off, v.src, P.m2l_ord.data(), P.nbox, v.n_pairs, P.p, bo, bs, osq.data(), nullptr);
-                SFMM_HIP(hipMemcpy(&P.m2l_order_sq, osq.data(), sizeof(long long), hipMemcpyDeviceToHost));
-            } else {
-                P.m2l_order_sq = (long long)P.full.n_m2l * P.p * P.p;
-            }
-        }
-        out->m2l_order_sq = P.executed ? P.m2l_order_sq : 0;
-        out->order = P.p;
-        out->leaf_size = P.opt.leaf_size;
-        out->q_total = P.q_total;
-        out->execute_scratch_bytes = (int64_t)exec_scratch_bytes(P);
-        out->judge_psi = P.judged ? P.judge_psi : -1.0;
-        out->judge_alpha = P.judged ? P.judge_alpha : -1.0;
-        out->judge_targets = P.judged ? P.judge_S : 0;
-        out->fell_back = (P.judge_failed && !P.opt.no_fallback) ? 1 : 0;
+        if (!plan || !out) throw Error(ST_INVALID_ARG, "plan or out is NULL");
+        plan->wait();
+        plan_info(*plan, *out);
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
+    } catch (const std::exception& e) {
+        g_last_error = e.what();
+        return SFMM_ERR_INTERNAL;
+    }
+}
+
+sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
+    try {
+        PoolStream ps(nullptr);
+        if (!plan || !out) throw Error(ST_INVALID_ARG, "plan or out is NULL");
+        sfmm_plan_impl& P = *plan;
+        P.wait();
+        ensure_full(P, nullptr);
+        plan_info(P, *out);
+        out->n_m2l = P.full.n_m2l;
+        out->n_p2p = P.full.n_p2p;
+        const bool by_policy = P.ran_policy && P.full.n_m2l > 0;
+        if (P.executed && by_policy && P.policy_order_sq < 0) {
+            const FarView v = full_view(P, nullptr);
+            DVec<int> bo, bs;
+            DVec<long long> osq;
+            osq.resize(1);
+            pair_orders(P, P.ctx(), v, nullptr);
+            order_split(v.off, v.src, P.m2l_ord.data(), P.nbox, v.n_pairs, P.p, bo, bs, osq.data(), nullptr);
+            SFMM_HIP(hipMemcpy(&P.policy_order_sq, osq.data(), sizeof(long long), hipMemcpyDeviceToHost));
+        }
+        const long long fixed_sq = (long long)P.full.n_m2l * P.p * P.p;
+        out->m2l_order_sq = !P.executed ? 0 : by_policy ? P.policy_order_sq : fixed_sq;
+        return SFMM_OK;
+    } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
+        g_last_error = e.what();
+        return SFMM_ERR_INTERNAL;
     }
 }
 
