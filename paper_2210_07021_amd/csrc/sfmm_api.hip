@@ -748,6 +748,11 @@ sfmm_status fail(const Error& e) {
     g_last_error = e.what();
     return (sfmm_status)e.status;
 }
+// what the standard library throws (no host memory)
+sfmm_status fail(const std::exception& e) {
+    g_last_error = e.what();
+    return SFMM_ERR_INTERNAL;
+}
 
 template <typename S, typename D>
 void copy_widen(D* dst, const S* dev, size_t n) {
@@ -1290,8 +1295,7 @@ sfmm_status sfmm_plan(const double* src, const double* q, int64_t N, const doubl
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1325,8 +1329,7 @@ sfmm_status sfmm_execute(sfmm_plan_t plan, double* psi, double* defl, void* stre
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1358,8 +1361,7 @@ sfmm_status sfmm_execute_hessian(sfmm_plan_t plan, double* psi, double* defl, do
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1370,6 +1372,8 @@ sfmm_status sfmm_lensing(const double* hess, int64_t M, double* out, void* strea
         lensing_from_hessian(hess, M, out, (hipStream_t)stream);
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1410,8 +1414,7 @@ sfmm_status sfmm_raytrace(int32_t nlayer, const double* const* src, const double
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1440,8 +1443,7 @@ sfmm_status sfmm_execute_noalloc(sfmm_plan_t plan, double* psi, double* defl, vo
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1455,8 +1457,7 @@ sfmm_status sfmm_plan_info(sfmm_plan_t plan, sfmm_stats* out) {
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1486,8 +1487,7 @@ sfmm_status sfmm_stats_get(sfmm_plan_t plan, sfmm_stats* out) {
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -1514,6 +1514,8 @@ sfmm_status sfmm_export_boxes(sfmm_plan_t plan, int32_t* level, int64_t* pixel, 
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
+    } catch (const std::exception& e) {
+        return fail(e);
     }
 }
 
@@ -1530,6 +1532,8 @@ sfmm_status sfmm_export_lists(sfmm_plan_t plan, int64_t* m2l_src, int64_t* m2l_t
         export_csr(P.full.p2p_off, P.full.p2p_src, P.nbox, P.full.n_p2p, p2p_src, p2p_tgt);
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1554,6 +1558,8 @@ sfmm_status sfmm_export_keys(sfmm_plan_t plan, uint64_t* src_keys, int64_t* src_
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
+    } catch (const std::exception& e) {
+        return fail(e);
     }
 }
 
@@ -1573,6 +1579,8 @@ sfmm_status sfmm_export_work(sfmm_plan_t plan, int64_t* tgt_count, int64_t* pair
         copy_widen(evals, w.data() + P.nbox, P.nbox);
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1629,6 +1637,8 @@ sfmm_status sfmm_export_expansions(sfmm_plan_t plan, double* multipole, double* 
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
+    } catch (const std::exception& e) {
+        return fail(e);
     }
 }
 
@@ -1681,6 +1691,8 @@ sfmm_status sfmm_order_samples(sfmm_plan_t plan, int64_t n, uint64_t seed, float
         }
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1736,6 +1748,8 @@ sfmm_status sfmm_mlp_grad(const float* weights, const float* features, const flo
         if (loss) *loss = h[kMlpWeights];
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1802,6 +1816,8 @@ sfmm_status sfmm_mlp_train(const float* features, const float* labels, int64_t n
         return SFMM_OK;
     } catch (const Error& e) {
         return fail(e);
+    } catch (const std::exception& e) {
+        return fail(e);
     }
 }
 
@@ -1827,6 +1843,8 @@ sfmm_status sfmm_mlp_forward(const float* weights, const float* features, int64_
         SFMM_HIP(hipMemcpy(y, out.data(), sizeof(float) * n, hipMemcpyDeviceToHost));
         return SFMM_OK;
     } catch (const Error& e) {
+        return fail(e);
+    } catch (const std::exception& e) {
         return fail(e);
     }
 }
@@ -1914,8 +1932,7 @@ sfmm_status sfmm_batch_plan(int32_t nshell, const double* const* src, const doub
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 
@@ -2020,8 +2037,7 @@ sfmm_status sfmm_batch_execute(sfmm_batch_t batch, double* const* psi, double* c
     } catch (const Error& e) {
         return fail(e);
     } catch (const std::exception& e) {
-        g_last_error = e.what();
-        return SFMM_ERR_INTERNAL;
+        return fail(e);
     }
 }
 

@@ -3,6 +3,7 @@ headers as the HIP code)."""
 import math
 import os
 import random
+import re
 import shutil
 import subprocess
 
@@ -82,3 +83,14 @@ def test_pair_log_of_subnormal_arguments(host_rules):
         lg, inv = (float.fromhex(t) for t in line.split())
         assert abs(lg - math.log(x)) <= 2.5e-16 * abs(math.log(x)), x
         assert inv == math.inf or abs(inv * x - 1.0) <= 4 * 2.0**-52, x
+
+
+def test_no_exception_leaves_a_c_entry():
+    """Every C entry that can throw turns the library's errors and those of the
+    standard library (no host memory for a copy) into a status."""
+    text = open(os.path.join(HERE, "..", "paper_2210_07021_amd", "csrc", "sfmm_api.hip")).read()
+    entries = re.split(r"\n(?=sfmm_status sfmm_|void sfmm_|const char\* sfmm_|int32_t sfmm_)", text[text.index('extern "C"'):])
+    tried = [e for e in entries if re.search(r"\n    try \{", e)]
+    assert len(tried) >= 19
+    for e in tried:
+        assert re.search(r"\n    \} catch \(const Error& e\) \{\n.*\n    \} catch \(const std::exception& e\) \{", e), e[:60]
