@@ -353,6 +353,19 @@ struct NearCtx {
     const double *tx, *ty, *tz;
     const double* hfar;  // [nb] a close leaf farther than this from every target goes through its expansion
 };
+// Sort key of an ordered list's entry: its round (0 .. 63), the source's first
+// particle (31 bits), and room for the entry's place in the list as it was made
+constexpr int kActIndexBits = 27;
+__host__ __device__ inline uint64_t act_order_key(int round, int first) {
+    return (uint64_t)(uint32_t)round << (31 + kActIndexBits) | (uint64_t)(uint32_t)first << kActIndexBits;
+}
+__host__ __device__ inline int act_place(uint64_t key) { return (int)(key & ((1u << kActIndexBits) - 1)); }
+// whether every list of a CSR over n boxes leaves its places that room
+inline bool ordered_lists_fit(const int* off, int n) {
+    for (int b = 0; b < n; ++b)
+        if (off[b + 1] - off[b] > 1 << kActIndexBits) return false;
+    return true;
+}
 // Direct-act lists praw (CSR poff) of the ntl leaves tl to psrc: entries summed
 // particle by particle first (nn[T] of them), then those taken through their
 // expansion; ordered: both in the order in which Algorithm 1's frontier walk

@@ -597,7 +597,7 @@ __device__ __forceinline__ uint64_t box_key(const NearCtx& c, int b) {
 __device__ __forceinline__ uint64_t act_key(const NearCtx& c, int S, int T, uint64_t kt) {
     const int ls = c.level[S];
     const int self = S == T ? ls : common_levels(c.pixel[S] << (2 * (kOrder - ls)), kt);
-    return (uint64_t)(ls - self + 32) << 57 | (uint64_t)(uint32_t)c.first[S] << 26;
+    return act_order_key(ls - self + 32, c.first[S]);  // 2 .. 61
 }
 
 // the 64-bit value of lane j (uniform) in scalar registers
@@ -790,7 +790,7 @@ __global__ void __launch_bounds__(kLongThreads) k_near_long(NearCtx c, const int
         for (int base = 0; base < n; base += kLongThreads) {
             const int e = base + tid;
             const bool live = e < n;
-            const int S = live ? praw[k0 + (ORDERED ? (int)(key[e] & 0x3ffffff) : e)] : 0;
+            const int S = live ? praw[k0 + (ORDERED ? act_place(key[e]) : e)] : 0;
             const bool far = act_far(c, live, S, t, t0, nt), near = live && !far;
             const uint64_t mn = __ballot(near), mf = __ballot(far);
             if (lane == 0) {

@@ -606,6 +606,13 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     P.ntl_all = h[2];
     P.n_order = h[3];
     P.n_m2l_fp64 = h[5];
+    // the precision tier orders its direct acts by keys that hold an entry's place
+    if (P.opt.precision == SFMM_FP32_MIXED && n_p2p > 1 << kActIndexBits) {
+        std::vector<int> off_h((size_t)nb + 1);
+        SFMM_HIP(hipMemcpyAsync(off_h.data(), P.p2p_off.data(), sizeof(int) * off_h.size(), hipMemcpyDeviceToHost, s));
+        SFMM_HIP(hipStreamSynchronize(s));
+        if (!ordered_lists_fit(off_h.data(), nb)) throw Error(ST_INVALID_ARG, "interaction lists too large");
+    }
     // target box of every entry: the per-pair order policies need it
     const bool ent = P.opt.order_policy != SFMM_ORDER_FIXED;
     DVec<int> praw;

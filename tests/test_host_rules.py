@@ -94,3 +94,17 @@ def test_no_exception_leaves_a_c_entry():
     assert len(tried) >= 19
     for e in tried:
         assert re.search(r"\n    \} catch \(const Error& e\) \{\n.*\n    \} catch \(const std::exception& e\) \{", e), e[:60]
+
+
+def test_places_of_long_ordered_lists(host_rules):
+    """The precision tier's direct acts are sorted by keys that end in an entry's
+    place in its list: places of more than 26 bits ran into the source's first
+    particle.  Keys ascend with (round, first particle), and longer lists than
+    the places hold are refused."""
+    rng = random.Random(9)
+    firsts = sorted({rng.randrange(2**31) for _ in range(300)} | {0, 1, 2**31 - 1})
+    rows = [(r, f, rng.choice([0, 2**26 - 1, 2**26, 2**27 - 1, rng.randrange(2**27)])) for r in (2, 31, 32, 61) for f in firsts]
+    out = _run(host_rules, "actkey", "".join("%d %d %d\n" % r for r in rows))
+    for (_, _, e), line in zip(rows, out):
+        assert [int(x) for x in line.split()] == [e, 1]
+    assert out[len(rows)].split() == ["1", "0"]
