@@ -25,11 +25,10 @@ sys.path.insert(0, ROOT)
 PEAK_FP64_TFLOPS = 78.6      # MI355X FP64 vector (and FP64 matrix) peak
 PEAK_HBM_GBS = 8000.0
 # FP64 flops of one particle-target pair as the pair loop executes them (FMA
-# = 2): 3 for d, 5 for |d|^2, ~23 for log|d|^2 (range reduction, table entry,
-# degree-7 series), 8 for 1/|d|^2 (hardware estimate + 2 Newton steps), 1 for
-# q/|d|^2, 8 for the four accumulations; the VALU counters read 7.27e10 FP64
-# flops for 1.52e9 pairs on clustered-1e7
-FLOP_PER_P2P_PAIR = 48
+# = 2): 3 for d, 5 for |d|^2, 16 for log|d|^2 (table entry, degree-5 series, log 2
+# in two words), 8 for 1/|d|^2 (the table's estimate, one step of third order),
+# 1 for q/|d|^2, 8 for the four accumulations
+FLOP_PER_P2P_PAIR = 41
 
 
 # Source files of each timed kernel: the traffic measured by the counters is
@@ -40,7 +39,8 @@ KERNEL_SOURCES = {
     "m2p": ["k_p2p.hip", "expand.hpp", "common.hpp"],
 }
 KERNEL_NAMES = {"m2l": "k_m2l_team", "p2p": "k_p2p", "m2p": "k_m2p"}
-M2L_TEAM2_MIN_BOXES = 65536  # the library's switch to two-lane M2L teams (boxes)
+M2L_ROW_MAX_BOXES = 81920  # the library's switch to two-lane M2L teams: above this many boxes with targets
+SAMPLE_SORT_PAIRS = (8192, 10 << 20)  # pairs that are split into buckets which LDS sorts (above 8,192)
 
 
 def source_hash(stage: str) -> str:
@@ -274,7 +274,7 @@ def main():
         bound, flops, peak, unit = work[dom]
         achieved = flops / (stages_ms[dom] * 1e-3) / 1e12
         kname = KERNEL_NAMES[dom]
-        if dom == "m2l" and stats["boxes_executed"] >= M2L_TEAM2_MIN_BOXES:
+        if dom == "m2l" and stats["boxes_executed"] > M2L_ROW_MAX_BOXES:
             kname = "k_m2l_team2"  # two lanes per target box on large trees
         roofline = {"kernel": kname, "bound": bound, "achieved": achieved, "peak": peak, "unit": unit,
                     "frac": achieved / peak, "traffic": measured_traffic(args.workload, dom),
@@ -292,10 +292,13 @@ def main():
         kernels["l2p"] = {"bound": "hbm", "achieved": round(a_, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                           "frac": round(a_ / PEAK_HBM_GBS, 4), "ms": stages_ms["l2p"]}
         # the source keys and sort stage: per point 24 B of coordinates in,
-        # 12 B of key and index out, 8 radix passes of 8 bits over the 62-bit
-        # keys (12 B read and written each), and the gather of the 32-byte
-        # sorted records (read and written)
-        sort_bytes = N * (36 + 8 * 24 + 64)
+        # 12 B of key and index out, the sort, and the gather of the 32-byte
+        # sorted records (read and written).  Sort: one pass in LDS (12 B read
+        # and written), or the split (8 B read and 2 B of bucket number written,
+        # 14 B read and 12 B written) and that pass per bucket, or 8 radix
+        # passes of 8 bits over the 62-bit keys
+        lo, hi = SAMPLE_SORT_PAIRS
+        sort_bytes = N * (36 + (24 if N <= lo else 60 if N <= hi else 8 * 24) + 64)
         a_ = sort_bytes / (stages_ms["src_keys_sort"] * 1e-3) / 1e9
         kernels["sort"] = {"bound": "hbm", "achieved": round(a_, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                            "frac": round(a_ / PEAK_HBM_GBS, 4), "ms": stages_ms["src_keys_sort"]}

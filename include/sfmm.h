@@ -264,11 +264,14 @@ sfmm_status sfmm_execute_noalloc(sfmm_plan_t plan, double* psi, double* defl, vo
  *   `stream`, so that one shell's latency-bound stretches overlap another's
  *   kernels.  The first call (and any call with other output pointers or
  *   another stream than the one before) runs every shell directly; the second
- *   records the same work in a HIP graph (the streams become its parallel
- *   branches) and launches it; later calls replay the graph: one launch for
- *   all shells.  Batches with the bound or learned order policy are run
- *   directly every time (their per-order split reads sizes on the host).  With
- *   the null stream the call returns when the work is done.
+ *   does so again and, while the GPU works, records the same work in a HIP
+ *   graph (the streams become its parallel branches); from the third on the
+ *   graph is replayed: one launch for all shells.  On a stream that is being
+ *   captured the caller's graph takes the pass itself, after a direct call with
+ *   the same outputs (otherwise SFMM_ERR_INVALID_ARG).  Batches with the bound
+ *   or learned order policy are run directly every time (their per-order split
+ *   reads sizes on the host).  With the null stream the call returns when the
+ *   work is done.
  * sfmm_batch_plan_at: the plan of shell i, owned by the batch (never to be
  *   destroyed by the caller; it may be executed directly, ordered with the
  *   batch's own calls).

@@ -495,8 +495,8 @@ class _PlanView(Plan):
 
 class Batch:
     """Several independent spheres (shells) planned together; execute() runs
-    all of them, from the second call with the same outputs as a recorded HIP
-    graph (sfmm_batch_plan / sfmm_batch_execute)."""
+    all of them, from the third call with the same outputs as a HIP graph that
+    the second one recorded (sfmm_batch_plan / sfmm_batch_execute)."""
 
     def __init__(self, srcs, qs, tgts, **options):
         import torch

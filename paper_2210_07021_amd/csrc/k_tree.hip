@@ -1,6 +1,7 @@
 // Tree build on the GPU: order-29 HEALPix keys (Sec. 3.1), the adaptive
-// quasi-quad-tree level by level, box geometry (Sec. 3.5), target location
-// (Sec. 3.7), and the frontier form of Algorithm 1 (Sec. 3.4).
+// quasi-quad-tree from the common prefixes of the sorted keys, all levels at
+// once, target location (Sec. 3.7), and the frontier form of Algorithm 1 (Sec.
+// 3.4) that makes the full lists of the exports and statistics.
 #include "common.hpp"
 #include "geom.hpp"
 

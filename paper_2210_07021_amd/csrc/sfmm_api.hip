@@ -1,6 +1,6 @@
 // Host driver of libsfmm and its C ABI (include/sfmm.h).  All device work
-// is ordered on the caller's stream; the plan reads back only a few counts
-// (per tree level and per walk round) to size the next step.
+// is ordered on the caller's stream; the plan reads back the sizes of the tree,
+// of the lists and of the near field's items, a wait each, to size what follows.
 #include "../../include/sfmm.h"
 #include "common.hpp"
 
