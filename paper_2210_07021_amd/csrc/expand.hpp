@@ -119,12 +119,50 @@ struct LogPoly {
 };
 constexpr LogPoly kLogPoly = {1.0 / 5.0, -0.25, 1.0 / 3.0, 6.93147180369123816490e-01, 1.90821492927058770002e-10};
 constexpr int kLogTab = 512;
-// (log, not log_f64: an error of the entry is one of every value near c_j)
-SFMM_HD double2 log_tab_entry(int j) {
-    const double c = 0.5 + (j + 0.5) / 1024.0;
-    const double ci = 1.0 / c;
-    return make_double2(ci, -log(ci));
+// The table {1/c_j, -log(1/c_j)}, made by the compiler: an error of an entry is
+// one of every value near c_j, so the logs are correctly rounded (with log_f64's
+// they were up to an ulp off).  log c_j in two doubles, c_j = (1025 + 2 j)/2048:
+// from log(1025/1024) - log 2 on, log((n + 2)/n) = 2 atanh(1/(n + 1)) a step;
+// less ci c - 1 for the rounded ci = 1/c.
+struct LogTab {
+    double e[2 * kLogTab];
+};
+constexpr LogTab make_log_tab() {
+    struct Two {
+        double hi, lo;
+        constexpr void add(double x) {
+            const double s = hi + x, b = s - hi;
+            lo += (hi - (s - b)) + (x - b);
+            hi = s;
+        }
+        constexpr void add_2atanh_inv(double m) {  // 2 atanh(1/m), m > 1000
+            const double x = 1.0 / m, x2 = x * x;
+            lo += 2.0 * (-prod_less_1(x, m) / m) + 2.0 * x * x2 * (1.0 / 3.0 + x2 * (1.0 / 5.0 + x2 / 7.0));
+            add(2.0 * x);
+        }
+        static constexpr double prod_less_1(double a, double b) {  // a b - 1 for a b near 1 (Dekker's product)
+            const double ca = 134217729.0 * a, cb = 134217729.0 * b;
+            const double ah = ca - (ca - a), al = a - ah, bh = cb - (cb - b), bl = b - bh, p = a * b;
+            return (p - 1.0) + (((ah * bh - p) + ah * bl + al * bh) + al * bl);
+        }
+    };
+    LogTab t{};
+    Two l{-6.93147180559945286227e-01, -2.31904681384629955842e-17};  // -log 2
+    l.add_2atanh_inv(2049.0);
+    for (int j = 0; j < kLogTab; ++j) {
+        const double c = (1025.0 + 2.0 * j) / 2048.0, ci = 1.0 / c;
+        t.e[2 * j] = ci;
+        t.e[2 * j + 1] = l.hi + (l.lo - Two::prod_less_1(ci, c));
+        l.add_2atanh_inv(1026.0 + 2.0 * j);
+    }
+    return t;
 }
+#if defined(__HIP_DEVICE_COMPILE__)
+static __device__ const LogTab kLogTabData = make_log_tab();
+#else
+static constexpr LogTab kLogTabData = make_log_tab();
+#endif
+SFMM_HD double2 log_tab_entry(int j) { return make_double2(kLogTabData.e[2 * j], kLogTabData.e[2 * j + 1]); }
 
 // the table entry of a mantissa m in [1/2, 1) whose high word is hi (of the
 // argument itself it would be another one's where that is subnormal)

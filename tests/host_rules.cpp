@@ -13,6 +13,7 @@
 //            from the sort key of an ordered direct-act list and whether the
 //            rows' keys ascend; then the longest list that is taken (1) and
 //            the next one (0)
+//   logtab : prints the entries of the pair loop's table
 //   log    : reads x, prints the pair loop's log of x and 1/x
 //   logerr : largest and root mean square errors of the pair loop's log (in
 //            max(1, |log x|)) and reciprocal (relative), against long double,
@@ -92,6 +93,10 @@ int main(int argc, char** argv) {
         }
         const int fits[4] = {0, 5, 5 + (1 << kActIndexBits), 6 + (1 << kActIndexBits)}, too[3] = {0, 0, 1 + (1 << kActIndexBits)};
         printf("%d %d\n", ordered_lists_fit(fits, 3) ? 1 : 0, ordered_lists_fit(too, 2) ? 1 : 0);
+        return 0;
+    }
+    if (!strcmp(argv[1], "logtab")) {
+        for (int j = 0; j < kLogTab; ++j) printf("%a %a\n", log_tab_entry(j).x, log_tab_entry(j).y);
         return 0;
     }
     if (!strcmp(argv[1], "log")) {

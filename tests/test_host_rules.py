@@ -6,6 +6,7 @@ import random
 import re
 import shutil
 import subprocess
+from decimal import Decimal, getcontext
 
 import pytest
 
@@ -108,3 +109,12 @@ def test_places_of_long_ordered_lists(host_rules):
     for (_, _, e), line in zip(rows, out):
         assert [int(x) for x in line.split()] == [e, 1]
     assert out[len(rows)].split() == ["1", "0"]
+
+
+def test_log_table_is_correctly_rounded(host_rules):
+    getcontext().prec = 50
+    for j, line in enumerate(_run(host_rules, "logtab")[:-1]):
+        ci, nl = (float.fromhex(t) for t in line.split())
+        assert ci == 1.0 / (0.5 + (j + 0.5) / 1024)
+        assert nl == float(-Decimal(ci).ln()), j
+    assert j == 511
