@@ -389,9 +389,9 @@ int32_t sfmm_order_for_tolerance(double tol);
  * stage with HIP events on the caller's stream and, at the end of the call,
  * synchronises the stream and adds the elapsed times to process-wide
  * per-stage totals.  Stages (indices into the arrays of sfmm_profile_read):
- *   0 source keys+sort, 1 tree levels, 2 box geometry, 3 walk (Algorithm 1),
- *   4 list sort/CSR, 5 target keys+sort+locate and the split of the
- *   direct-act lists into direct sums and expansions, 6 P2M, 7 M2M (all levels),
+ *   0 source keys+sort, 1 tree, 2 box geometry, 3 walk (Algorithm 1, lists
+ *   included), 4 split of the direct-act lists into direct sums and expansions,
+ *   work items, M2L order, 5 target keys+sort+locate, 6 P2M, 7 M2M (all levels),
  *   8 M2L, 9 L2L (all levels), 10 L2P, 11 P2P (direct part of the close
  *   leaves), 12 close leaves evaluated by their multipole expansion.
  * ms[SFMM_NUM_STAGES] receives the summed milliseconds and calls[] the number
