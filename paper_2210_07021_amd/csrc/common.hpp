@@ -332,10 +332,11 @@ void group_walk_level(const GroupCtx& w, const GroupOut& o, int box0, int box1, 
 void group_walk_count(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t s);
 void group_walk_fill(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t s);
 // the leaves with targets as a list tl, the CSR ends moff[nbox] and
-// poff[nbox], and out[0..5] (host memory): the totals of the four counts,
-// *dmax, and the boxes with targets before box lc1
+// poff[nbox], and out[0..6] (host memory): the totals of the four counts,
+// *dmax, the boxes with targets before box lc1, and 1 in out[6] (0 before) if
+// some leaf has more than kOneGroupList direct acts (pcnt)
 void target_leaves(const int* tflag, const int* toff, const int* noff, int nbox, int lc1, const int* tot,
-                   const int* dmax, int* tl, int* moff, int* poff, int* out, hipStream_t s);
+                   const int* dmax, const int* pcnt, int* tl, int* moff, int* poff, int* out, hipStream_t s);
 // 8-bit sort keys of the boxes with targets: levels <= lc first, then the
 // others; most team rounds first within each part (tw_coarse or tw_fine pairs
 // a round), so the teams of a wave run the same number of rounds.  The sort is
@@ -353,25 +354,22 @@ struct NearCtx {
     const double *tx, *ty, *tz;
     const double* hfar;  // [nb] a close leaf farther than this from every target goes through its expansion
 };
-// Sort key of an ordered list's entry: its round (0 .. 63), the source's first
-// particle (31 bits), and room for the entry's place in the list as it was made
-constexpr int kActIndexBits = 27;
+// Sort key of an ordered list's entry (37 bits): its round (0 .. 63), then the
+// source's first particle.  Above it there is room for the list's number (lists
+// sorted together), or below it for the entry's place (a list of at most
+// kOneGroupList entries, sorted by one workgroup).
+constexpr int kActKeyBits = 37, kActPlaceBits = 64 - kActKeyBits;
+constexpr int kOneGroupList = 7680;
 __host__ __device__ inline uint64_t act_order_key(int round, int first) {
-    return (uint64_t)(uint32_t)round << (31 + kActIndexBits) | (uint64_t)(uint32_t)first << kActIndexBits;
-}
-__host__ __device__ inline int act_place(uint64_t key) { return (int)(key & ((1u << kActIndexBits) - 1)); }
-// whether every list of a CSR over n boxes leaves its places that room
-inline bool ordered_lists_fit(const int* off, int n) {
-    for (int b = 0; b < n; ++b)
-        if (off[b + 1] - off[b] > 1 << kActIndexBits) return false;
-    return true;
+    return (uint64_t)(uint32_t)round << 31 | (uint64_t)(uint32_t)first;
 }
 // Direct-act lists praw (CSR poff) of the ntl leaves tl to psrc: entries summed
 // particle by particle first (nn[T] of them), then those taken through their
 // expansion; ordered: both in the order in which Algorithm 1's frontier walk
-// emits them (the second part backwards)
-void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, const int* poff, const int* praw, int* psrc, int* nn,
-                hipStream_t s);
+// emits them (the second part backwards).  huge: some list has more than
+// kOneGroupList entries (one read-back more, to the host memory pin)
+void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, const int* poff, const int* praw,
+                int* psrc, int* nn, bool huge, int* pin, hipStream_t s);
 // ---------------------------------------------------------------- fmm
 struct FmmCtx {
     int p;

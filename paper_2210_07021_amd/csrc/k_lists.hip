@@ -525,10 +525,13 @@ void group_walk_fill(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t
 // [5] the boxes with targets before box lc1 (the precision tier's FP64 ones).
 __global__ void k_target_leaves(const int* __restrict__ tflag, const int* __restrict__ toff,
                                 const int* __restrict__ noff, int nbox, int lc1, const int* __restrict__ tot,
-                                const int* __restrict__ dmax, int* __restrict__ tl, int* __restrict__ moff,
-                                int* __restrict__ poff, int* __restrict__ out) {
+                                const int* __restrict__ dmax, const int* __restrict__ pcnt, int* __restrict__ tl,
+                                int* __restrict__ moff, int* __restrict__ poff, volatile int* out) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nbox && tflag[b]) tl[toff[b]] = b;
+    if (b < nbox && tflag[b]) {
+        tl[toff[b]] = b;
+        if (pcnt[b] > kOneGroupList) out[6] = 1;
+    }
     if (b == 0) {
         for (int k = 0; k < 4; ++k) out[k] = tot[k];
         out[4] = *dmax;
@@ -539,8 +542,9 @@ __global__ void k_target_leaves(const int* __restrict__ tflag, const int* __rest
 }
 
 void target_leaves(const int* tflag, const int* toff, const int* noff, int nbox, int lc1, const int* tot,
-                   const int* dmax, int* tl, int* moff, int* poff, int* out, hipStream_t s) {
-    k_target_leaves<<<nblk(nbox, 256), 256, 0, s>>>(tflag, toff, noff, nbox, lc1, tot, dmax, tl, moff, poff, out);
+                   const int* dmax, const int* pcnt, int* tl, int* moff, int* poff, int* out, hipStream_t s) {
+    k_target_leaves<<<nblk(nbox, 256), 256, 0, s>>>(tflag, toff, noff, nbox, lc1, tot, dmax, pcnt, tl, moff, poff,
+                                                    out);
     SFMM_LAUNCH_CHECK();
 }
 
@@ -597,7 +601,7 @@ __device__ __forceinline__ uint64_t box_key(const NearCtx& c, int b) {
 __device__ __forceinline__ uint64_t act_key(const NearCtx& c, int S, int T, uint64_t kt) {
     const int ls = c.level[S];
     const int self = S == T ? ls : common_levels(c.pixel[S] << (2 * (kOrder - ls)), kt);
-    return act_order_key(ls - self + 32, c.first[S]);  // 2 .. 61
+    return act_order_key(ls - self + 32, c.first[S]);  // a round of 2 .. 61
 }
 
 // the 64-bit value of lane j (uniform) in scalar registers
@@ -666,20 +670,33 @@ __device__ __forceinline__ bool act_far(const NearCtx& c, bool live, int S, cons
 // An ordered list's keys sit in registers, four to a lane, and every entry's
 // rank is counted against each key in turn.  Longer lists are queued for
 // k_near_long, in two queues of 1 + ntl ints: up to kMidList entries, and more.
+// Lists of more than kOneGroupList entries go to a third one (huge): their
+// entries, their number, then the leaf and the first of its places among the
+// entries of all of them.
 constexpr int kShortRanked = 256, kShortPlain = 512, kMidList = 1024;
 template <bool ORDERED>
 __global__ void __launch_bounds__(256) k_near_short(NearCtx c, const int* __restrict__ tl, int ntl,
                                                     const int* __restrict__ poff, const int* __restrict__ praw,
                                                     int* __restrict__ psrc, int* __restrict__ nn,
-                                                    int* __restrict__ queue) {
+                                                    int* __restrict__ queue, int* __restrict__ huge) {
     const int i = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
     if (i >= ntl) return;  // uniform across the wave
     const int T = tl[i], k0 = poff[T], n = poff[T + 1] - k0;
     if (n > (ORDERED ? kShortRanked : kShortPlain)) {
         if (lane == 0) {
-            int* q = n <= kMidList ? queue : queue + 1 + ntl;
-            q[1 + atomicAdd(q, 1)] = T;
+            if (n > kOneGroupList) {
+                // number and first place together: list j's entries lie behind
+                // those of the lists before it, as the sort by j leaves them
+                const unsigned long long at =
+                    atomicAdd(reinterpret_cast<unsigned long long*>(huge), (1ull << 32) | (unsigned)n);
+                const int j = (int)(at >> 32);
+                huge[2 + 2 * j] = T;
+                huge[3 + 2 * j] = (int)(uint32_t)at;
+            } else {
+                int* q = n <= kMidList ? queue : queue + 1 + ntl;
+                q[1 + atomicAdd(q, 1)] = T;
+            }
         }
         return;
     }
@@ -742,28 +759,26 @@ __global__ void __launch_bounds__(256) k_near_short(NearCtx c, const int* __rest
 }
 
 // Longer lists: a workgroup each (256 threads up to kMidList entries, 1024
-// beyond).  Ordered: the keys (with the entry's place in the raw list) go
-// through a bitonic network in LDS, or in gkeys when a list holds more than CAP
-// entries.  The network keeps the smaller key at
-// the lower place in every comparator (mirrored first step), so places past
-// the end never take part.
+// beyond).  Ordered, up to CAP entries: the keys (with the entry's place in the
+// raw list) go through a bitonic network in LDS.  The network keeps the smaller
+// key at the lower place in every comparator (mirrored first step), so places
+// past the end never take part.
 template <bool ORDERED, int kLongThreads, int CAP>
 __global__ void __launch_bounds__(kLongThreads) k_near_long(NearCtx c, const int* __restrict__ poff,
                                                             const int* __restrict__ praw, int* __restrict__ psrc,
-                                                            int* __restrict__ nn, const int* __restrict__ queue,
-                                                            uint64_t* __restrict__ gkeys) {
-    __shared__ uint64_t skeys[ORDERED ? CAP : 1];
+                                                            int* __restrict__ nn, const int* __restrict__ queue) {
+    __shared__ uint64_t key[ORDERED ? CAP : 1];
     __shared__ int wsum[2][kLongThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t lt = (1ull << lane) - 1;
     const int nl = queue[0];
     for (int j = blockIdx.x; j < nl; j += gridDim.x) {
         const int T = queue[1 + j], k0 = poff[T], n = poff[T + 1] - k0;
-        uint64_t* key = n <= CAP ? skeys : gkeys + k0;
+        const int* raw = praw + k0;
         const WalkRec t = c.rec[T];
         if constexpr (ORDERED) {
             const uint64_t kt = box_key(c, T);
-            for (int e = tid; e < n; e += kLongThreads) key[e] = act_key(c, praw[k0 + e], T, kt) | (uint64_t)e;
+            for (int e = tid; e < n; e += kLongThreads) key[e] = act_key(c, raw[e], T, kt) << kActPlaceBits | (uint64_t)e;
             __syncthreads();
             for (int lk = 1; (1 << (lk - 1)) < n; ++lk) {
                 for (int lh = lk; lh > 0; --lh) {
@@ -790,7 +805,7 @@ __global__ void __launch_bounds__(kLongThreads) k_near_long(NearCtx c, const int
         for (int base = 0; base < n; base += kLongThreads) {
             const int e = base + tid;
             const bool live = e < n;
-            const int S = live ? praw[k0 + (ORDERED ? act_place(key[e]) : e)] : 0;
+            const int S = live ? raw[ORDERED ? (int)(key[e] & ((1u << kActPlaceBits) - 1)) : e] : 0;
             const bool far = act_far(c, live, S, t, t0, nt), near = live && !far;
             const uint64_t mn = __ballot(near), mf = __ballot(far);
             if (lane == 0) {
@@ -813,22 +828,98 @@ __global__ void __launch_bounds__(kLongThreads) k_near_long(NearCtx c, const int
     }
 }
 
+// The huge lists are taken by the whole chip, entry by entry: sort keys (ordered;
+// list j's number above the order's key) and one sort of them all, then the far
+// flags, a scan of these over all lists, and every entry to its place.  By one
+// workgroup each, lists of 1e5 to 2.6e5 entries took 4 ms and more for their
+// network and 16 ms for the flags against 600 targets (1e6 sources of one clump
+// in leaves of 8); here some 0.4 ms each.
+// blockIdx.x: the list; vals null: the entries as they were made
+struct HugeList {
+    int T, base, k0, n;
+};
+__device__ __forceinline__ HugeList huge_list(const int* __restrict__ huge, const int* __restrict__ poff) {
+    const int T = huge[2 + 2 * blockIdx.x], k0 = poff[T];
+    return {T, huge[3 + 2 * blockIdx.x], k0, poff[T + 1] - k0};
+}
+
+__global__ void __launch_bounds__(256) k_huge_keys(NearCtx c, const int* __restrict__ poff,
+                                                   const int* __restrict__ praw, const int* __restrict__ huge,
+                                                   uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    const HugeList l = huge_list(huge, poff);
+    const uint64_t kt = box_key(c, l.T);
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < l.n; e += 256 * gridDim.y) {
+        const int S = praw[l.k0 + e];
+        keys[l.base + e] = (uint64_t)blockIdx.x << kActKeyBits | act_key(c, S, l.T, kt);
+        vals[l.base + e] = (uint32_t)S;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_huge_flags(NearCtx c, const int* __restrict__ poff,
+                                                    const int* __restrict__ praw, const int* __restrict__ huge,
+                                                    const uint32_t* __restrict__ vals, int* __restrict__ far) {
+    const HugeList l = huge_list(huge, poff);
+    const WalkRec t = c.rec[l.T];
+    const int t0 = c.tfirst[l.T], nt = c.tcount[l.T];
+    for (int e0 = blockIdx.y * 256; e0 < l.n; e0 += 256 * gridDim.y) {  // uniform across the workgroup
+        const int e = e0 + threadIdx.x;
+        const bool live = e < l.n;
+        const int S = !live ? 0 : vals ? (int)vals[l.base + e] : praw[l.k0 + e];
+        const bool f = act_far(c, live, S, t, t0, nt);
+        if (live) far[l.base + e] = f ? 1 : 0;
+    }
+}
+
+// before [ne + 1]: far entries before each one of all the lists', then their number
+__global__ void __launch_bounds__(256) k_huge_place(const int* __restrict__ poff, const int* __restrict__ praw,
+                                                    const int* __restrict__ huge, const uint32_t* __restrict__ vals,
+                                                    const int* __restrict__ far, const int* __restrict__ before,
+                                                    int* __restrict__ psrc, int* __restrict__ nn) {
+    const HugeList l = huge_list(huge, poff);
+    const int b0 = before[l.base];
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < l.n; e += 256 * gridDim.y) {
+        const int S = vals ? (int)vals[l.base + e] : praw[l.k0 + e], bf = before[l.base + e] - b0;
+        psrc[l.k0 + (far[l.base + e] ? l.n - 1 - bf : e - bf)] = S;
+    }
+    if (blockIdx.y == 0 && threadIdx.x == 0) nn[l.T] = l.n - (before[l.base + l.n] - b0);
+}
+
+static void huge_lists(const NearCtx& c, bool ordered, const int* poff, const int* praw, const int* huge, int nh, int ne,
+                       int* psrc, int* nn, hipStream_t s) {
+    const dim3 g(nh, (unsigned)std::max(1, std::min(1024, 8192 / nh)));
+    DVec<uint64_t> keys;
+    DVec<uint32_t> vals;
+    if (ordered) {
+        int bits = kActKeyBits;
+        while (nh - 1 >> (bits - kActKeyBits)) ++bits;
+        keys.resize(ne);
+        vals.resize(ne);
+        k_huge_keys<<<g, 256, 0, s>>>(c, poff, praw, huge, keys.data(), vals.data());
+        SFMM_LAUNCH_CHECK();
+        radix_sort_u64(keys.data(), vals.data(), ne, bits, s);
+    }
+    DVec<int> far, before;
+    far.resize(ne);
+    before.resize((size_t)ne + 1);
+    k_huge_flags<<<g, 256, 0, s>>>(c, poff, praw, huge, vals.data(), far.data());
+    SFMM_LAUNCH_CHECK();
+    scan_excl_i32(far.data(), before.data(), ne, before.data() + ne, s);
+    k_huge_place<<<g, 256, 0, s>>>(poff, praw, huge, vals.data(), far.data(), before.data(), psrc, nn);
+    SFMM_LAUNCH_CHECK();
+}
+
 void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, const int* poff, const int* praw,
-                int* psrc, int* nn, hipStream_t s) {
+                int* psrc, int* nn, bool huge, int* pin, hipStream_t s) {
     if (ntl <= 0 || np <= 0) return;
-    DVec<int> queue;
-    DVec<uint64_t> gkeys;
+    DVec<int> queue, qhuge;
     queue.resize(2 * ((size_t)ntl + 1));
+    qhuge.resize(2 + 2 * (size_t)std::min(ntl, np / (kOneGroupList + 1)));
     int* qmid = queue.data();
     int* qlong = qmid + ntl + 1;
-    zero_runs({qmid, sizeof(int)}, {qlong, sizeof(int)}, {nullptr, 0}, s);
+    zero_runs({qmid, sizeof(int)}, {qlong, sizeof(int)}, {qhuge.data(), 2 * sizeof(int)}, s);
     const unsigned g = nblk(64 * (int64_t)ntl, 256);
-    if (ordered) {
-        gkeys.resize(np);
-        k_near_short<true><<<g, 256, 0, s>>>(c, tl, ntl, poff, praw, psrc, nn, qmid);
-    } else {
-        k_near_short<false><<<g, 256, 0, s>>>(c, tl, ntl, poff, praw, psrc, nn, qmid);
-    }
+    if (ordered) k_near_short<true><<<g, 256, 0, s>>>(c, tl, ntl, poff, praw, psrc, nn, qmid, qhuge.data());
+    else k_near_short<false><<<g, 256, 0, s>>>(c, tl, ntl, poff, praw, psrc, nn, qmid, qhuge.data());
     SFMM_LAUNCH_CHECK();
     // at most this many lists hold more than the short kernel takes, and more
     // than kMidList entries
@@ -836,16 +927,20 @@ void near_lists(const NearCtx& c, bool ordered, const int* tl, int ntl, int np, 
     const int nlong = std::min(ntl, np / (kMidList + 1));
     auto launch = [&](auto mid, auto lng) {
         if (nlong > 0) {
-            lng<<<std::min(nlong, 1024), 1024, 0, s>>>(c, poff, praw, psrc, nn, qlong, gkeys.data());
+            lng<<<std::min(nlong, 1024), 1024, 0, s>>>(c, poff, praw, psrc, nn, qlong);
             SFMM_LAUNCH_CHECK();
         }
         if (nmid > 0) {
-            mid<<<std::min(nmid, 4096), 256, 0, s>>>(c, poff, praw, psrc, nn, qmid, gkeys.data());
+            mid<<<std::min(nmid, 4096), 256, 0, s>>>(c, poff, praw, psrc, nn, qmid);
             SFMM_LAUNCH_CHECK();
         }
     };
-    if (ordered) launch(k_near_long<true, 256, kMidList>, k_near_long<true, 1024, 7680>);
+    if (ordered) launch(k_near_long<true, 256, kMidList>, k_near_long<true, 1024, kOneGroupList>);
     else launch(k_near_long<false, 256, 1>, k_near_long<false, 1024, 1>);
+    if (!huge) return;
+    SFMM_HIP(hipMemcpyAsync(pin, qhuge.data(), 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    SFMM_HIP(hipStreamSynchronize(s));
+    if (pin[1] > 0) huge_lists(c, ordered, poff, praw, qhuge.data(), pin[1], pin[0], psrc, nn, s);
 }
 
 }  // namespace sfmm

@@ -559,8 +559,9 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
         scan_excl_i32_n(cnt.data(), off.data(), 4, nb, tot.data(), s);
         SFMM_HIP(hipMemcpyAsync(P.m2l_off.data(), off.data(), sizeof(int) * nb, hipMemcpyDeviceToDevice, s));
         SFMM_HIP(hipMemcpyAsync(P.p2p_off.data(), off.data() + nb, sizeof(int) * nb, hipMemcpyDeviceToDevice, s));
-        target_leaves(o.tflag, toff, noff, nb, P.lvl_start[std::min(lc + 1, nlev)], tot.data(), o.dmax, P.tl.data(),
-                      P.m2l_off.data(), P.p2p_off.data(), h, s);
+        h[6] = 0;
+        target_leaves(o.tflag, toff, noff, nb, P.lvl_start[std::min(lc + 1, nlev)], tot.data(), o.dmax, o.pcnt,
+                      P.tl.data(), P.m2l_off.data(), P.p2p_off.data(), h, s);
         SFMM_HIP(hipStreamSynchronize(s));
     };
     zero_runs({tot.data(), 5 * sizeof(int)}, {big.data(), sizeof(int)}, {nullptr, 0}, s);
@@ -606,13 +607,6 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     P.ntl_all = h[2];
     P.n_order = h[3];
     P.n_m2l_fp64 = h[5];
-    // the precision tier orders its direct acts by keys that hold an entry's place
-    if (P.opt.precision == SFMM_FP32_MIXED && n_p2p > 1 << kActIndexBits) {
-        std::vector<int> off_h((size_t)nb + 1);
-        SFMM_HIP(hipMemcpyAsync(off_h.data(), P.p2p_off.data(), sizeof(int) * off_h.size(), hipMemcpyDeviceToHost, s));
-        SFMM_HIP(hipStreamSynchronize(s));
-        if (!ordered_lists_fit(off_h.data(), nb)) throw Error(ST_INVALID_ARG, "interaction lists too large");
-    }
     // target box of every entry: the per-pair order policies need it
     const bool ent = P.opt.order_policy != SFMM_ORDER_FIXED;
     DVec<int> praw;
@@ -631,7 +625,8 @@ void build_lists(sfmm_plan_impl& P, hipStream_t s, Profiler& prof) {
     P.nn.resize(nb);
     const NearCtx nc{rec.data(),      P.pixel.data(), P.level.data(), P.first.data(), P.tfirst.data(),
                      P.tcount.data(), P.tx.data(),    P.ty.data(),    P.tz.data(),    hfar.data()};
-    near_lists(nc, P.opt.precision == SFMM_FP32_MIXED, P.tl.data(), P.ntl_all, n_p2p, P.p2p_off.data(), praw.data(), P.p2p_src.data(), P.nn.data(), s);
+    near_lists(nc, P.opt.precision == SFMM_FP32_MIXED, P.tl.data(), P.ntl_all, n_p2p, P.p2p_off.data(), praw.data(),
+               P.p2p_src.data(), P.nn.data(), h[6] != 0, h + 8, s);
     const int segn = P.opt.near_segment > 0 ? P.opt.near_segment : kSegNear;
     const int segf = P.opt.far_segment > 0 ? P.opt.far_segment : far_segment(P.ntl_all, P.M);
     // short segments of our own choice stay within 64 MB of partial slots and

@@ -10,9 +10,9 @@
 //            steers for the largest stack and then goes depth first (per
 //            number of waves)
 //   actkey : reads "round first place" rows, prints the place that comes back
-//            from the sort key of an ordered direct-act list and whether the
-//            rows' keys ascend; then the longest list that is taken (1) and
-//            the next one (0)
+//            from a list's sort key and whether the rows' keys ascend; then the
+//            bits that are left for a list's number above the order's key, and
+//            1 if a place of the longest list of one workgroup has room below
 //   logtab : prints the entries of the pair loop's table
 //   log    : reads x, prints the pair loop's log of x and 1/x
 //   logerr : largest and root mean square errors of the pair loop's log (in
@@ -87,12 +87,11 @@ int main(int argc, char** argv) {
         long r, f, e;
         uint64_t last = 0;
         while (scanf("%ld %ld %ld", &r, &f, &e) == 3) {
-            const uint64_t k = act_order_key((int)r, (int)f) | (uint64_t)e;
-            printf("%d %d\n", act_place(k), k > last ? 1 : 0);
+            const uint64_t k = act_order_key((int)r, (int)f) << kActPlaceBits | (uint64_t)e;
+            printf("%d %d\n", (int)(k & ((1u << kActPlaceBits) - 1)), k > last ? 1 : 0);
             last = k;
         }
-        const int fits[4] = {0, 5, 5 + (1 << kActIndexBits), 6 + (1 << kActIndexBits)}, too[3] = {0, 0, 1 + (1 << kActIndexBits)};
-        printf("%d %d\n", ordered_lists_fit(fits, 3) ? 1 : 0, ordered_lists_fit(too, 2) ? 1 : 0);
+        printf("%d %d\n", 64 - kActKeyBits, kOneGroupList <= 1 << kActPlaceBits ? 1 : 0);
         return 0;
     }
     if (!strcmp(argv[1], "logtab")) {

@@ -97,18 +97,19 @@ def test_no_exception_leaves_a_c_entry():
         assert re.search(r"\n    \} catch \(const Error& e\) \{\n.*\n    \} catch \(const std::exception& e\) \{", e), e[:60]
 
 
-def test_places_of_long_ordered_lists(host_rules):
-    """The precision tier's direct acts are sorted by keys that end in an entry's
-    place in its list: places of more than 26 bits ran into the source's first
-    particle.  Keys ascend with (round, first particle), and longer lists than
-    the places hold are refused."""
+def test_sort_keys_of_ordered_lists(host_rules):
+    """The precision tier's direct acts are ordered by (round, first particle); a
+    list's place below that key or a list's number above it has room of its own.
+    (26 bits for the place once ran into the first particle in lists of 2^26.)"""
     rng = random.Random(9)
     firsts = sorted({rng.randrange(2**31) for _ in range(300)} | {0, 1, 2**31 - 1})
-    rows = [(r, f, rng.choice([0, 2**26 - 1, 2**26, 2**27 - 1, rng.randrange(2**27)])) for r in (2, 31, 32, 61) for f in firsts]
+    rows = [(r, f, rng.choice([0, 7679, 2**26, 2**27 - 1, rng.randrange(2**27)])) for r in (2, 31, 32, 61) for f in firsts]
     out = _run(host_rules, "actkey", "".join("%d %d %d\n" % r for r in rows))
     for (_, _, e), line in zip(rows, out):
         assert [int(x) for x in line.split()] == [e, 1]
-    assert out[len(rows)].split() == ["1", "0"]
+    # a list of more than 7,680 entries each: fewer than 2^31 / 7681 of them
+    bits, fits = (int(x) for x in out[len(rows)].split())
+    assert 2**bits > 2**31 // 7681 and fits == 1
 
 
 def test_log_table_is_correctly_rounded(host_rules):
