@@ -444,6 +444,7 @@ struct WorkItems {
     const int4 *items = nullptr, *red = nullptr;
     double* part = nullptr;  // [nslot][4]
     int n = 0, nred = 0, nslot = 0;
+    int leaves = 0;  // target leaves of the lists
 };
 // The items of both kinds (direct sums, expansions) in shared buffers
 struct NearWork {

@@ -15,9 +15,9 @@
 //   * every other close leaf is summed particle by particle: k_p2p.
 //
 // k_p2p: a wave (or, where there are few, a workgroup of four) owns one target
-// leaf (or a segment of its list) and takes its targets in groups of ng <= 64, TB targets per lane (two
-// in FP64, one in the precision tier) and teams of L = floor(64 / ceil(ng /
-// TB)) lanes.  The close leaves' particle ranges are concatenated into one
+// leaf (or a segment of its list) and takes its targets in groups of ng <= 64,
+// TB targets per lane (two in FP64, one in the precision tier and for leaves
+// with few targets) and teams of L = floor(64 / ceil(ng / TB)) lanes.  The close leaves' particle ranges are concatenated into one
 // flat index space (wave prefix sum of their counts, 64 entries at a time);
 // each tile of 128 particles is decoded once (binary search by lane shuffles)
 // and staged in LDS, and lane r of a team takes particles r, r + L, ... of the tile.  The partial sums stay in registers
@@ -246,6 +246,7 @@ void build_items(const int* tl, int ntl, const int* off, const int* nn, const in
     out.near.n = pin[0];
     out.near.nslot = pin[1];
     out.near.nred = pin[2];
+    out.near.leaves = out.far.leaves = ntl;
     out.far.items = out.items.data() + n_near;
     out.far.red = out.red.data() + red_near;
     out.far.part = out.part.data() + 4 * (size_t)pin[1];
@@ -582,10 +583,20 @@ __device__ __forceinline__ void tile_pairs(const TileF64& t, const double2* ltab
 //   LDS return path (3 x 16 bytes a pair for the particle and the table entry,
 //   128 bytes a cycle) stays behind the VALU, and ng targets keep
 //   2 floor(64 / ceil(ng / 2)) lanes busy where teams of floor(64 / ng) left
-//   up to half of them idle.
+//   up to half of them idle.  Where the leaves have kP2POneTarget targets each
+//   or fewer on average, an item is too short for that: its tiles' latency
+//   counts, one target a lane leaves room for a fifth wave per SIMD, and a
+//   grid of kP2POneGrid workgroups makes the table fewer times (us, two
+//   targets without and one with the bounded grid: 1e6 targets in 223,000
+//   leaves 637 and 506; 2e6 in 708,000 leaves 2,216 and 1,703; 2e5 in 126,000
+//   leaves of a clustered sky 523 and 394).  Two targets win from some 9 a
+//   leaf (10.2: 1,634 against 1,717 us; 8.5: 718 against 661), and gain
+//   nothing from the bounded grid (868 and 905 us).
 //   FP32 (precision tier): a target per lane and teams of floor(64 / ng), as
 //   the order of its FP32 tile sums is part of its result.
 constexpr int kP2PFewItems = 4096;
+constexpr int64_t kP2POneTarget = 8;
+constexpr unsigned kP2POneGrid = 4096;
 // waves of a workgroup: the precision tier needs no table, so its one-wave
 // items go one to a workgroup (nothing waits for the longest of four)
 constexpr int p2p_waves(bool f32, int wpi) { return wpi > 1 ? wpi : f32 ? 1 : 4; }
@@ -600,15 +611,18 @@ __device__ __forceinline__ void team_sync() {
     }
 }
 
-template <bool F32, bool HESS, bool NPM, int WPI>
-__global__ void __launch_bounds__(64 * p2p_waves(F32, WPI)) __attribute__((amdgpu_waves_per_eu(HESS || NPM ? 2 : F32 ? 6 : 4)))
+constexpr int p2p_waves_per_simd(bool f32, bool wide, int tb) { return wide ? 2 : f32 ? 6 : tb == 1 ? 5 : 4; }
+
+template <bool F32, bool HESS, bool NPM, int WPI, int TB>
+__global__ void __launch_bounds__(64 * p2p_waves(F32, WPI))
+    __attribute__((amdgpu_waves_per_eu(p2p_waves_per_simd(F32, HESS || NPM, TB))))
 k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restrict__ src,
       const int* __restrict__ tfirst, const int* __restrict__ tcount, const double* __restrict__ tx,
       const double* __restrict__ ty, const double* __restrict__ tz, const uint32_t* __restrict__ tperm,
       double* __restrict__ psi, double* __restrict__ defl, int64_t m_out, double* __restrict__ part, LogPoly lk,
       double* __restrict__ hess, NpmK nk) {
     using Tile = std::conditional_t<F32, TileF32, TileF64>;
-    constexpr int TB = F32 ? 1 : 2, NR = HESS ? 8 : 4, NT = 64 * WPI, kP2PWaves = p2p_waves(F32, WPI);
+    constexpr int NR = HESS ? 8 : 4, NT = 64 * WPI, kP2PWaves = p2p_waves(F32, WPI);
     // a wave's tile and its part of the end-of-group reduction share LDS
     static_assert(sizeof(Tile) >= NR * 64 * sizeof(double), "the reduction fits the tile");
     __shared__ __align__(16) unsigned char sm[sizeof(Tile) * kP2PWaves];
@@ -628,8 +642,10 @@ k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restric
     asm("" : "+v"(lk.c4));
     const int ew = 2 * c.p + 2;
     const double4* __restrict__ spt = c.spt;
-    const int it = WPI > 1 ? blockIdx.x : blockIdx.x * kP2PWaves + wv;
-    if (it < nitems) {  // uniform across the item's team
+    // uniform across the item's team (WPI > 1: one item a workgroup); nitems is
+    // an int, so the last step stays below 2^32
+    for (unsigned it = WPI > 1 ? blockIdx.x : blockIdx.x * kP2PWaves + wv; it < (unsigned)nitems;
+         it += gridDim.x * kP2PWaves) {
         const int4 item = items[it];
         const int T = item.x;
         const int k0 = item.y, K = item.z - item.y;
@@ -895,20 +911,25 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
     // few items: a workgroup each, groups of 64 targets of one leaf side by side
     const bool few = w.n < kP2PFewItems;
     const int pw = p2p_waves(fp32, few ? 4 : 1);
-    const dim3 g(few ? (unsigned)w.n : nblk(w.n, pw), std::max(few ? 2u : 1u, target_groups(m_out, w.n)));
-#define P2P_W(T, H, N, W)                                                                                       \
-    k_p2p<T, H, N, W><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
-                                                   defl, m_out, part, kLogPoly, hess, nk)
-#define P2P_(T, H, N)             \
-    if (few) P2P_W(T, H, N, 4);   \
-    else P2P_W(T, H, N, 1)
+    // leaves with few targets: one target a lane, a bounded grid
+    const bool one = !fp32 && !few && !hess && !npm && m_out <= kP2POneTarget * (int64_t)w.leaves;
+    const unsigned gx = few ? (unsigned)w.n : one ? std::min(nblk(w.n, pw), kP2POneGrid) : nblk(w.n, pw);
+    const dim3 g(gx, std::max(few ? 2u : 1u, target_groups(m_out, w.n)));
+#define P2P_W(T, H, N, W, B)                                                                                 \
+    k_p2p<T, H, N, W, B><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
+                                               defl, m_out, part, kLogPoly, hess, nk)
+#define P2P_(T, H, N)                        \
+    if (few) P2P_W(T, H, N, 4, (T ? 1 : 2)); \
+    else P2P_W(T, H, N, 1, (T ? 1 : 2))
 #define P2P_N(T, H)                  \
     if (npm) {                       \
         P2P_(T, H, true);            \
     } else {                         \
         P2P_(T, H, false);           \
     }
-    if (fp32) {
+    if (one) {
+        P2P_W(false, false, false, 1, 1);
+    } else if (fp32) {
         if (hess) P2P_N(true, true) else P2P_N(true, false)
     } else {
         if (hess) P2P_N(false, true) else P2P_N(false, false)
