@@ -427,11 +427,12 @@ void fmm_m2l_f64_classes(const FmmCtx& c, const int* order, int n, const int* bo
 void fmm_l2l(const FmmCtx& c, int c0, int c1, hipStream_t s);
 // (kappa - kappa_bar, gamma_1, gamma_2, mu) [4][m] from the Hessian [3][m]
 void lensing_from_hessian(const double* hess, int64_t m, double* out, hipStream_t s);
-// hess [3][m_out] (may be null): also the Hessian of Sec. 2.2 in the
-// targets' e_theta, e_phi basis (added, like psi and defl)
+// psi and defl [3][m_out] in the caller's target order: the local expansion and
+// the near field near [4][m] (plan order).  hess [3][m_out] (may be null): also
+// the Hessian of Sec. 2.2 in the targets' e_theta, e_phi basis, with near_hess [3][m]
 void fmm_l2p(const FmmCtx& c, const double* tx, const double* ty, const double* tz, const int* tleaf,
-             const uint32_t* tperm, int64_t m, double psi_shift, double* psi, double* defl, int64_t m_out,
-             hipStream_t s, double* hess = nullptr);
+             const uint32_t* tperm, int64_t m, double psi_shift, const double* near, const double* near_hess,
+             double* psi, double* defl, int64_t m_out, hipStream_t s, double* hess = nullptr);
 // the ratio and particle count from which a close leaf is taken through its
 // expansion at order p (kM2PMinOrder up)
 constexpr int kM2PMinOrder = 12;
@@ -468,17 +469,17 @@ void near_work(const int* count, const int* off, const int* nn, const int* src, 
                long long* pairs, long long* evals, hipStream_t s);
 // fp32: the precision tier's pair arithmetic (two-float coordinates, FP32
 // log / reciprocal, FP64 sums per tile)
+// near [4][m]: psi and alpha of the targets in plan order, added to.
 // part: the partial slots of the split boxes ([w.nslot][4] doubles), or
 // null for the work items' own buffer w.part.  hess (may be null): also add
-// the Hessian of Sec. 2.2 to hess [3][m_out]; part then has [w.nslot][8]
+// the Hessian of Sec. 2.2 to hess [3][m]; part then has [w.nslot][8]
 // doubles and may not be null.
 void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, const int* tfirst,
-             const int* tcount, const double* tx, const double* ty, const double* tz, const uint32_t* tperm,
-             double* psi, double* defl, int64_t m_out, hipStream_t s, double* part = nullptr,
-             double* hess = nullptr);
+             const int* tcount, const double* tx, const double* ty, const double* tz, double* near, int64_t m,
+             hipStream_t s, double* part = nullptr, double* hess = nullptr);
 void fmm_m2p(const FmmCtx& c, const WorkItems& w, const int* src, const int* tfirst, const int* tcount,
-             const double* tx, const double* ty, const double* tz, const uint32_t* tperm, double* psi,
-             double* defl, int64_t m_out, hipStream_t s, double* part = nullptr, double* hess = nullptr);
+             const double* tx, const double* ty, const double* tz, double* near, int64_t m, hipStream_t s,
+             double* part = nullptr, double* hess = nullptr);
 
 // ---------------------------------------------------------------- multi-plane rays
 // A = identity [4][m]; one layer's step of the rays [3][m] by -w defl (along

@@ -444,12 +444,15 @@ void fmm_m2l_f64_classes(const FmmCtx& c, const int* order, int n, const int* bo
     SFMM_LAUNCH_CHECK();
 }
 
-// Local expansion at each target (sorted by leaf), added to psi and alpha in
-// the caller's target order
+// Local expansion at each target (sorted by leaf) and its near field, near
+// [4][m] in that order, to psi and alpha in the caller's order.  Bound by the
+// scattered outputs: adding to what the near field had left there read them
+// back as well (3e6 targets: 467 us, now 320; 1e6: 151 and 107), and the near
+// field's own sums were scattered too (832 and 741 us, leaves of 8).
 template <int P>
 __global__ void __launch_bounds__(128) k_l2p(FmmCtx c, const double* tx, const double* ty, const double* tz,
                                             const int* tleaf, const uint32_t* tperm, int64_t m, double psi_shift,
-                                            double* psi, double* defl, int64_t m_out) {
+                                            const double* near, double* psi, double* defl, int64_t m_out) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= m) return;
     const int L = tleaf[i];
@@ -458,19 +461,20 @@ __global__ void __launch_bounds__(128) k_l2p(FmmCtx c, const double* tx, const d
     double p, ax, ay, az;
     l2p_eval<P>(c.local + (size_t)L * (2 * P + 2), f, rho, tx[i], ty[i], tz[i], &p, &ax, &ay, &az);
     const int64_t o = tperm[i];
-    psi[o] += p + psi_shift;
-    defl[o] += ax;
-    defl[m_out + o] += ay;
-    defl[2 * m_out + o] += az;
+    psi[o] = near[i] + (p + psi_shift);
+    defl[o] = near[m + i] + ax;
+    defl[m_out + o] = near[2 * m + i] + ay;
+    defl[2 * m_out + o] = near[3 * m + i] + az;
 }
 
-// k_l2p that also adds the local expansion's Hessian (Sec. 2.2) to hess
-// [3][m_out] (H_tt, H_tp, H_pp in the target's e_theta, e_phi)
+// k_l2p that also takes the local expansion's Hessian (Sec. 2.2) and the near
+// field's, near_hess [3][m], to hess [3][m_out] (H_tt, H_tp, H_pp in the
+// target's e_theta, e_phi)
 template <int P>
 __global__ void __launch_bounds__(128) k_l2p_hess(FmmCtx c, const double* tx, const double* ty, const double* tz,
                                                  const int* tleaf, const uint32_t* tperm, int64_t m,
-                                                 double psi_shift, double* psi, double* defl, double* hess,
-                                                 int64_t m_out) {
+                                                 double psi_shift, const double* near, const double* near_hess,
+                                                 double* psi, double* defl, double* hess, int64_t m_out) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= m) return;
     const int L = tleaf[i];
@@ -482,13 +486,13 @@ __global__ void __launch_bounds__(128) k_l2p_hess(FmmCtx c, const double* tx, co
     double p, ax, ay, az, h[3];
     l2p_eval_hess<P>(c.local + (size_t)L * (2 * P + 2), f, rho, nx, ny, nz, et, ep, &p, &ax, &ay, &az, h);
     const int64_t o = tperm[i];
-    psi[o] += p + psi_shift;
-    defl[o] += ax;
-    defl[m_out + o] += ay;
-    defl[2 * m_out + o] += az;
-    hess[o] += h[0];
-    hess[m_out + o] += h[1];
-    hess[2 * m_out + o] += h[2];
+    psi[o] = near[i] + (p + psi_shift);
+    defl[o] = near[m + i] + ax;
+    defl[m_out + o] = near[2 * m + i] + ay;
+    defl[2 * m_out + o] = near[3 * m + i] + az;
+    hess[o] = near_hess[i] + h[0];
+    hess[m_out + o] = near_hess[m + i] + h[1];
+    hess[2 * m_out + o] = near_hess[2 * m + i] + h[2];
 }
 
 void fmm_p2m(const FmmCtx& c, int nb, hipStream_t s) {
@@ -551,17 +555,17 @@ bool m2l_f32_tail_supported(int p) { return p >= 5 && p <= 24; }
 
 
 void fmm_l2p(const FmmCtx& c, const double* tx, const double* ty, const double* tz, const int* tleaf,
-             const uint32_t* tperm, int64_t m, double psi_shift, double* psi, double* defl, int64_t m_out,
-             hipStream_t s, double* hess) {
+             const uint32_t* tperm, int64_t m, double psi_shift, const double* near, const double* near_hess,
+             double* psi, double* defl, int64_t m_out, hipStream_t s, double* hess) {
     if (m <= 0) return;
-#define L_(P)                                                                                         \
-    case P:                                                                                           \
-        if (hess)                                                                                     \
-            k_l2p_hess<P><<<nblk(m, 128), 128, 0, s>>>(c, tx, ty, tz, tleaf, tperm, m, psi_shift, psi, \
-                                                       defl, hess, m_out);                            \
-        else                                                                                          \
-            k_l2p<P><<<nblk(m, 128), 128, 0, s>>>(c, tx, ty, tz, tleaf, tperm, m, psi_shift, psi, defl, \
-                                                  m_out);                                             \
+#define L_(P)                                                                                           \
+    case P:                                                                                             \
+        if (hess)                                                                                       \
+            k_l2p_hess<P><<<nblk(m, 128), 128, 0, s>>>(c, tx, ty, tz, tleaf, tperm, m, psi_shift, near, \
+                                                       near_hess, psi, defl, hess, m_out);              \
+        else                                                                                            \
+            k_l2p<P><<<nblk(m, 128), 128, 0, s>>>(c, tx, ty, tz, tleaf, tperm, m, psi_shift, near, psi, \
+                                                  defl, m_out);                                         \
         break;
     SFMM_DISPATCH(c.p, L_)
 #undef L_

@@ -279,10 +279,8 @@ void build_items(const int* tl, int ntl, const int* off, const int* nn, const in
 template <bool HESS>
 __global__ void __launch_bounds__(64) k_near_reduce(const int4* __restrict__ red, const int* __restrict__ tfirst,
                                                    const int* __restrict__ tcount,
-                                                   const uint32_t* __restrict__ tperm,
-                                                   const double* __restrict__ part, double* __restrict__ psi,
-                                                   double* __restrict__ defl, double* __restrict__ hess,
-                                                   int64_t m_out) {
+                                                   const double* __restrict__ part, double* __restrict__ near,
+                                                   double* __restrict__ hess, int64_t m) {
     constexpr int NV = HESS ? 7 : 4, ST = HESS ? 8 : 4;
     const int4 r = red[blockIdx.x];
     const int T = r.x, ns = r.y, base = r.z;
@@ -311,29 +309,28 @@ __global__ void __launch_bounds__(64) k_near_reduce(const int4* __restrict__ red
 #pragma unroll
             for (int k = 0; k < NV; ++k) v[k] += q[k];
         }
-        const int64_t o = tperm[t0 + t];
-        psi[o] += v[0];
-        defl[o] += v[1];
-        defl[m_out + o] += v[2];
-        defl[2 * m_out + o] += v[3];
+        const int64_t o = t0 + t;
+        near[o] += v[0];
+        near[m + o] += v[1];
+        near[2 * m + o] += v[2];
+        near[3 * m + o] += v[3];
         if constexpr (HESS) {
             hess[o] += v[4];
-            hess[m_out + o] += v[5];
-            hess[2 * m_out + o] += v[6];
+            hess[m + o] += v[5];
+            hess[2 * m + o] += v[6];
         }
     }
 }
 
-// psi and alpha contributions of one target: straight to the outputs, or to
-// its slot of the partial buffer
-__device__ __forceinline__ void emit_target(int slot, int64_t o, double ps, double a0, double a1, double a2,
-                                            double* __restrict__ part, double* __restrict__ psi,
-                                            double* __restrict__ defl, int64_t m_out) {
+// psi and alpha contributions of one target: straight to its near field (near
+// [4][m], plan order), or to its slot of the partial buffer
+__device__ __forceinline__ void emit_target(int slot, int64_t i, double ps, double a0, double a1, double a2,
+                                            double* __restrict__ part, double* __restrict__ near, int64_t m) {
     if (slot < 0) {
-        psi[o] += ps;
-        defl[o] += a0;
-        defl[m_out + o] += a1;
-        defl[2 * m_out + o] += a2;
+        near[i] += ps;
+        near[m + i] += a0;
+        near[2 * m + i] += a1;
+        near[3 * m + i] += a2;
     } else {
         double* q = part + 4 * (size_t)slot;
         q[0] = ps;
@@ -344,18 +341,14 @@ __device__ __forceinline__ void emit_target(int slot, int64_t o, double ps, doub
 }
 
 // the same with the Hessian h[3] (slots of 8 doubles)
-__device__ __forceinline__ void emit_target_hess(int slot, int64_t o, double ps, double a0, double a1, double a2,
+__device__ __forceinline__ void emit_target_hess(int slot, int64_t i, double ps, double a0, double a1, double a2,
                                                  const double* h, double* __restrict__ part,
-                                                 double* __restrict__ psi, double* __restrict__ defl,
-                                                 double* __restrict__ hess, int64_t m_out) {
+                                                 double* __restrict__ near, double* __restrict__ hess, int64_t m) {
     if (slot < 0) {
-        psi[o] += ps;
-        defl[o] += a0;
-        defl[m_out + o] += a1;
-        defl[2 * m_out + o] += a2;
-        hess[o] += h[0];
-        hess[m_out + o] += h[1];
-        hess[2 * m_out + o] += h[2];
+        emit_target(-1, i, ps, a0, a1, a2, part, near, m);
+        hess[i] += h[0];
+        hess[m + i] += h[1];
+        hess[2 * m + i] += h[2];
     } else {
         double* q = part + 8 * (size_t)slot;
         q[0] = ps;
@@ -618,9 +611,8 @@ __global__ void __launch_bounds__(64 * p2p_waves(F32, WPI))
     __attribute__((amdgpu_waves_per_eu(p2p_waves_per_simd(F32, HESS || NPM, TB))))
 k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restrict__ src,
       const int* __restrict__ tfirst, const int* __restrict__ tcount, const double* __restrict__ tx,
-      const double* __restrict__ ty, const double* __restrict__ tz, const uint32_t* __restrict__ tperm,
-      double* __restrict__ psi, double* __restrict__ defl, int64_t m_out, double* __restrict__ part, LogPoly lk,
-      double* __restrict__ hess, NpmK nk) {
+      const double* __restrict__ ty, const double* __restrict__ tz, double* __restrict__ near, int64_t m,
+      double* __restrict__ part, LogPoly lk, double* __restrict__ hess, NpmK nk) {
     using Tile = std::conditional_t<F32, TileF32, TileF64>;
     constexpr int NR = HESS ? 8 : 4, NT = 64 * WPI, kP2PWaves = p2p_waves(F32, WPI);
     // a wave's tile and its part of the end-of-group reduction share LDS
@@ -747,12 +739,11 @@ k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restric
                 if constexpr (HESS) {
                     const double h4 = fs[4][tid], h5 = fs[5][tid], h6 = fs[6][tid], h7 = fs[7][tid];
                     const double h[3] = {(h4 - 2.0 * h5) * kInv2Pi, -2.0 * h6 * kInv2Pi, (h4 - 2.0 * h7) * kInv2Pi};
-                    emit_target_hess(slot, tperm[me], (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
-                                     (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, h, part, psi, defl, hess,
-                                     m_out);
+                    emit_target_hess(slot, me, (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
+                                     (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, h, part, near, hess, m);
                 } else {
-                    emit_target(slot, tperm[me], (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
-                                (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, part, psi, defl, m_out);
+                    emit_target(slot, me, (s0 + (1.0 - kLog4) * qn) * kInv4Pi, (s1 - ux * vr) * kInv2Pi,
+                                (s2 - uy * vr) * kInv2Pi, (s3 - uz * vr) * kInv2Pi, part, near, m);
                 }
             }
             team_sync<WPI>();  // fin and the tiles are reused by the next group
@@ -775,8 +766,7 @@ __global__ void __launch_bounds__(64) k_m2p(FmmCtx c, const int4* __restrict__ i
                                            const int* __restrict__ src, const int* __restrict__ tfirst,
                                            const int* __restrict__ tcount, const double* __restrict__ tx,
                                            const double* __restrict__ ty, const double* __restrict__ tz,
-                                           const uint32_t* __restrict__ tperm, double* __restrict__ psi,
-                                           double* __restrict__ defl, int64_t m_out, double* __restrict__ part,
+                                           double* __restrict__ near, int64_t m, double* __restrict__ part,
                                            double* __restrict__ hess) {
     constexpr int EW = 2 * P + 2;
     // the staged records double as the end-of-group reduction buffer
@@ -877,32 +867,27 @@ __global__ void __launch_bounds__(64) k_m2p(FmmCtx c, const int4* __restrict__ i
                 }
             }
             if constexpr (HESS)
-                emit_target_hess(item.w < 0 ? -1 : item.w + tg + lane, tperm[g0 + lane], s0, s1, s2, s3, h, part,
-                                 psi, defl, hess, m_out);
+                emit_target_hess(item.w < 0 ? -1 : item.w + tg + lane, g0 + lane, s0, s1, s2, s3, h, part,
+                                 near, hess, m);
             else
-                emit_target(item.w < 0 ? -1 : item.w + tg + lane, tperm[g0 + lane], s0, s1, s2, s3, part, psi,
-                            defl, m_out);
+                emit_target(item.w < 0 ? -1 : item.w + tg + lane, g0 + lane, s0, s1, s2, s3, part, near, m);
         }
         __syncthreads();  // red is reused by the next group
     }
 }
 
-void reduce_items(const WorkItems& w, const int* tfirst, const int* tcount, const uint32_t* tperm, double* psi,
-                  double* defl, int64_t m_out, double* part, hipStream_t s, double* hess) {
+void reduce_items(const WorkItems& w, const int* tfirst, const int* tcount, double* near, int64_t m, double* part,
+                  hipStream_t s, double* hess) {
     if (w.nred <= 0) return;
-    const dim3 g((unsigned)w.nred, target_groups(m_out, w.nred));
-    if (hess)
-        k_near_reduce<true><<<g, 64, 0, s>>>(w.red, tfirst, tcount, tperm, part, psi, defl,
-                                                            hess, m_out);
-    else
-        k_near_reduce<false><<<g, 64, 0, s>>>(w.red, tfirst, tcount, tperm, part, psi, defl,
-                                                             nullptr, m_out);
+    const dim3 g((unsigned)w.nred, target_groups(m, w.nred));
+    if (hess) k_near_reduce<true><<<g, 64, 0, s>>>(w.red, tfirst, tcount, part, near, hess, m);
+    else k_near_reduce<false><<<g, 64, 0, s>>>(w.red, tfirst, tcount, part, near, nullptr, m);
     SFMM_LAUNCH_CHECK();
 }
 
 void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, const int* tfirst,
-             const int* tcount, const double* tx, const double* ty, const double* tz, const uint32_t* tperm,
-             double* psi, double* defl, int64_t m_out, hipStream_t s, double* part, double* hess) {
+             const int* tcount, const double* tx, const double* ty, const double* tz, double* near, int64_t m,
+             hipStream_t s, double* part, double* hess) {
     if (w.n <= 0) return;
     if (hess && !part && w.nred > 0) throw Error(ST_INTERNAL, "the Hessian needs partial slots of 8 doubles");
     if (!part) part = w.part;
@@ -912,12 +897,12 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
     const bool few = w.n < kP2PFewItems;
     const int pw = p2p_waves(fp32, few ? 4 : 1);
     // leaves with few targets: one target a lane, a bounded grid
-    const bool one = !fp32 && !few && !hess && !npm && m_out <= kP2POneTarget * (int64_t)w.leaves;
+    const bool one = !fp32 && !few && !hess && !npm && m <= kP2POneTarget * (int64_t)w.leaves;
     const unsigned gx = few ? (unsigned)w.n : one ? std::min(nblk(w.n, pw), kP2POneGrid) : nblk(w.n, pw);
-    const dim3 g(gx, std::max(few ? 2u : 1u, target_groups(m_out, w.n)));
-#define P2P_W(T, H, N, W, B)                                                                                 \
-    k_p2p<T, H, N, W, B><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, tperm, psi, \
-                                               defl, m_out, part, kLogPoly, hess, nk)
+    const dim3 g(gx, std::max(few ? 2u : 1u, target_groups(m, w.n)));
+#define P2P_W(T, H, N, W, B)                                                                                   \
+    k_p2p<T, H, N, W, B><<<g, 64 * pw, 0, s>>>(c, w.items, w.n, src, tfirst, tcount, tx, ty, tz, near, m, part, \
+                                               kLogPoly, hess, nk)
 #define P2P_(T, H, N)                        \
     if (few) P2P_W(T, H, N, 4, (T ? 1 : 2)); \
     else P2P_W(T, H, N, 1, (T ? 1 : 2))
@@ -938,29 +923,27 @@ void fmm_p2p(const FmmCtx& c, bool fp32, const WorkItems& w, const int* src, con
 #undef P2P_
 #undef P2P_W
     SFMM_LAUNCH_CHECK();
-    reduce_items(w, tfirst, tcount, tperm, psi, defl, m_out, part, s, hess);
+    reduce_items(w, tfirst, tcount, near, m, part, s, hess);
 }
 
 void fmm_m2p(const FmmCtx& c, const WorkItems& w, const int* src, const int* tfirst, const int* tcount,
-             const double* tx, const double* ty, const double* tz, const uint32_t* tperm, double* psi,
-             double* defl, int64_t m_out, hipStream_t s, double* part, double* hess) {
+             const double* tx, const double* ty, const double* tz, double* near, int64_t m, hipStream_t s,
+             double* part, double* hess) {
     if (w.n <= 0 || c.p < kM2PMinOrder) return;
     if (hess && !part && w.nred > 0) throw Error(ST_INTERNAL, "the Hessian needs partial slots of 8 doubles");
     if (!part) part = w.part;
-    const dim3 g((unsigned)w.n, target_groups(m_out, w.n));
-#define L_(P)                                                                                                 \
-    case P:                                                                                                   \
-        if (hess)                                                                                             \
-            k_m2p<P, true><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz,  \
-                                                        tperm, psi, defl, m_out, part, hess);                 \
-        else                                                                                                  \
-            k_m2p<P, false><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, \
-                                                         tperm, psi, defl, m_out, part, nullptr);             \
+    const dim3 g((unsigned)w.n, target_groups(m, w.n));
+#define L_(P)                                                                                                \
+    case P:                                                                                                  \
+        if (hess) k_m2p<P, true><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, near, m, part, \
+                                                  hess);                                                     \
+        else k_m2p<P, false><<<g, 64, 0, s>>>(c, w.items, src, tfirst, tcount, tx, ty, tz, near, m, part,    \
+                                              nullptr);                                                      \
         break;
     SFMM_DISPATCH(c.p, L_)
 #undef L_
     SFMM_LAUNCH_CHECK();
-    reduce_items(w, tfirst, tcount, tperm, psi, defl, m_out, part, s, hess);
+    reduce_items(w, tfirst, tcount, near, m, part, s, hess);
 }
 
 double npm_constant(double sigma) {

@@ -154,6 +154,8 @@ struct sfmm_plan_impl {
     DVec<double> zrec;  // one zero record (lanes past the end of an FMM-act list)
     DVec<float> multf;  // precision tier: FP32 A-blocks of the multipoles
     DVec<double> hess_part;  // partial slots of 8 doubles (sfmm_execute_hessian)
+    // near field at the targets, psi and alpha [4][M], and its Hessian [3][M] (sfmm_execute_hessian)
+    DVec<double> near, near_hess;
     // per-pair order policies
     DVec<int> m2l_ent;        // target box of every FMM-act entry (per-pair order policies)
     DVec<float> mlp_w;        // order network (learned policy)
@@ -682,6 +684,7 @@ void build_targets(sfmm_plan_impl& P, const DVec<double4>& u, hipStream_t s) {
     P.tx.resize(M);
     P.ty.resize(M);
     P.tz.resize(M);
+    P.near.resize(4 * (size_t)std::max<int64_t>(M, 1));
     P.tleaf.resize(std::max<int64_t>(M, 1));
     P.tfirst.resize(P.nbox);
     P.tcount.resize(P.nbox);
@@ -1015,23 +1018,24 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
     double* far_part = xs ? xs->far_part : nullptr;
     double* near_part = xs ? xs->near_part : nullptr;
     if (hess) {
+        P.near_hess.resize(3 * (size_t)std::max<int64_t>(P.M, 1));
         P.hess_part.resize(8 * ((size_t)std::max(P.work.far.nslot, 1) + (size_t)std::max(P.work.near.nslot, 1)));
         far_part = P.hess_part.data();
         near_part = P.hess_part.data() + 8 * (size_t)std::max(P.work.far.nslot, 1);
     }
+    double* near_hess = hess ? P.near_hess.data() : nullptr;
     // the direct acts need no more than Lemma 1
     auto near_field = [&](hipStream_t ns) {
-        zero_runs({psi, sizeof(double) * (size_t)P.M}, {defl, 3 * sizeof(double) * (size_t)P.M},
-                  {hess, hess ? 3 * sizeof(double) * (size_t)P.M : 0}, ns);
+        zero_runs({P.near.data(), 4 * sizeof(double) * (size_t)P.M},
+                  {near_hess, hess ? 3 * sizeof(double) * (size_t)P.M : 0}, {nullptr, 0}, ns);
         {
             StageScope st(prof, S_M2P);
             fmm_m2p(c, P.work.far, P.p2p_src.data(), P.tfirst.data(), P.tcount.data(), P.tx.data(), P.ty.data(),
-                    P.tz.data(), P.tperm.data(), psi, defl, P.M, ns, far_part, hess);
+                    P.tz.data(), P.near.data(), P.M, ns, far_part, near_hess);
         }
         StageScope st(prof, S_P2P);
         fmm_p2p(c, P.opt.precision == SFMM_FP32_MIXED, P.work.near, P.p2p_src.data(), P.tfirst.data(),
-                P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.tperm.data(), psi, defl, P.M, ns, near_part,
-                hess);
+                P.tcount.data(), P.tx.data(), P.ty.data(), P.tz.data(), P.near.data(), P.M, ns, near_part, near_hess);
     };
     Beside ov;
     near_field(!xs && !prof.on && near_beside(nlev, s) ? ov.fork(s) : s);
@@ -1053,12 +1057,12 @@ void execute_impl(sfmm_plan_impl& P, double* psi, double* defl, hipStream_t s, c
         StageScope st(prof, S_L2L);
         for (int L = 1; L < nlev; ++L) fmm_l2l(c, P.lvl_start[L], P.lvl_start[L + 1], s);
     }
-    // far field at the targets, added to the near one
+    // far and near field at the targets
     ov.end(s);
     {
         StageScope st(prof, S_L2P);
-        fmm_l2p(c, P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), P.tperm.data(), P.M, shift, psi,
-                defl, P.M, s, hess);
+        fmm_l2p(c, P.tx.data(), P.ty.data(), P.tz.data(), P.tleaf.data(), P.tperm.data(), P.M, shift,
+                P.near.data(), near_hess, psi, defl, P.M, s, hess);
     }
     prof.flush();
 }
