@@ -526,11 +526,11 @@ void group_walk_fill(const GroupCtx& w, const GroupOut& o, int nbox, hipStream_t
 __global__ void k_target_leaves(const int* __restrict__ tflag, const int* __restrict__ toff,
                                 const int* __restrict__ noff, int nbox, int lc1, const int* __restrict__ tot,
                                 const int* __restrict__ dmax, const int* __restrict__ pcnt, int* __restrict__ tl,
-                                int* __restrict__ moff, int* __restrict__ poff, volatile int* out) {
+                                int* __restrict__ moff, int* __restrict__ poff, int* __restrict__ out) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < nbox && tflag[b]) {
         tl[toff[b]] = b;
-        if (pcnt[b] > kOneGroupList) out[6] = 1;
+        if (pcnt[b] > kOneGroupList) __hip_atomic_store(out + 6, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (b == 0) {
         for (int k = 0; k < 4; ++k) out[k] = tot[k];
