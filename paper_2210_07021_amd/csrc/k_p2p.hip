@@ -292,9 +292,9 @@ __global__ void __launch_bounds__(64) k_near_reduce(const int4* __restrict__ red
         const double* q = part + ST * ((size_t)base + t);
         const size_t step = ST * (size_t)nt;
         constexpr int U = 8;
+        double x[U][NV];
         int sg = 0;
         for (; sg + U <= ns; sg += U, q += U * step) {
-            double x[U][NV];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -305,9 +305,18 @@ __global__ void __launch_bounds__(64) k_near_reduce(const int4* __restrict__ red
 #pragma unroll
                 for (int k = 0; k < NV; ++k) v[k] += x[u][k];
         }
-        for (; sg < ns; ++sg, q += step) {
+        if (sg < ns) {  // the last fewer than eight, the very last loaded again past the end
 #pragma unroll
-            for (int k = 0; k < NV; ++k) v[k] += q[k];
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < NV; ++k) x[u][k] = q[min(u, ns - 1 - sg) * step + k];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (sg + u >= ns) break;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) v[k] += x[u][k];
+            }
         }
         const int64_t o = t0 + t;
         near[o] += v[0];
@@ -636,8 +645,9 @@ k_p2p(FmmCtx c, const int4* __restrict__ items, int nitems, const int* __restric
     const double4* __restrict__ spt = c.spt;
     // uniform across the item's team (WPI > 1: one item a workgroup); nitems is
     // an int, so the last step stays below 2^32
+    constexpr bool kStrided = !F32 && TB == 1;  // the others' grids hold every item
     for (unsigned it = WPI > 1 ? blockIdx.x : blockIdx.x * kP2PWaves + wv; it < (unsigned)nitems;
-         it += gridDim.x * kP2PWaves) {
+         it = kStrided ? it + gridDim.x * kP2PWaves : ~0u) {
         const int4 item = items[it];
         const int T = item.x;
         const int k0 = item.y, K = item.z - item.y;
